@@ -171,9 +171,16 @@ def timed(g, iters, steps, warmup):
 TUNE_ITERS = 6
 
 
+def grid_plan(g):
+    """The grid's plan with its longest pass as the pass."""
+    p, q = g.plan(), g.pass_info()
+    p.update(steps_per_pass=q["steps"], bytes_per_pass=q["bytes"])
+    return p
+
+
 def pass_gbps(plan, launch_s):
     """Algorithmic GB/s of the grid's own pass: the bytes one pass must move
-    (one sweep, or a pair of steps where the grid runs two steps per pass)
+    (one sweep, or two or four steps where the grid runs that many per pass)
     over the pass's device time; launch_s is the time per iteration."""
     return plan["bytes_per_pass"] / (launch_s * plan["steps_per_pass"]) / 1e9
 
@@ -181,7 +188,7 @@ def pass_gbps(plan, launch_s):
 def grid_leg(n, odf, dtype, exec_, iters, steps, warmup, tile=None, **kw):
     g = make_grid(n, odf=odf, dtype=dtype, exec_=exec_, tile=tile, **kw)
     try:
-        plan = g.plan()
+        plan = grid_plan(g)
         t = timed(g, iters, steps, warmup)
     finally:
         g.close()
@@ -304,7 +311,7 @@ def amr_leg(iters=500, multires_only=False):
     for exec_ in () if multires_only else ("graph", "persistent"):
         g = make_grid(768, blocks=blocks, dtype="f64", exec_=exec_)
         try:
-            plan = g.plan()
+            plan = grid_plan(g)
             t = timed(g, iters, 1, 1)
         finally:
             g.close()
@@ -326,7 +333,7 @@ def amr_leg(iters=500, multires_only=False):
     for exec_ in ("graph", "persistent"):
         g = make_grid(768, blocks=blocks, dtype="f64", exec_=exec_, cell=cell)
         try:
-            plan = g.plan()
+            plan = grid_plan(g)
             t = timed(g, iters, 1, 1)
         finally:
             g.close()
@@ -356,8 +363,8 @@ def imbalance_leg(iters=1000, odfs=(8, 64, 512, 4096, 32768)):
             g = make_grid(1024, odf=odf, dtype="f64", exec_=exec_,
                           tile=mtile if exec_ == "msgdriven" else tile, **imb)
             try:
-                tile = tile or g.plan()["tile"]
-                plan = g.plan()
+                tile = tile or grid_plan(g)["tile"]
+                plan = grid_plan(g)
                 t = timed(g, iters, 1, 0)
             finally:
                 g.close()
@@ -388,7 +395,7 @@ def jacobi2d_leg(n=32768, iters=100, odfs=(1, 4, 16, 64, 256, 1024)):
         for exec_, it, steps in (("graph", iters, 2), ("per_chare", 10 if odf <= 64 else 4, 1)):
             g = od.Grid2D(n, odf=odf, dtype="f64", exec=exec_, tile=tile, hints=1)
             try:
-                plan = g.plan()
+                plan = grid_plan(g)
                 tm = timed(g, it, steps, 1)
             finally:
                 g.close()
@@ -591,7 +598,8 @@ def main():
     roof = {"bound": "hbm", "achieved": round(achieved, 1), "peak": PEAK_HBM_GBPS, "unit": "GB/s",
             "frac": round(achieved / PEAK_HBM_GBPS, 4),
             "traffic": load_traffic(workload) if args.exec in ("graph", "fused") else None,
-            "kernel": (("k_persistent2 (every pass of two fused 7-point steps in one cooperative launch; "
+            "kernel": ("k_deep (four 7-point steps per pass over boxes of the whole grid)" if spp == 4
+                       else ("k_persistent2 (every pass of two fused 7-point steps in one cooperative launch; "
                         "time per pass)" if args.exec == "persistent"
                         else "k_sweep2 (two fused 7-point steps per pass + halo reads)") if spp == 2
                        else KERNEL_OF_EXEC.get(args.exec, args.exec)),

@@ -158,6 +158,12 @@ typedef struct {
      * blocks the tiles are also cut so that every line of cells a pair
      * reads lies in one block.
      * od_plan_info.steps_per_pass tells which is in use.
+     * Bit 14 (OD_FUSED, OD_GRAPH): pairs at most.  By default grids of these
+     * forms that run pairs, with no imbalance and no tile shape fixed by the
+     * caller, run groups of four iterations as one pass where the grid has
+     * at least 64 cells along x and y and x extents and chare origins that are
+     * multiples of 16 bytes (od_pass_info); the values are again the same,
+     * and what is left over of a count runs as pairs and a single sweep.
      * Bit 8 is reserved.  Other bits are ignored. */
     int32_t hints;
     /* 7 (or 0): 3D 7-point stencil.  5: the 2D 5-point stencil of the
@@ -317,7 +323,7 @@ typedef struct {
                                        storage (the buffer od_create_static takes)    */
     int64_t control_bytes;          /* rest of the workspace: descriptors and device
                                        state, for this handle's plan                 */
-    int32_t steps_per_pass;         /* 2: iterations run in pairs (OD_FUSED, OD_GRAPH,
+    int32_t steps_per_pass;         /* of the passes by tiles: 2: iterations run in pairs (OD_FUSED, OD_GRAPH,
                                        OD_PERSISTENT, OD_MSGDRIVEN; hints bit 12);
                                        else 1                                          */
     int64_t bytes_per_pass;         /* algorithmic HBM bytes of one pass: one sweep, or
@@ -325,6 +331,16 @@ typedef struct {
                                        of other chares within two steps' reach)       */
 } od_plan_info;
 od_status od_plan(struct od_grid* g, od_plan_info* info);
+
+/* The longest pass the grid runs: *steps iterations in one pass over the
+ * field (4, 2 or 1; hints bits 12 and 14), *bytes its algorithmic HBM bytes
+ * (bytes_per_pass, or with four steps one read and one write of the field).
+ * Four-step passes cut the whole grid, not each chare, into *count boxes
+ * (0: none): up to cap of them are written to boxes, 10 values each: the
+ * cells [x0, x1), [y0, y1) a workgroup computes, the cells [x0, x1),
+ * [y0, y1), [z0, z1) it writes (global interior coordinates). */
+od_status od_pass_info(struct od_grid* g, int32_t* steps, int64_t* bytes, int32_t* boxes, int32_t cap,
+                       int32_t* count);
 
 /* Per-tile descriptor export for host-side checks (brute-force halo maps):
  * for tile t: its chare, origin in the chare, extent, and for each face

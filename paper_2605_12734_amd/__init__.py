@@ -124,6 +124,18 @@ def plan_info(handle) -> dict:
             "steps_per_pass": info.steps_per_pass, "bytes_per_pass": info.bytes_per_pass}
 
 
+def pass_info(handle) -> dict:
+    """Steps and algorithmic bytes of the grid's longest pass, and the boxes
+    of a four-step pass: rows (computed x0 x1 y0 y1, written x0 x1 y0 y1 z0 z1)."""
+    steps, nbytes, count = ctypes.c_int32(), ctypes.c_int64(), ctypes.c_int32()
+    args = (ctypes.byref(steps), ctypes.byref(nbytes))
+    check(lib().od_pass_info(handle, *args, None, 0, ctypes.byref(count)), "od_pass_info")
+    boxes = np.zeros((count.value, 10), dtype=np.int32)
+    check(lib().od_pass_info(handle, *args, boxes.ctypes.data_as(ctypes.POINTER(ctypes.c_int32)), count.value,
+                             ctypes.byref(count)), "od_pass_info")
+    return {"steps": steps.value, "bytes": nbytes.value, "boxes": boxes}
+
+
 def tile_infos(handle, count: int) -> list:
     out = []
     ti = B.od_tile_info()
@@ -182,6 +194,7 @@ def host_plan(**kw) -> dict:
         info = plan_info(p.h)
         info["tiles"] = tile_infos(p.h, info["ntiles"])
         info["chares"] = chare_boxes(p.h, info["nchares"])
+        info["pass"] = pass_info(p.h)
         if kw.get("exec") == "msgdriven":
             info["deps"] = tile_deps(p.h, info["ntiles"])
         return info
@@ -280,6 +293,9 @@ class Grid:
     # -- introspection ----------------------------------------------------
     def plan(self) -> dict:
         return plan_info(self.h)
+
+    def pass_info(self) -> dict:
+        return pass_info(self.h)
 
     def tiles(self) -> list:
         return tile_infos(self.h, self.plan()["ntiles"])

@@ -193,6 +193,15 @@ bool two_step_room(const Grid& G) {
     return form && !(cfg.hints & 4096) && !p.multires && (!imbalance || cfg.stencil != 5);
 }
 
+// Four steps per pass: the fused and graph forms where they can pair steps,
+// the 3D stencil without imbalance, unless hints bit 14 or a tile shape fixed
+// by the caller (whose passes then run that shape).
+bool deep_possible(const Grid& G) {
+    const od_config& cfg = G.cfg;
+    return (cfg.exec == OD_FUSED || cfg.exec == OD_GRAPH) && cfg.stencil != 5 && !G.plan.multires &&
+           G.imb.heavy == 0 && !(cfg.hints & (4096 | 16384)) && !G.user_tile;
+}
+
 // Block and local coordinates of global cell (x, y, z) as a FaceDev: its
 // chare, or for a cell of the domain's ghost shell the Dirichlet
 // pseudo-block of that face (normal coordinate 0; every cell of it holds
@@ -391,6 +400,7 @@ std::string build_layout(const od_config& cfg, Grid& G) {
             if (c.o[0] % vx != 0)
                 return "explicit block x-origins must be multiples of " + std::to_string(vx) + " for this dtype";
     }
+    G.user_tile = cfg.tile[0] > 0;
     plan_default_tile(cfg, p);
     p.xcd_order = (cfg.hints & 2) == 0;
     // message-driven tiles publish to other XCDs only across group
@@ -642,7 +652,17 @@ std::string build_layout(const od_config& cfg, Grid& G) {
     G.L.dep_idx = cv.take((G.dep_idx.size() + 1) * 4);
     G.L.segs = cv.take(std::max<size_t>(G.segs_h.size(), 1) * sizeof(FillSeg));
     G.L.xexp = cv.take(std::max<size_t>(G.xexp_h.size(), 1) * sizeof(XExpDev));
-    G.L.total = align_up(cv.off, kAlign) + kAlign;
+    G.L.total = G.L.total_pairs = align_up(cv.off, kAlign) + kAlign;
+    // four-step passes, behind everything else (a workspace that ends here
+    // runs pairs): tiles, and per axis the index of each coordinate (x, y, z)
+    // and the first plane behind each plane's blocks
+    G.deep_h.clear();
+    if (deep_possible(G) && G.L.field_end / 16 <= UINT32_MAX) G.deep_h = deep_tiles(p, s);
+    if (!G.deep_h.empty()) {
+        G.L.deep = cv.take(G.deep_h.size() * sizeof(DeepTile));
+        G.L.deep_tab = cv.take((size_t)(p.n[0] + p.n[1] + 2 * p.n[2]) * 4);
+        G.L.total = align_up(cv.off, kAlign) + kAlign;
+    }
     return fill_tile_descs(G);
 }
 
@@ -922,6 +942,31 @@ od_status Grid::upload() {
     if (e == hipSuccess) e = put(L.bc, cfg.bc, 6 * 8);
     if (e == hipSuccess) e = put(L.dep_ptr, dep_ptr.data(), dep_ptr.size() * 4);
     if (e == hipSuccess) e = put(L.dep_idx, dep_idx.data(), dep_idx.size() * 4);
+    std::vector<int32_t> tab;
+    if (!deep_h.empty()) {
+        for (int d = 0; d < 3; ++d)
+            for (int64_t v = 0; v < p.n[d]; ++v) tab.push_back(p.regular ? cidx[d][(size_t)v] : (int32_t)(v / p.gran));
+        const size_t z = (size_t)(p.n[0] + p.n[1]);
+        for (int64_t v = 0; v < p.n[2]; ++v) {
+            int64_t q = v + 1;
+            while (q < p.n[2] && tab[z + (size_t)q] == tab[z + (size_t)v]) ++q;
+            tab.push_back((int32_t)q);
+        }
+        if (e == hipSuccess) e = put(L.deep, deep_h.data(), deep_h.size() * sizeof(DeepTile));
+        if (e == hipSuccess) e = put(L.deep_tab, tab.data(), tab.size() * 4);
+        const int32_t* t = reinterpret_cast<const int32_t*>(cp(L.deep_tab));
+        deep_map.arena = base;
+        deep_map.blocks = reinterpret_cast<const BlockDev*>(cp(L.blocks));
+        deep_map.ix = t;
+        deep_map.iy = t + p.n[0];
+        deep_map.iz = deep_map.iy + p.n[1];
+        deep_map.zn = deep_map.iz + p.n[2];
+        deep_map.owner = p.regular ? nullptr : reinterpret_cast<const int32_t*>(cp(L.owner));
+        deep_map.corigin = reinterpret_cast<const int32_t*>(cp(L.corigin));
+        deep_map.dir_pb = reinterpret_cast<const int32_t*>(cp(L.dir_pb));
+        for (int d = 0; d < 2; ++d) deep_map.k[d] = p.regular ? p.k[d] : (int32_t)p.og[d];
+        for (int d = 0; d < 3; ++d) deep_map.n[d] = (int32_t)p.n[d];
+    }
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) return fail(OD_EHIP, std::string("descriptor upload: ") + hipGetErrorString(e));
 
@@ -1030,6 +1075,17 @@ od_status Grid::fused_two(hipStream_t s2, int par, int64_t step) {
     return OD_OK;
 }
 
+od_status Grid::fused_deep(hipStream_t s2, int par, bool last) {
+    hipError_t e = launch_deep(s, s2, deep_map, reinterpret_cast<const DeepTile*>(cp(L.deep)), (int32_t)deep_h.size(),
+                               par, res_ptr(), 0, 1, mode(), last);
+    if (e != hipSuccess) return fail(OD_EHIP, std::string("four-step sweep launch: ") + hipGetErrorString(e));
+    return OD_OK;
+}
+
+od_status Grid::fused_pass(hipStream_t s2, int par, int64_t step, int k, bool last) {
+    return k == kDeepSteps ? fused_deep(s2, par, last) : (k == 2 ? fused_two(s2, par, step) : fused_one(s2, par, step));
+}
+
 od_status Grid::upload_tiles() {
     hipError_t he = hipMemcpyAsync(cp(L.tiles), tiles_h.data(), tiles_h.size() * sizeof(TileDev),
                                    hipMemcpyHostToDevice, st);
@@ -1056,13 +1112,9 @@ od_status Grid::graph_run(int64_t n) {
             od_status os = OD_OK;
             int par = parity;
             for (int64_t i = 0; i < m && os == OD_OK; par ^= 1) {
-                if (two_step && m - i >= 2) {
-                    os = fused_two(cap_st, par, iters + i);
-                    i += 2;
-                } else {
-                    os = fused_one(cap_st, par, iters + i);
-                    i += 1;
-                }
+                const int k = steps_of(m - i);
+                os = fused_pass(cap_st, par, iters + i, k, i + k == m);
+                i += k;
             }
             e = hipStreamEndCapture(cap_st, &graph);
             if (os != OD_OK) {
@@ -1078,7 +1130,7 @@ od_status Grid::graph_run(int64_t n) {
         }
         hipError_t e = hipGraphLaunch(it->second, st);
         if (e != hipSuccess) return fail(OD_EHIP, std::string("graph launch: ") + hipGetErrorString(e));
-        parity ^= (int)((two_step ? m / 2 + m % 2 : m) & 1);   // one flip per pass
+        for (int64_t i = 0; i < m; parity ^= 1) i += steps_of(m - i);   // one flip per pass
         iters += m;
         n -= m;
     }
@@ -1315,8 +1367,8 @@ od_status Grid::iterate(int64_t n) {
         case OD_FUSED: {
             msg_final = false;
             for (int64_t i = 0; i < n;) {
-                const int k = two_step && n - i >= 2 ? 2 : 1;
-                od_status os = k == 2 ? fused_two(st, parity, iters) : fused_one(st, parity, iters);
+                const int k = steps_of(n - i);
+                od_status os = fused_pass(st, parity, iters, k, i + k == n);
                 if (os != OD_OK) return os;
                 parity ^= 1;
                 iters += k;

@@ -120,6 +120,7 @@ od_status od_create(const od_config* cfg, void* hip_stream, void* dev_workspace,
     if (dev_workspace == nullptr) return fail(OD_EINVAL, "workspace is NULL");
     if (reinterpret_cast<uintptr_t>(dev_workspace) % od::kAlign != 0)
         return fail(OD_EINVAL, "workspace must be 256-byte aligned");
+    if (workspace_bytes < G.L.total) G.drop_deep();
     if (workspace_bytes < G.L.total)
         return fail(OD_ENOMEM, "workspace of " + std::to_string(workspace_bytes) + " bytes, need " +
                                    std::to_string(G.L.total));
@@ -155,6 +156,7 @@ od_status od_create_static(const od_config* cfg, void* hip_stream, void* dev_fie
     G.tune_room = false;   // descriptor room for the planned tiles only
     od_status s = plan_only(cfg, G);
     if (s != OD_OK) return s;
+    if (G.L.total - G.L.ctrl_begin > kStaticControlBytes) G.drop_deep();
     const size_t ctrl_bytes = G.L.total - G.L.ctrl_begin;
     if (ctrl_bytes > kStaticControlBytes)
         return fail(OD_ENOMEM, "grid needs " + std::to_string(ctrl_bytes) +
@@ -311,6 +313,22 @@ od_status od_plan(od_grid* g, od_plan_info* info) {
     info->control_bytes = (int64_t)(G.L.total - G.L.ctrl_begin);
     info->steps_per_pass = G.two_step ? 2 : 1;
     info->bytes_per_pass = G.bytes_per_pass();
+    return OD_OK;
+}
+
+od_status od_pass_info(od_grid* g, int32_t* steps, int64_t* bytes, int32_t* boxes, int32_t cap, int32_t* count) {
+    if (!g || !steps || !bytes || !count || cap < 0 || (cap > 0 && !boxes)) return fail(OD_EINVAL, "NULL argument");
+    const Grid& G = g->g;
+    *steps = G.deep() ? od::kDeepSteps : (G.two_step ? 2 : 1);
+    *bytes = G.deep() ? 2 * (int64_t)G.s * G.plan.interior : G.bytes_per_pass();
+    *count = (int32_t)G.deep_h.size();
+    int ex, ey;
+    od::deep_shape(G.s, &ex, &ey);
+    for (int32_t i = 0; i < *count && i < cap; ++i) {
+        const od::DeepTile& t = G.deep_h[(size_t)i];
+        const int32_t v[10] = {t.xs, t.xs + ex, t.ys, t.ys + ey, t.xo0, t.xo1, t.yo0, t.yo1, t.z0, t.z1};
+        std::copy(v, v + 10, boxes + 10 * (size_t)i);
+    }
     return OD_OK;
 }
 

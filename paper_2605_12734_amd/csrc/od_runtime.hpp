@@ -8,6 +8,7 @@
 #include <utility>
 #include <vector>
 
+#include "deep.hpp"
 #include "kernels.hpp"
 #include "od_internal.hpp"
 
@@ -27,6 +28,8 @@ struct Layout {
     // device state, addressed through Grid::cp (ctrl_begin == field_end)
     size_t ctrl_begin = 0;
     size_t ccell = 0, segs = 0, xpub = 0, xexp = 0, tiles2 = 0;
+    size_t deep = 0, deep_tab = 0;           // four-step passes: tiles, per-axis tables
+    size_t total_pairs = 0;                  // total without them
     size_t pend = 0, qslots = 0, qctl = 0;   // message-driven dependency counters and XCD queues
     size_t stamps = 0;                       // persistent timeline (hints bit 3)
 };
@@ -57,6 +60,18 @@ struct Grid {
     // tiles' extra line descriptors
     bool two_step = false;
     std::vector<Tile2Dev> tiles2_h;
+    // four steps per pass (fused and graph forms, see deep_possible): tiles
+    // (none: pairs at most) and the device-side map
+    std::vector<DeepTile> deep_h;
+    DeepMap deep_map{};
+    bool user_tile = false;          // the caller fixed the tile shape
+    bool deep() const { return !deep_h.empty(); }
+    void drop_deep() {
+        deep_h.clear();
+        L.total = L.total_pairs;
+    }
+    // passes of an iteration count: fours, pairs, singles
+    int steps_of(int64_t left) const { return deep() && left >= kDeepSteps ? kDeepSteps : (two_step && left >= 2 ? 2 : 1); }
     int64_t halo2_cells = 0;         // cells of other chares within two steps of each chare
     std::vector<int32_t> dep_ptr, dep_idx;
     ImbDev imb{};                    // load-imbalance draw (heavy == 0: none)
@@ -154,6 +169,9 @@ struct Grid {
     unsigned long long* res_ptr();
     od_status fused_one(hipStream_t s2, int par, int64_t step);
     od_status fused_two(hipStream_t s2, int par, int64_t step);   // steps step, step + 1: parity par -> par ^ 1
+    od_status fused_deep(hipStream_t s2, int par, bool last);     // kDeepSteps steps: parity par -> par ^ 1
+    // k steps (steps_of); last: the residual is wanted
+    od_status fused_pass(hipStream_t s2, int par, int64_t step, int k, bool last);
     od_status upload_tiles();                      // tile descriptors (and two-step lines) to the device
     int64_t bytes_per_pass() const;
     od_status graph_run(int64_t n);

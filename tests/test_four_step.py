@@ -1,0 +1,168 @@
+"""Four Jacobi steps per pass: the boxes of a pass (host) and its bits (GPU).
+
+The pass cuts the whole grid into boxes of 64 x 64 lanes that cross chares;
+each computes a ring of four cells more than it writes, except at the grid's
+faces.  Everything is compared with the CPU oracle bit for bit."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_2605_12734_amd as od
+import workloads
+
+DT = {"f64": np.float64, "f32": np.float32}
+BC6 = (1.0, 0.5, 0.25, 0.125, 2.0, 3.0)
+RING = 4
+
+
+@pytest.mark.parametrize("dtype,vx", [("f64", 2), ("f32", 4)])
+@pytest.mark.parametrize("n", [(64, 64, 1), (64, 65, 2), (68, 64, 9), (120, 120, 3), (124, 121, 4), (176, 177, 5),
+                               (180, 119, 16), (300, 500, 7), (512, 512, 40), (1000, 66, 1)])
+def test_boxes_write_each_cell_once_and_keep_their_ring(dtype, vx, n):
+    p = od.host_plan(n=n, odf=1, dtype=dtype, exec="graph")["pass"]
+    assert p["steps"] == 4 and p["bytes"] == 2 * (16 // vx) * n[0] * n[1] * n[2]
+    seen = np.zeros((n[2], n[1], n[0]), dtype=np.int8)
+    for cx0, cx1, cy0, cy1, x0, x1, y0, y1, z0, z1 in p["boxes"]:
+        assert cx0 % vx == 0 and x0 % vx == 0 and x1 % vx == 0
+        # the lanes stay in the grid, and no written cell is within the ring's
+        # reach of the cells computed from nothing
+        assert 0 <= cx0 <= x0 < x1 <= cx1 <= n[0] and 0 <= cy0 <= y0 < y1 <= cy1 <= n[1] and 0 <= z0 < z1 <= n[2]
+        assert cx0 == 0 or x0 - cx0 >= RING
+        assert cy0 == 0 or y0 - cy0 >= RING
+        assert cx1 == n[0] or cx1 - x1 >= RING
+        assert cy1 == n[1] or cy1 - y1 >= RING
+        seen[z0:z1, y0:y1, x0:x1] += 1
+    assert (seen == 1).all()
+
+
+@pytest.mark.parametrize("kw,steps", [
+    (dict(n=(64, 64, 8)), 4), (dict(n=(62, 64, 8)), 2), (dict(n=(64, 63, 8)), 2),
+    (dict(n=(65, 64, 8)), 2),                                  # rows end inside a vector
+    (dict(n=(66, 64, 8), dtype="f32"), 2),
+    (dict(n=(66, 64, 64), odf=8), 2),                          # chares start inside a vector
+    (dict(n=(64, 67, 64), odf=8), 4),                          # along y they may start anywhere
+    (dict(n=64, odf=8, exec="persistent"), 2), (dict(n=64, odf=8, exec="msgdriven"), 2),
+    (dict(n=64, odf=8, hints=1 << 14), 2), (dict(n=64, odf=8, hints=1 << 12), 1),
+    (dict(n=64, odf=8, tile=(32, 16, 16)), 2),                 # the caller's tile shape is what runs
+    (dict(n=64, odf=8, exec="fused", imbalance_pct=10, imbalance_max_extra=4), 2),
+])
+def test_which_grids_run_four_steps(kw, steps):
+    kw = dict(dict(odf=1, dtype="f64", exec="graph"), **kw)
+    assert od.host_plan(**kw)["pass"]["steps"] == steps
+
+
+def _same(U, want):
+    if not np.array_equal(U, want):
+        d = np.argwhere(~((U == want) | (np.isnan(U) & np.isnan(want))))
+        if len(d):
+            k, j, i = d[0]
+            raise AssertionError(f"{len(d)} cells differ; first at padded (k,j,i)=({k},{j},{i}): "
+                                 f"{U[k, j, i]!r} vs {want[k, j, i]!r}")
+
+
+def _run(n, odf, dtype, iters, exec_="fused", seed=5, write=None, want_steps=4, **kw):
+    g = od.Grid(n, odf=odf, dtype=dtype, exec=exec_, bc=BC6, seed=seed, hints=1, **kw)
+    try:
+        assert g.pass_info()["steps"] == want_steps
+        if write is not None:
+            g.write(write)
+        for k in iters:
+            g.iterate(k)
+        return g.read(), g.residual()
+    finally:
+        g.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("n,odf", [((64, 64, 1), 1), ((64, 64, 9), 1), ((68, 65, 3), 1), ((120, 121, 4), 1),
+                                   ((124, 120, 5), 1), ((176, 70, 12), 1), ((180, 64, 20), 1), ((128, 72, 64), 64),
+                                   ((64, 67, 30), 8), ((192, 130, 33), 27), ((256, 64, 48), 512)])
+def test_edges_of_boxes_and_chares(dtype, n, odf):
+    want, _, r = oracle.solve(n, DT[dtype], seed=5, iters=8, bc=BC6)
+    U, got = _run(n, odf, dtype, [8])
+    _same(U, want)
+    assert got == r
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("exec_", ["fused", "graph"])
+@pytest.mark.parametrize("iters", [[4], [5], [6], [7], [4, 4], [3, 8, 1, 4], [1, 11]])
+def test_what_is_left_of_a_count(exec_, iters):
+    want, _, r = oracle.solve((128, 64, 24), np.float64, seed=5, iters=sum(iters), bc=BC6)
+    U, got = _run((128, 64, 24), 8, "f64", iters, exec_)
+    _same(U, want)
+    assert got == r
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+def test_uneven_blocks(dtype):
+    n = 128
+    blocks = workloads.octree_blocks(n=n, root=64, min_edge=16, p_refine=0.5, seed=3)
+    want, _, r = oracle.solve(n, DT[dtype], seed=5, iters=9, bc=BC6)
+    U, got = _run(n, 1, dtype, [9], blocks=blocks)
+    _same(U, want)
+    assert got == r
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("field", ["shell", "signs", "tiny", "zeros", "huge"])
+def test_values_the_division_and_the_boundary_can_go_wrong_on(dtype, field):
+    # every shell cell its own value; sums of both signs; sums around and below
+    # the smallest normal number, where the quotient rounds to fewer bits;
+    # zeros of both signs; infinities (whose differences make NaNs)
+    n = (132, 70, 14)
+    rng = np.random.default_rng(7)
+    U = rng.random((n[2] + 2, n[1] + 2, n[0] + 2))
+    info = np.finfo(DT[dtype])
+    if field == "signs":
+        U = U - 0.5
+    elif field == "tiny":
+        U = (U - 0.3) * float(info.tiny) * 2.0 ** rng.integers(-info.nmant, 60, U.shape)
+    elif field == "zeros":
+        U = np.where(U < 0.7, 0.0, -0.0)
+    elif field == "huge":
+        U = np.where(U < 0.0005, np.inf, (U - 0.5) * float(info.max) / 8)
+    U = U.astype(DT[dtype])
+    for a in (0, 1, 2):   # shell edges and corners read back as 0
+        for b in range(a):
+            for i in (0, -1):
+                for j in (0, -1):
+                    at = [slice(None)] * 3
+                    at[a], at[b] = i, j
+                    U[tuple(at)] = 0
+    want, _, r = oracle.jacobi(U.copy(), 8)
+    got, gr = _run(n, 1, dtype, [8], write=U)
+    assert np.array_equal(got.view(np.uint8), want.view(np.uint8)) or field == "huge"
+    _same(got, want)
+    assert gr == r
+
+
+@pytest.mark.gpu
+def test_a_workspace_of_the_pairs_size_runs_pairs():
+    import ctypes
+
+    import torch
+
+    from paper_2605_12734_amd import _binding as B
+
+    kw = dict(n=(128, 64, 24), odf=8, dtype="f64", exec="fused", bc=BC6, seed=5)
+    cfg, _keep = od.make_config(**kw)
+    pairs, _k2 = od.make_config(hints=1 << 14, **kw)
+    size = ctypes.c_size_t()
+    od.check(od.lib().od_workspace_bytes(ctypes.byref(pairs), ctypes.byref(size)), "bytes")
+    ws = torch.empty(size.value, dtype=torch.uint8, device="cuda:0")
+    h = ctypes.c_void_p()
+    od.check(od.lib().od_create(ctypes.byref(cfg), None, ctypes.c_void_p(ws.data_ptr()), size, ctypes.byref(h)),
+             "od_create")
+    try:
+        assert od.pass_info(h)["steps"] == 2
+        od.check(od.lib().od_iterate(h, 8), "od_iterate")
+        r = ctypes.c_double()
+        od.check(od.lib().od_residual(h, ctypes.byref(r)), "od_residual")
+        assert r.value == oracle.solve((128, 64, 24), np.float64, seed=5, iters=8, bc=BC6)[2]
+    finally:
+        od.check(od.lib().od_destroy(h), "od_destroy")
+    assert B.OD_F64 == 8
