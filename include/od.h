@@ -113,7 +113,7 @@ typedef struct {
      * chare); od_extra_sweeps reports the draw.  A re-run recomputes the
      * same values, so results do not change, only the time.  Where steps
      * run in pairs, a chare re-runs extra(t) + extra(t + 1) one-step sweeps
-     * before the pass of steps t and t + 1.  0 = off. */
+     * before the pass of steps t and t + 1; likewise in fours.  0 = off. */
     int32_t imbalance_pct;
     int32_t imbalance_max_extra;
     /* Implementation hints, 0 = defaults; none of them changes a result.
@@ -159,8 +159,7 @@ typedef struct {
      * reads lies in one block.
      * od_plan_info.steps_per_pass tells which is in use.
      * Bit 14 (OD_FUSED, OD_GRAPH): pairs at most.  By default grids of these
-     * forms that run pairs, with no imbalance and no tile shape fixed by the
-     * caller, run groups of four iterations as one pass where the grid has
+     * forms that run pairs, with no tile shape fixed by the caller, run groups of four iterations as one pass where the grid has
      * at least 64 cells along x and y and x extents and chare origins that are
      * multiples of 16 bytes (od_pass_info); the values are again the same,
      * and what is left over of a count runs as pairs and a single sweep.

@@ -351,6 +351,11 @@ __device__ __forceinline__ T sweep_tile(T* __restrict__ arena, const BlockDev* _
     return r;
 }
 
+// imb.only: the re-runs that go ahead of a four-step pass, as a launch of
+// their own.  (512^3 fp64, 10 % of 512 chares re-running 1-4 times a step,
+// us per iteration: 318, of which the pass takes 154, against 455 with pairs
+// that run each tile's re-runs and pass in one workgroup; ODF 8 319 / 446,
+// 4096 332 / 449.)
 template <typename T, int TX, int TY, bool XEXP = false>
 __global__ void __launch_bounds__((TX / V16<T>::N) * TY)
 k_sweep(T* __restrict__ arena, const BlockDev* __restrict__ blocks, const TileDev* __restrict__ tiles,
@@ -359,9 +364,15 @@ k_sweep(T* __restrict__ arena, const BlockDev* __restrict__ blocks, const TileDe
     using S = SW<T, TX, TY>;
     __shared__ T lds[S::LDS];
     __shared__ T red[S::NT / 64];
+    const TileDev& t = tiles[blockIdx.x];
+    if (imb.only > 0) {
+        int extra = 0;
+        for (int k = 0; k < imb.only; ++k) extra += imb_extra(imb, step + k, t.blk);
+        for (int e = 0; e < extra; ++e) (void)sweep_tile<T, TX, TY>(arena, blocks, t, parity, lds, hints);
+        return;
+    }
     if (blockIdx.x == 0)
         for (int s = zero_lo + (int)threadIdx.x; s < zero_hi; s += S::NT) res[2 * s + parity] = 0ull;
-    const TileDev& t = tiles[blockIdx.x];
     const int reps = 1 + imb_extra(imb, step, t.blk);
     T r = 0;
     for (int rep = 0; rep < reps; ++rep)

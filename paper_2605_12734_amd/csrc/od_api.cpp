@@ -194,12 +194,13 @@ bool two_step_room(const Grid& G) {
 }
 
 // Four steps per pass: the fused and graph forms where they can pair steps,
-// the 3D stencil without imbalance, unless hints bit 14 or a tile shape fixed
-// by the caller (whose passes then run that shape).
+// the 3D stencil, unless hints bit 14 or a tile shape fixed by the caller
+// (whose passes then run that shape).  Under load imbalance the heavy chares'
+// re-runs of the four steps are a launch of their own before the pass.
 bool deep_possible(const Grid& G) {
     const od_config& cfg = G.cfg;
     return (cfg.exec == OD_FUSED || cfg.exec == OD_GRAPH) && cfg.stencil != 5 && !G.plan.multires &&
-           G.imb.heavy == 0 && !(cfg.hints & (4096 | 16384)) && !G.user_tile;
+           !(cfg.hints & (4096 | 16384)) && !G.user_tile;
 }
 
 // Block and local coordinates of global cell (x, y, z) as a FaceDev: its
@@ -1075,7 +1076,16 @@ od_status Grid::fused_two(hipStream_t s2, int par, int64_t step) {
     return OD_OK;
 }
 
-od_status Grid::fused_deep(hipStream_t s2, int par, bool last) {
+od_status Grid::fused_deep(hipStream_t s2, int par, int64_t step, bool last) {
+    if (imb.heavy > 0) {
+        ImbDev m = imb;
+        m.only = kDeepSteps;
+        hipError_t e0 = launch_sweep(s, plan.tile[0], plan.tile[1], s2, base,
+                                     reinterpret_cast<const BlockDev*>(cp(L.blocks)),
+                                     reinterpret_cast<const TileDev*>(cp(L.tiles)), (int32_t)tiles_h.size(), par,
+                                     res_ptr(), 0, 0, m, step, mode());
+        if (e0 != hipSuccess) return fail(OD_EHIP, std::string("re-run launch: ") + hipGetErrorString(e0));
+    }
     hipError_t e = launch_deep(s, s2, deep_map, reinterpret_cast<const DeepTile*>(cp(L.deep)), (int32_t)deep_h.size(),
                                par, res_ptr(), 0, 1, mode(), last);
     if (e != hipSuccess) return fail(OD_EHIP, std::string("four-step sweep launch: ") + hipGetErrorString(e));
@@ -1083,7 +1093,7 @@ od_status Grid::fused_deep(hipStream_t s2, int par, bool last) {
 }
 
 od_status Grid::fused_pass(hipStream_t s2, int par, int64_t step, int k, bool last) {
-    return k == kDeepSteps ? fused_deep(s2, par, last) : (k == 2 ? fused_two(s2, par, step) : fused_one(s2, par, step));
+    return k == kDeepSteps ? fused_deep(s2, par, step, last) : (k == 2 ? fused_two(s2, par, step) : fused_one(s2, par, step));
 }
 
 od_status Grid::upload_tiles() {

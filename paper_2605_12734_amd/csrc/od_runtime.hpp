@@ -169,7 +169,7 @@ struct Grid {
     unsigned long long* res_ptr();
     od_status fused_one(hipStream_t s2, int par, int64_t step);
     od_status fused_two(hipStream_t s2, int par, int64_t step);   // steps step, step + 1: parity par -> par ^ 1
-    od_status fused_deep(hipStream_t s2, int par, bool last);     // kDeepSteps steps: parity par -> par ^ 1
+    od_status fused_deep(hipStream_t s2, int par, int64_t step, bool last);   // kDeepSteps steps: parity par -> par ^ 1
     // k steps (steps_of); last: the residual is wanted
     od_status fused_pass(hipStream_t s2, int par, int64_t step, int k, bool last);
     od_status upload_tiles();                      // tile descriptors (and two-step lines) to the device

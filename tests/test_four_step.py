@@ -44,7 +44,7 @@ def test_boxes_write_each_cell_once_and_keep_their_ring(dtype, vx, n):
     (dict(n=64, odf=8, exec="persistent"), 2), (dict(n=64, odf=8, exec="msgdriven"), 2),
     (dict(n=64, odf=8, hints=1 << 14), 2), (dict(n=64, odf=8, hints=1 << 12), 1),
     (dict(n=64, odf=8, tile=(32, 16, 16)), 2),                 # the caller's tile shape is what runs
-    (dict(n=64, odf=8, exec="fused", imbalance_pct=10, imbalance_max_extra=4), 2),
+    (dict(n=64, odf=8, exec="fused", imbalance_pct=10, imbalance_max_extra=4), 4),
 ])
 def test_which_grids_run_four_steps(kw, steps):
     kw = dict(dict(odf=1, dtype="f64", exec="graph"), **kw)
@@ -91,6 +91,19 @@ def test_edges_of_boxes_and_chares(dtype, n, odf):
 def test_what_is_left_of_a_count(exec_, iters):
     want, _, r = oracle.solve((128, 64, 24), np.float64, seed=5, iters=sum(iters), bc=BC6)
     U, got = _run((128, 64, 24), 8, "f64", iters, exec_)
+    _same(U, want)
+    assert got == r
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("odf,iters", [(64, [4]), (64, [3, 8]), (8, [11])])
+def test_imbalance_re_runs_before_the_pass(dtype, odf, iters):
+    # half the chares re-run up to four times a step: their re-runs write the
+    # other parity before the pass overwrites it
+    n = (128, 72, 40)
+    want, _, r = oracle.solve(n, DT[dtype], seed=5, iters=sum(iters), bc=BC6)
+    U, got = _run(n, odf, dtype, iters, imbalance_pct=50, imbalance_max_extra=4)
     _same(U, want)
     assert got == r
 
