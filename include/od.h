@@ -158,8 +158,10 @@ typedef struct {
      * blocks the tiles are also cut so that every line of cells a pair
      * reads lies in one block.
      * od_plan_info.steps_per_pass tells which is in use.
-     * Bit 14 (OD_FUSED, OD_GRAPH): pairs at most.  By default grids of these
-     * forms that run pairs, with no tile shape fixed by the caller, run groups of four iterations as one pass where the grid has
+     * Bit 14 (OD_FUSED, OD_GRAPH, OD_PERSISTENT, OD_MSGDRIVEN): pairs at
+     * most.  By default grids that run pairs, with no tile shape fixed by the
+     * caller (and in the cooperative forms without imbalance, OD_PERSISTENT
+     * without a schedule forced by bits 4, 5, 11 or 13), run groups of four iterations as one pass where the grid has
      * at least 64 cells along x and y and x extents and chare origins that are
      * multiples of 16 bytes (od_pass_info); the values are again the same,
      * and what is left over of a count runs as pairs and a single sweep.

@@ -53,4 +53,21 @@ hipError_t launch_deep(int dtype_bytes, hipStream_t st, const DeepMap& g, const 
                        int parity, unsigned long long* res, int32_t zero_lo, int32_t zero_hi, int hints,
                        bool want_res);
 
+
+// Every pass of an iteration count in one cooperative launch of `grid`
+// workgroups (at most deep_max_grid); bar / err as launch_persistent.
+hipError_t launch_deep_persistent(int dtype_bytes, hipStream_t st, int grid, const DeepMap& g, const DeepTile* tiles,
+                                  int32_t ntiles, int parity, int64_t passes, unsigned long long* res,
+                                  unsigned int* bar, unsigned int* err, int64_t wait_ticks, int hints, bool want_res);
+// The message-driven scheduler over boxes: a scheduler step is one pass.
+hipError_t launch_deep_msg(int dtype_bytes, hipStream_t st, int grid, const MsgArgs& a, const DeepMap& g,
+                           const DeepTile* tiles);
+// Workgroups of either cooperative form that are co-resident on the device.
+int deep_max_grid(int dtype_bytes);
+hipError_t launch_fill_i32(hipStream_t st, int32_t* p, int32_t n, int32_t v);
+
+// For each box the boxes whose written cells its lanes read, and those that
+// read its own (CSR, ascending, symmetric).
+void deep_deps(const std::vector<DeepTile>& t, int dtype_bytes, std::vector<int32_t>& ptr, std::vector<int32_t>& idx);
+
 }  // namespace od

@@ -15,6 +15,7 @@
 #include <algorithm>
 #include <string>
 
+#include "deep_dev.hpp"
 #include "kernels.hpp"
 
 // Planes of the register column loaded ahead of the one being computed
@@ -1929,6 +1930,53 @@ k_msgdriven2(MsgArgs a) {
     queue_loop<S::NT>(a, sweep, red);
 }
 
+// Four-step passes (deep_dev.hpp) of a persistent grid: every pass in one
+// cooperative launch, boxes dealt to the workgroups by a fixed stride, the
+// per-XCD barrier between passes.  The boxes are cut to fill the chip in whole
+// rounds, so a counter would find nothing to balance.  Bound as the pass; us
+// per iteration against pairs from counters: 512^3 fp64 ODF 512 157 / 292,
+// fp32 85 / 166, 256^3 fp64 24.3 / 46.1, 64^3 fp64 8.0 / 18.4.
+template <typename T, int NW>
+__global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
+k_deep_persistent(DeepMap g, const DeepTile* __restrict__ tiles, int32_t ntiles, int parity, int64_t passes,
+                  unsigned long long* __restrict__ res, unsigned int* bar, unsigned int* err, int64_t wait_ticks,
+                  int hints, int want_res) {
+    __shared__ __align__(16) typename Deep<T, NW>::Lds L;
+    __shared__ int s_xcd;
+    __shared__ unsigned int s_xwgs, s_nxcd;
+    if (passes > 1 && !persist_register(bar, err, wait_ticks, &s_xcd, &s_xwgs, &s_nxcd)) return;
+    for (int64_t it = 0; it < passes; ++it) {
+        const int p = parity ^ (int)(it & 1);
+        const bool last = want_res && it + 1 == passes;
+        if (blockIdx.x == 0 && threadIdx.x == 0) res[p] = 0ull;
+        T r = 0;
+        for (int32_t i = (int32_t)blockIdx.x; i < ntiles; i += (int32_t)gridDim.x) {
+            const T b = deep_box<T, NW>(g, tiles[i], p, L, hints, last);
+            r = b > r ? b : r;
+            __syncthreads();   // the LDS is the next box's
+        }
+        if (last) wg_residual<T, NW * 64>(r, &res[p ^ 1], L.red);
+        if (it + 1 < passes && !xcd_barrier(bar, err, wait_ticks, nullptr, s_xcd, s_xwgs, s_nxcd)) return;
+    }
+    persist_cleanup(bar);
+}
+
+// Message-driven tasks of four steps: a task is one pass of one box, and a box
+// waits for those whose cells its lanes read (the lists reach its whole ring).
+// us per iteration against tasks of two steps: 512^3 fp64 ODF 512 149 / 292,
+// fp32 100 / 166, 256^3 fp64 29 / 52, 64^3 fp64 7.7 / 18.6.
+template <typename T, int NW>
+__global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
+k_deep_msg(MsgArgs a, DeepMap g, const DeepTile* __restrict__ tiles) {
+    __shared__ __align__(16) typename Deep<T, NW>::Lds L;
+    __shared__ double red[NW];
+    const int32_t tgt = ld_rlx(&a.target[0]);
+    auto sweep = [&](int32_t i, int32_t step) -> double {
+        return (double)deep_box<T, NW>(g, tiles[i], step & 1, L, a.hints, step + 1 == tgt);
+    };
+    queue_loop<NW * 64>(a, sweep, red);
+}
+
 // Serving: tiles of independent fp64 and fp32 solves in one launch.  The two
 // tile variants have the same thread count; each task runs the variant of
 // its solve's dtype on a shared LDS buffer.  Block offsets are in elements
@@ -2389,6 +2437,50 @@ int persistent_max_grid(int dtype_bytes, int tx, int ty, int kind, int max_waves
     OD_VARIANTS_F32(OD_OCC)
 #undef OD_OCC
     return 0;
+}
+
+int deep_max_grid(int dtype_bytes) {
+    int dev = 0, ncu = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return 0;
+    if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
+    constexpr int W8 = deep_waves(8), W4 = deep_waves(4);
+    const int a = dtype_bytes == 8 ? coop_cap(k_deep_persistent<double, W8>, W8 * 64, "od::k_deep_persistent<double, " + std::to_string(W8) + ">", 8)
+                                   : coop_cap(k_deep_persistent<float, W4>, W4 * 64, "od::k_deep_persistent<float, " + std::to_string(W4) + ">", 8);
+    const int b = dtype_bytes == 8 ? coop_cap(k_deep_msg<double, W8>, W8 * 64, "od::k_deep_msg<double, " + std::to_string(W8) + ">", 8)
+                                   : coop_cap(k_deep_msg<float, W4>, W4 * 64, "od::k_deep_msg<float, " + std::to_string(W4) + ">", 8);
+    return (a < b ? a : b) * ncu;
+}
+
+hipError_t launch_deep_persistent(int dtype_bytes, hipStream_t st, int grid, const DeepMap& g, const DeepTile* tiles,
+                                  int32_t ntiles, int parity, int64_t passes, unsigned long long* res,
+                                  unsigned int* bar, unsigned int* err, int64_t wait_ticks, int hints, bool want_res) {
+    if (passes <= 0) return hipSuccess;
+    DeepMap m = g;
+    int w = want_res ? 1 : 0;
+    void* args[] = {&m, &tiles, &ntiles, &parity, &passes, &res, &bar, &err, &wait_ticks, &hints, &w};
+    const void* fn = dtype_bytes == 8 ? reinterpret_cast<const void*>(k_deep_persistent<double, deep_waves(8)>)
+                                      : reinterpret_cast<const void*>(k_deep_persistent<float, deep_waves(4)>);
+    return hipLaunchCooperativeKernel(fn, dim3(grid), dim3(deep_waves(dtype_bytes) * 64), args, 0, st);
+}
+
+hipError_t launch_deep_msg(int dtype_bytes, hipStream_t st, int grid, const MsgArgs& a, const DeepMap& g,
+                           const DeepTile* tiles) {
+    MsgArgs ma = a;
+    DeepMap m = g;
+    void* args[] = {&ma, &m, &tiles};
+    const void* fn = dtype_bytes == 8 ? reinterpret_cast<const void*>(k_deep_msg<double, deep_waves(8)>)
+                                      : reinterpret_cast<const void*>(k_deep_msg<float, deep_waves(4)>);
+    return hipLaunchCooperativeKernel(fn, dim3(grid), dim3(deep_waves(dtype_bytes) * 64), args, 0, st);
+}
+
+__global__ void k_fill_i32(int32_t* p, int32_t n, int32_t v) {
+    for (int32_t i = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x); i < n; i += (int32_t)(gridDim.x * blockDim.x))
+        p[i] = v;
+}
+hipError_t launch_fill_i32(hipStream_t st, int32_t* p, int32_t n, int32_t v) {
+    if (n <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_fill_i32, dim3((unsigned)std::min((n + 255) / 256, 1024)), dim3(256), 0, st, p, n, v);
+    return hipGetLastError();
 }
 
 hipError_t launch_persistent(int dtype_bytes, int tx, int ty, hipStream_t st, int grid, void* arena,

@@ -193,14 +193,19 @@ bool two_step_room(const Grid& G) {
     return form && !(cfg.hints & 4096) && !p.multires && (!imbalance || cfg.stencil != 5);
 }
 
-// Four steps per pass: the fused and graph forms where they can pair steps,
-// the 3D stencil, unless hints bit 14 or a tile shape fixed by the caller
+// Four steps per pass: the batched forms where they can pair steps (the
+// persistent form with no schedule forced by hints and no timeline), the 3D
+// stencil, unless hints bit 14 or a tile shape fixed by the caller
 // (whose passes then run that shape).  Under load imbalance the heavy chares'
-// re-runs of the four steps are a launch of their own before the pass.
+// re-runs of the four steps are a launch of their own before the pass (fused
+// form; the cooperative forms keep pairs there).
 bool deep_possible(const Grid& G) {
     const od_config& cfg = G.cfg;
-    return (cfg.exec == OD_FUSED || cfg.exec == OD_GRAPH) && cfg.stencil != 5 && !G.plan.multires &&
-           !(cfg.hints & (4096 | 16384)) && !G.user_tile;
+    const bool form = cfg.exec == OD_FUSED || cfg.exec == OD_GRAPH ||
+                      (cfg.exec == OD_PERSISTENT && G.imb.heavy == 0 &&
+                       !(cfg.hints & (kHintTimeline | 16 | 32 | 2048 | 8192))) ||
+                      (cfg.exec == OD_MSGDRIVEN && G.imb.heavy == 0);
+    return form && cfg.stencil != 5 && !G.plan.multires && !(cfg.hints & (4096 | 16384)) && !G.user_tile;
 }
 
 // Block and local coordinates of global cell (x, y, z) as a FaceDev: its
@@ -662,6 +667,15 @@ std::string build_layout(const od_config& cfg, Grid& G) {
     if (!G.deep_h.empty()) {
         G.L.deep = cv.take(G.deep_h.size() * sizeof(DeepTile));
         G.L.deep_tab = cv.take((size_t)(p.n[0] + p.n[1] + 2 * p.n[2]) * 4);
+        if (cfg.exec == OD_MSGDRIVEN) {
+            const size_t nd = G.deep_h.size();
+            deep_deps(G.deep_h, s, G.deep_ptr, G.deep_idx);
+            G.L.deep_dep = cv.take((G.deep_ptr.size() + G.deep_idx.size()) * 4);
+            G.L.deep_done = cv.take(nd * 4);
+            G.L.deep_pend = cv.take(nd * 2 * 4);
+            G.L.deep_xpub = cv.take(nd);
+            G.L.deep_slots = cv.take(2 * (2 * nd + 8) * 8);
+        }
         G.L.total = align_up(cv.off, kAlign) + kAlign;
     }
     return fill_tile_descs(G);
@@ -878,6 +892,14 @@ od_status Grid::setup_cooperative(bool fresh_plan) {
     if (grid >= kNumXcd) grid -= grid % kNumXcd;
     grid_wgs = grid;
     if (grid <= 0) return fail(OD_EHIP, "no co-resident workgroups for the cooperative kernel");
+    if (!deep_h.empty() && deep_wgs == 0) {
+        // whole XCD rounds, but never fewer than the boxes where they all fit:
+        // 240 workgroups for the 243 boxes of 512^3 take two rounds (238 us per
+        // iteration instead of 156)
+        deep_wgs = std::min<int>(deep_max_grid(s), (int)align_up(deep_h.size(), kNumXcd));
+        if (deep_wgs >= kNumXcd) deep_wgs -= deep_wgs % kNumXcd;
+        if (deep_wgs <= 0) deep_h.clear();
+    }
     if (cfg.exec == OD_PERSISTENT) {
         std::vector<TileHost> list = base_tiles;
         if (sched() == 3 && two_step) {
@@ -955,6 +977,10 @@ od_status Grid::upload() {
         }
         if (e == hipSuccess) e = put(L.deep, deep_h.data(), deep_h.size() * sizeof(DeepTile));
         if (e == hipSuccess) e = put(L.deep_tab, tab.data(), tab.size() * 4);
+        if (cfg.exec == OD_MSGDRIVEN) {
+            if (e == hipSuccess) e = put(L.deep_dep, deep_ptr.data(), deep_ptr.size() * 4);
+            if (e == hipSuccess) e = put(L.deep_dep + deep_ptr.size() * 4, deep_idx.data(), deep_idx.size() * 4);
+        }
         const int32_t* t = reinterpret_cast<const int32_t*>(cp(L.deep_tab));
         deep_map.arena = base;
         deep_map.blocks = reinterpret_cast<const BlockDev*>(cp(L.blocks));
@@ -998,6 +1024,7 @@ od_status Grid::reset_state() {
     parity = 0;
     iters = 0;
     flips = 0;
+    msg_counters = 0;
     faces_packed = false;
     return OD_OK;
 }
@@ -1163,6 +1190,20 @@ od_status Grid::persistent_run(int64_t n) {
         iters += n;
         return OD_OK;
     }
+    if (deep() && n >= kDeepSteps) {
+        const int64_t passes = n / kDeepSteps;
+        hipError_t e = launch_deep_persistent(s, st, deep_wgs, deep_map, reinterpret_cast<const DeepTile*>(cp(L.deep)),
+                                              (int32_t)deep_h.size(), parity, passes, res_ptr(),
+                                              reinterpret_cast<unsigned int*>(cp(L.bar)),
+                                              reinterpret_cast<unsigned int*>(cp(L.err)),
+                                              device_wait_ticks(cfg.wait_s > 0 ? cfg.wait_s : 10.0), mode(),
+                                              n % kDeepSteps == 0);
+        if (e != hipSuccess) return fail(OD_EHIP, std::string("persistent launch: ") + hipGetErrorString(e));
+        parity ^= (int)(passes & 1);
+        iters += passes * kDeepSteps;
+        n -= passes * kDeepSteps;
+        if (n == 0) return OD_OK;
+    }
     if (two_step) {
         // n / 2 two-step passes in one launch, an odd last step as a single sweep
         const int64_t passes = n / 2;
@@ -1215,22 +1256,42 @@ od_status Grid::msgdriven_run(int64_t n) {
     // 24-bit slot sequences never alias and finish counters never wrap.
     const int64_t per = std::max<int64_t>(1, std::min<int64_t>(((int64_t)1 << 16) - 1,
                                                                ((int64_t)1 << 23) / std::max<size_t>(tiles_h.size(), 1)));
-    // two-step tasks: n / 2 passes, an odd last iteration as a one-step launch
+    // tasks of four steps over boxes, what is left as tasks of two steps and a
+    // one-step launch
+    if (deep()) {
+        const int64_t per_box = std::max<int64_t>(1, std::min<int64_t>(((int64_t)1 << 16) - 1,
+                                                                       ((int64_t)1 << 23) / (int64_t)deep_h.size()));
+        for (int64_t m = n / kDeepSteps; m > 0;) {
+            const int64_t k = std::min(m, per_box);
+            od_status st2 = msgdriven_launch(k, kDeepSteps);
+            if (st2 != OD_OK) return st2;
+            m -= k;
+        }
+        n %= kDeepSteps;
+    }
     int64_t m = two_step ? n / 2 : n;
     while (m > 0) {
         const int64_t k = std::min(m, per);
-        od_status st2 = msgdriven_launch(k, two_step);
+        od_status st2 = msgdriven_launch(k, two_step ? 2 : 1);
         if (st2 != OD_OK) return st2;
         m -= k;
     }
-    if (two_step && (n & 1)) return msgdriven_launch(1, false);
+    if (two_step && (n & 1)) return msgdriven_launch(1, 1);
     return OD_OK;
 }
 
-od_status Grid::msgdriven_launch(int64_t n, bool pairs) {
+od_status Grid::msgdriven_launch(int64_t n, int steps) {
     // target = flips + n scheduler steps; the final-step residual slots
     // (2, 3) are cleared
     const int32_t tgt = (int32_t)(flips + n);
+    const bool pairs = steps == 2, boxes = steps == kDeepSteps;
+    // between launches every step counter of the kind used last holds flips
+    if ((boxes ? 1 : 0) != msg_counters) {
+        hipError_t e0 = launch_fill_i32(st, reinterpret_cast<int32_t*>(cp(boxes ? L.deep_done : L.done)),
+                                        (int32_t)(boxes ? deep_h.size() : tiles_h.size()), (int32_t)flips);
+        if (e0 != hipSuccess) return fail(OD_EHIP, std::string("step counters: ") + hipGetErrorString(e0));
+        msg_counters = boxes ? 1 : 0;
+    }
     MsgArgs a{};
     a.arena = base;
     a.blocks = reinterpret_cast<const BlockDev*>(cp(L.blocks));
@@ -1247,7 +1308,7 @@ od_status Grid::msgdriven_launch(int64_t n, bool pairs) {
     a.imb = imb;
     // scheduler step k of this launch is iteration iters + (k - flips) per
     // step of a one-step task, two per two-step task
-    a.imb_base = pairs ? iters - 2 * flips : iters - flips;
+    a.imb_base = iters - steps * flips;
     a.wait_ticks = device_wait_ticks(cfg.wait_s > 0 ? cfg.wait_s : 10.0);
     a.hints = mode();
     a.seed = cfg.seed;
@@ -1262,16 +1323,31 @@ od_status Grid::msgdriven_launch(int64_t n, bool pairs) {
     a.ready = reinterpret_cast<int32_t*>(a.qslots);   // the cursor scheduler uses the ready-queue region
     a.qhead = reinterpret_cast<unsigned int*>(cp(L.qctl));
     a.qsteps = (int32_t)n;
+    if (boxes) {
+        a.ntiles = (int32_t)deep_h.size();
+        a.dep_ptr = reinterpret_cast<const int32_t*>(cp(L.deep_dep));
+        a.dep_idx = a.dep_ptr + deep_ptr.size();
+        a.done = reinterpret_cast<int32_t*>(cp(L.deep_done));
+        a.pend = reinterpret_cast<int32_t*>(cp(L.deep_pend));
+        a.xpub = reinterpret_cast<uint8_t*>(cp(L.deep_xpub));
+        a.qslots = reinterpret_cast<unsigned long long*>(cp(L.deep_slots));
+        a.pslots = a.qslots + (2 * deep_h.size() + 8);
+        a.ready = reinterpret_cast<int32_t*>(a.qslots);
+        // (the tuner's choices were timed on tiles)
+        a.sched = ((cfg.hints & 64) ? 1 : ((cfg.hints & 128) ? 2 : 0)) |
+                  (((cfg.hints & 512) ? 1 : ((cfg.hints & 1024) ? 2 : 0)) << 2);
+    }
     // the init kernel stores the target step and clears the final-step
     // residual pair (kernel arguments: nothing on the host outlives this call)
     hipError_t e = launch_queue_init(st, a, tgt, reinterpret_cast<int32_t*>(cp(L.target)), res_ptr() + 2);
     if (e != hipSuccess) return fail(OD_EHIP, std::string("queue init: ") + hipGetErrorString(e));
-    e = pairs ? launch_msgdriven2(s, plan.tile[0], plan.tile[1], st, grid_wgs, a)
+    e = boxes ? launch_deep_msg(s, st, deep_wgs, a, deep_map, reinterpret_cast<const DeepTile*>(cp(L.deep)))
+        : pairs ? launch_msgdriven2(s, plan.tile[0], plan.tile[1], st, grid_wgs, a)
               : launch_msgdriven(s, plan.tile[0], plan.tile[1], st, grid_wgs, a);
     if (e != hipSuccess) return fail(OD_EHIP, std::string("msg-driven launch: ") + hipGetErrorString(e));
     parity = tgt & 1;
     flips = tgt;
-    iters += pairs ? 2 * n : n;
+    iters += steps * n;
     msg_final = true;
     return OD_OK;
 }

@@ -29,6 +29,7 @@ struct Layout {
     size_t ctrl_begin = 0;
     size_t ccell = 0, segs = 0, xpub = 0, xexp = 0, tiles2 = 0;
     size_t deep = 0, deep_tab = 0;           // four-step passes: tiles, per-axis tables
+    size_t deep_dep = 0, deep_done = 0, deep_pend = 0, deep_xpub = 0, deep_slots = 0;   // message-driven boxes
     size_t total_pairs = 0;                  // total without them
     size_t pend = 0, qslots = 0, qctl = 0;   // message-driven dependency counters and XCD queues
     size_t stamps = 0;                       // persistent timeline (hints bit 3)
@@ -65,7 +66,14 @@ struct Grid {
     std::vector<DeepTile> deep_h;
     DeepMap deep_map{};
     bool user_tile = false;          // the caller fixed the tile shape
-    bool deep() const { return !deep_h.empty(); }
+    bool deep() const { return !deep_h.empty() && !tuning; }
+    // cooperative forms: co-resident workgroups; message-driven: dependency
+    // lists and which step counters hold the grid's step (0 = the tiles', 1 =
+    // the boxes')
+    int deep_wgs = 0;
+    std::vector<int32_t> deep_ptr, deep_idx;
+    int msg_counters = 0;
+    bool tuning = false;             // the autotuner times tiles: no four-step passes
     void drop_deep() {
         deep_h.clear();
         L.total = L.total_pairs;
@@ -177,7 +185,7 @@ struct Grid {
     od_status graph_run(int64_t n);
     od_status persistent_run(int64_t n);
     od_status msgdriven_run(int64_t n);
-    od_status msgdriven_launch(int64_t n, bool pairs);   // n scheduler steps (pairs: two-step tasks)
+    od_status msgdriven_launch(int64_t n, int steps);   // n scheduler steps of `steps` iterations a task
     od_status per_chare_run(int64_t n);
     od_status iterate(int64_t n);
     od_status residual(double* r);

@@ -223,7 +223,20 @@ static od_status tune_msgdriven(Grid& G, int32_t iters, std::array<int32_t, 5>& 
     return G.setup_cooperative(false);
 }
 
+static od_status tune(Grid& G, int32_t iters, int32_t out_tile[3]);
+
+// Tiles are timed as the passes that use them; grids that run four-step passes
+// keep the chosen tile for what is left of a count.
 od_status autotune(Grid& G, int32_t iters, int32_t out_tile[3]) {
+    struct Timing {
+        bool& on;
+        explicit Timing(bool& b) : on(b) { on = true; }
+        ~Timing() { on = false; }
+    } timing(G.tuning);
+    return tune(G, iters, out_tile);
+}
+
+static od_status tune(Grid& G, int32_t iters, int32_t out_tile[3]) {
     if (G.cfg.exec == OD_PER_CHARE)
         return fail(OD_EINVAL, "autotune does not apply to OD_PER_CHARE grids; create them with cfg.tile set to a "
                                "tuned shape");

@@ -41,7 +41,10 @@ def test_boxes_write_each_cell_once_and_keep_their_ring(dtype, vx, n):
     (dict(n=(66, 64, 8), dtype="f32"), 2),
     (dict(n=(66, 64, 64), odf=8), 2),                          # chares start inside a vector
     (dict(n=(64, 67, 64), odf=8), 4),                          # along y they may start anywhere
-    (dict(n=64, odf=8, exec="persistent"), 2), (dict(n=64, odf=8, exec="msgdriven"), 2),
+    (dict(n=64, odf=8, exec="persistent"), 4), (dict(n=64, odf=8, exec="msgdriven"), 4),
+    (dict(n=64, odf=8, exec="persistent", hints=1 << 4), 2),   # a schedule of tiles
+    (dict(n=64, odf=8, exec="persistent", hints=1 << 3), 1),   # the timeline is one of single steps
+    (dict(n=64, odf=8, exec="persistent", imbalance_pct=10, imbalance_max_extra=4), 2),
     (dict(n=64, odf=8, hints=1 << 14), 2), (dict(n=64, odf=8, hints=1 << 12), 1),
     (dict(n=64, odf=8, tile=(32, 16, 16)), 2),                 # the caller's tile shape is what runs
     (dict(n=64, odf=8, exec="fused", imbalance_pct=10, imbalance_max_extra=4), 4),
@@ -86,11 +89,32 @@ def test_edges_of_boxes_and_chares(dtype, n, odf):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("exec_", ["fused", "graph"])
+@pytest.mark.parametrize("exec_", ["fused", "graph", "persistent", "msgdriven"])
 @pytest.mark.parametrize("iters", [[4], [5], [6], [7], [4, 4], [3, 8, 1, 4], [1, 11]])
 def test_what_is_left_of_a_count(exec_, iters):
     want, _, r = oracle.solve((128, 64, 24), np.float64, seed=5, iters=sum(iters), bc=BC6)
     U, got = _run((128, 64, 24), 8, "f64", iters, exec_)
+    _same(U, want)
+    assert got == r
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("exec_,hints", [("persistent", 0), ("msgdriven", 0), ("msgdriven", 4), ("msgdriven", 64),
+                                         ("msgdriven", 512)])
+def test_boxes_in_one_launch(dtype, exec_, hints):
+    # more boxes than workgroups and several passes; message-driven also with
+    # the schedule check's delays, cursor claims and a publisher per XCD
+    n, iters = (300, 300, 70), 20
+    want, _, r = oracle.solve(n, DT[dtype], seed=5, iters=iters, bc=BC6)
+    g = od.Grid(n, odf=27, dtype=dtype, exec=exec_, bc=BC6, seed=5, hints=1 | hints)
+    try:
+        assert g.pass_info()["steps"] == 4
+        g.iterate(12)
+        g.iterate(8)
+        U, got = g.read(), g.residual()
+    finally:
+        g.close()
     _same(U, want)
     assert got == r
 
