@@ -192,6 +192,7 @@ struct Grid {
     // sync the grid's stream; OD_ETIMEDOUT if a device-side wait gave up
     od_status device_error();
     od_status io(void* host, size_t bytes, bool to_host);
+    od_status read_field(char* host, size_t plane);
     od_status read_points(const int64_t* idx, int64_t count, void* host_dst);
     od_status block_io(int32_t b, void* host, size_t bytes, bool to_host);
     od_status retile(const int32_t tile[3]);
