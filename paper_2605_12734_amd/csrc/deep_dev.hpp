@@ -30,7 +30,7 @@
 // runs 115-120 us per iteration at 512^3 fp64, with the stores too.
 //
 // Measured, us per iteration, this pass against pairs at the default tile:
-// 512^3 fp64 ODF 4096 154 / 270, fp32 76 / 156; 256^3 fp64 22.6 / 39.3; 64^3
+// 512^3 fp64 ODF 4096 153 / 270, fp32 76 / 156; 256^3 fp64 22.6 / 39.3; 64^3
 // fp64 7.3 / 16.8; 1024^3 fp64 1077 / 2221; 768^3 octree fp64 469 / 1021.  No
 // size that the rule (deep_tiles) admits ran slower: (512,512,16) fp32, the
 // worst of those tried, 9.8 / 11.0.
@@ -108,6 +108,29 @@ __device__ __forceinline__ float lane_shift(float v) {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
 }
 constexpr int kShr1 = 0x138, kShl1 = 0x130;   // whole-wave shift by one lane
+
+// fp64: the same with `alt` in the lanes of `mask`, in the shift's own instruction
+// (v_cndmask takes the shift on its first operand).  s_nop: a shift reads its
+// operand's lanes two wait states after a VALU write at the earliest; the mask has to be in vcc.
+// (512^3 154 against 158 us per iteration with a shift and a select.  In fp32,
+// where the addition does the shift, it measured 3 % slower.)
+template <int CTRL>
+__device__ __forceinline__ double lane_shift_or(double v, double alt, unsigned long long mask) {
+    int lo, hi;
+    if constexpr (CTRL == kShr1)
+        asm("s_mov_b64 vcc, %6\n\ts_nop 1\n\tv_cndmask_b32_dpp %0, %2, %4, vcc wave_shr:1 row_mask:0xf bank_mask:0xf bound_ctrl:0\n\t"
+            "v_cndmask_b32_dpp %1, %3, %5, vcc wave_shr:1 row_mask:0xf bank_mask:0xf bound_ctrl:0"
+            : "=&v"(lo), "=v"(hi)
+            : "v"(__double2loint(v)), "v"(__double2hiint(v)), "v"(__double2loint(alt)), "v"(__double2hiint(alt)),
+              "s"(mask) : "vcc");
+    else
+        asm("s_mov_b64 vcc, %6\n\ts_nop 1\n\tv_cndmask_b32_dpp %0, %2, %4, vcc wave_shl:1 row_mask:0xf bank_mask:0xf bound_ctrl:0\n\t"
+            "v_cndmask_b32_dpp %1, %3, %5, vcc wave_shl:1 row_mask:0xf bank_mask:0xf bound_ctrl:0"
+            : "=&v"(lo), "=v"(hi)
+            : "v"(__double2loint(v)), "v"(__double2hiint(v)), "v"(__double2loint(alt)), "v"(__double2hiint(alt)),
+              "s"(mask) : "vcc");
+    return __hiloint2double(hi, lo);
+}
 
 // Chare of a global interior cell from the per-axis index tables.
 __device__ __forceinline__ int32_t deep_owner(const DeepMap& m, int ix, int iy, int iz) {
@@ -222,6 +245,7 @@ __device__ __forceinline__ T deep_tile(const DeepMap& g, const DeepTile& t, cons
     const bool st_x = x >= t.xo0 && x < t.xo1;
     const int r0 = st_x ? t.yo0 - y : kRows, r1 = t.yo1 - y;   // rows r0 <= r < r1 are written
     const bool x_first = lx == 0, x_last = x + VX == nx;
+    const unsigned long long m_first = __ballot(x_first), m_last = __ballot(x_last);
 
     const int jlo = max(z0 - kDeepSteps, -1), jhi = z1 - 1 + kDeepSteps;
     const int lmax = min(jhi, nz);
@@ -288,17 +312,24 @@ __device__ __forceinline__ T deep_tile(const DeepMap& g, const DeepTile& t, cons
 #pragma unroll
                     for (int i = 0; i < VX; i += 2) m = min3_abs(m, (T)q[r][i], (T)q[r][i + 1]);
                 }
-                if (__builtin_expect(__any(!(m >= Sixth<T>::tiny)), 0)) {
-#pragma unroll
-                    for (int r = 0; r < kRows; ++r)
-#pragma unroll
-                        for (int i = 0; i < VX; ++i) N[s + 1][r][i] = q[r][i] / (T)6;
-                } else {
+                auto quick = [&]() {
 #pragma unroll
                     for (int r = 0; r < kRows; ++r)
 #pragma unroll
                         for (int i = 0; i < VX; ++i)
                             N[s + 1][r][i] = fma_((T)q[r][i], Sixth<T>::hi, (T)q[r][i] * Sixth<T>::lo);
+                };
+                const bool divide = __any(!(m >= Sixth<T>::tiny));
+                // (written so that either path leaves its result in place: the other
+                // order costs fp64 eight moves a level and fp32 registers)
+                if constexpr (sizeof(T) == 8) quick();
+                if (__builtin_expect(divide, 0)) {
+#pragma unroll
+                    for (int r = 0; r < kRows; ++r)
+#pragma unroll
+                        for (int i = 0; i < VX; ++i) N[s + 1][r][i] = q[r][i] / (T)6;
+                } else if constexpr (sizeof(T) == 4) {
+                    quick();
                 }
             }
         }
@@ -365,9 +396,19 @@ __device__ __forceinline__ T deep_tile(const DeepMap& g, const DeepTile& t, cons
 #pragma unroll
             for (int r = 0; r < kRows; ++r) {
                 const V c = N[s][r];
-                T left = lane_shift<kShr1>((T)c[VX - 1]), right = lane_shift<kShl1>((T)c[0]);
-                if constexpr (xm_face) left = x_first ? (T)bm[r / VX][r % VX] : left;
-                if constexpr (xp_face) right = x_last ? (T)bp[r / VX][r % VX] : right;
+                T left, right;
+                if constexpr (xm_face && sizeof(T) == 8) {
+                    left = lane_shift_or<kShr1>(c[VX - 1], bm[r / VX][r % VX], m_first);
+                } else {
+                    left = lane_shift<kShr1>((T)c[VX - 1]);
+                    if constexpr (xm_face) left = x_first ? (T)bm[r / VX][r % VX] : left;
+                }
+                if constexpr (xp_face && sizeof(T) == 8) {
+                    right = lane_shift_or<kShl1>(c[0], bp[r / VX][r % VX], m_last);
+                } else {
+                    right = lane_shift<kShl1>((T)c[0]);
+                    if constexpr (xp_face) right = x_last ? (T)bp[r / VX][r % VX] : right;
+                }
                 const V ym = r > 0 ? N[s][r > 0 ? r - 1 : 0] : yme;
                 const V yp = r < kRows - 1 ? N[s][r < kRows - 1 ? r + 1 : r] : ype;
                 V a;
