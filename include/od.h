@@ -161,9 +161,9 @@ typedef struct {
      * Bit 14 (OD_FUSED, OD_GRAPH, OD_PERSISTENT, OD_MSGDRIVEN): pairs at
      * most.  By default grids that run pairs, with no tile shape fixed by the
      * caller (and in the cooperative forms without imbalance, OD_PERSISTENT
-     * without a schedule forced by bits 4, 5, 11 or 13), run groups of four iterations as one pass where the grid has
-     * at least 64 cells along x and y and x extents and chare origins that are
-     * multiples of 16 bytes (od_pass_info); the values are again the same,
+     * without a schedule forced by bits 4, 5, 11 or 13), run groups of four iterations as one pass over boxes of the whole
+     * grid (od_pass_info; od_autotune may find a thin grid's tiles quicker and
+     * keep them); the values are again the same,
      * and what is left over of a count runs as pairs and a single sweep.
      * Bit 8 is reserved.  Other bits are ignored. */
     int32_t hints;

@@ -12,16 +12,24 @@ namespace od {
 
 namespace {
 
-template <typename T, int NW>
-__global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
+// A plane iteration of a full chip, in units of 50 ns: measured over cubes from
+// 64^3 to 512^3 as 2.5 (four rows) and 1.55 us (one) in fp64, 3.2 and 1.65 us in
+// fp32, whose CUs hold twice the workgroups.  us per iteration with four / one
+// rows: fp64 64^3 7.4 / 5.1, 128^3 9.9 / 9.0, 160^3 10.5 / 11.6, 256^3 22.6 / 34.7;
+// fp32 64^3 6.4 / 3.6, 192^3 11.1 / 10.5, 224^3 11.8 / 13.0, 512^3 89 / 115.
+int64_t plane_cost(int dtype_bytes, int rows) {
+    return dtype_bytes == 8 ? (rows == 1 ? 31 : 50) : (rows == 1 ? 33 : 65);
+}
+
+template <typename T, int R, bool RAG>
+__global__ void __launch_bounds__(deep_waves((int)sizeof(T)) * 64) OD_DEEP_OCC(R)
 k_deep(DeepMap g, const DeepTile* __restrict__ tiles, int parity, unsigned long long* __restrict__ res, int zero_lo,
        int zero_hi, int hints, int want_res) {
-    using D = Deep<T, NW>;
+    using D = Deep<T, R>;
     __shared__ __align__(16) typename D::Lds L;
     if (blockIdx.x == 0)
         for (int s = zero_lo + (int)threadIdx.x; s < zero_hi; s += D::NT) res[2 * s + parity] = 0ull;
-    const DeepTile& t = tiles[blockIdx.x];
-    T r = deep_box<T, NW>(g, t, parity, L, hints, want_res != 0);
+    T r = deep_box<T, R, RAG>(g, tiles[blockIdx.x], parity, L, hints, want_res != 0);
     if (!want_res) return;
     for (int off = 32; off > 0; off >>= 1) {
         const T o = __shfl_xor(r, off, 64);
@@ -31,80 +39,116 @@ k_deep(DeepMap g, const DeepTile* __restrict__ tiles, int parity, unsigned long 
     __syncthreads();
     if (threadIdx.x == 0) {
         T m = L.red[0];
-        for (int w = 1; w < NW; ++w) m = L.red[w] > m ? L.red[w] : m;
+        for (int w = 1; w < D::NW; ++w) m = L.red[w] > m ? L.red[w] : m;
         atomicMax(&res[parity ^ 1], (unsigned long long)__double_as_longlong((double)m));
     }
 }
+
+// Workgroups a CU holds: registers and LDS at four rows a strip (128 VGPRs of
+// levels), LDS at one.
+int per_cu(int dtype_bytes, int rows) { return (dtype_bytes == 8 ? 1 : 2) * (rows == 1 ? 2 : 1); }
 
 struct Cut {
     int32_t start, o0, o1;
 };
 
-// Tiles of one axis of n cells: lanes cover e cells from `start`, a multiple
-// of vx, and write [o0, o1).  At the grid's faces no ring is needed.
-std::vector<Cut> cut_axis(int64_t n, int32_t e, int32_t vx, int32_t align) {
-    std::vector<Cut> out;
-    const int64_t first = e - kDeepSteps, mid = e - 2 * kDeepSteps;
-    if (n < e) return out;
-    if (n == e) {
-        out.push_back({0, 0, (int32_t)n});
+// Boxes along an axis of n items (vectors, or rows) of which the lanes cover L:
+// item i holds cells(i + 1) - cells(i) cells.  A box writes [o0, o1) from the
+// lanes [start, start + L); between what it writes and lanes with more grid
+// behind them lie at least kDeepSteps cells.
+template <typename Cells>
+std::vector<Cut> cut_axis(int32_t n, int32_t L, Cells cells) {
+    auto left = [&](int32_t o) {   // first lane needed to write from o on
+        int32_t s = o;
+        while (s > 0 && cells(o) - cells(s) < kDeepSteps) --s;
+        return s;
+    };
+    auto right = [&](int32_t s) {   // items a box that starts at s can write up to
+        if (s + L >= n) return n;
+        int32_t o = s + L;
+        while (o > s && cells(s + L) - cells(o) < kDeepSteps) --o;
+        return o;
+    };
+    auto build = [&](int32_t most) {   // boxes of at most `most` items each
+        std::vector<Cut> out;
+        for (int32_t o = 0; o < n;) {
+            int32_t s = left(o);
+            int32_t e = std::min(right(s), std::min(n, o + most));
+            if (e <= o) return std::vector<Cut>{};
+            if (e == n) s = std::max(0, std::min(s, n - L));
+            out.push_back({s, o, e});
+            o = e;
+        }
         return out;
-    }
-    int64_t m = 2;
-    if (n > 2 * first) m = 2 + (n - 2 * first + mid - 1) / mid;
-    std::vector<int64_t> o((size_t)m + 1, 0);
-    o[(size_t)m] = n;
-    for (int64_t i = 1; i < m; ++i) {
-        // what the tiles before can reach, and what those behind must cover
-        const int64_t hi = i == 1 ? first : o[(size_t)i - 1] + mid;
-        int64_t lo = n - first - (m - 1 - i) * mid;
-        lo = (std::max<int64_t>(lo, o[(size_t)i - 1] + 1) + vx - 1) / vx * vx;
-        int64_t v = n * i / m / align * align;
-        if (v < lo || v > hi) v = std::min(std::max(v, lo), hi) / align * align;
-        if (v < lo || v > hi) v = hi / vx * vx;
-        if (v < lo || v > hi) return {};
-        o[(size_t)i] = v;
-    }
-    for (int64_t i = 0; i < m; ++i) {
-        int64_t s = i == 0 ? 0 : o[(size_t)i] - kDeepSteps;
-        const int64_t top = (n - e + vx - 1) / vx * vx;
-        s = i == m - 1 ? top : std::min(std::max<int64_t>(s, 0), top);
-        out.push_back({(int32_t)s, (int32_t)o[(size_t)i], (int32_t)o[(size_t)i + 1]});
+    };
+    std::vector<Cut> out = build(n);
+    if (out.size() < 2) return out;
+    // as many boxes, as even as their reach allows
+    const size_t m = out.size();
+    for (int32_t most = (n + (int32_t)m - 1) / (int32_t)m; most < n; ++most) {
+        std::vector<Cut> even = build(most);
+        if (even.size() == m) return even;
     }
     return out;
 }
 
 }  // namespace
 
-void deep_shape(int dtype_bytes, int* ex, int* ey) {
-    *ex = kEX;
-    *ey = deep_waves(dtype_bytes) * 64 / (kEX * dtype_bytes / 16) * kRows;
+void deep_shape(int dtype_bytes, int rows, int* lx, int* ey) {
+    *lx = kEX * dtype_bytes / 16;
+    *ey = deep_waves(dtype_bytes) * 64 / *lx * rows;
 }
 
-std::vector<DeepTile> deep_tiles(const Plan& p, int dtype_bytes) {
-    std::vector<DeepTile> out;
-    int ex, ey;
-    deep_shape(dtype_bytes, &ex, &ey);
-    const int32_t vx = 16 / dtype_bytes;
-    if (p.multires || p.n[0] < ex || p.n[0] % vx != 0 || p.n[1] < ey || p.n[2] < 1) return out;
-    for (const Chare& c : p.chares) {
-        if (c.u[0] % vx != 0) return out;   // a lane's vector lies in one chare
-        // plane steps are 32-bit byte counts
+DeepPlan deep_plan(const Plan& p, int dtype_bytes) {
+    DeepPlan out;
+    const int32_t VX = 16 / dtype_bytes;
+    if (p.multires || p.chares.empty()) return out;
+    for (const Chare& c : p.chares)   // plane steps are 32-bit byte counts
         if ((int64_t)(c.e[0] + 16) * c.e[1] * dtype_bytes > INT32_MAX) return out;
-    }
-    const std::vector<Cut> cx = cut_axis(p.n[0], ex, vx, 64 / dtype_bytes), cy = cut_axis(p.n[1], ey, 1, 1);
-    if (cx.empty() || cy.empty()) return out;
-    // z: as many pieces as fill the chip's 256 CUs in the fewest plane
-    // iterations, a piece of l planes taking l + 8
-    const int64_t xy = (int64_t)cx.size() * (int64_t)cy.size(), slots = 256 * deep_per_cu(dtype_bytes);
-    int64_t best = INT64_MAX, zc = 1;
-    for (int64_t k = 1; k <= p.n[2]; ++k) {
-        const int64_t len = (p.n[2] + k - 1) / k, cost = ((xy * k + slots - 1) / slots) * (len + 2 * kDeepSteps);
-        if (cost < best) {
-            best = cost;
-            zc = k;
+    // vectors along x: every chare's row begins one (explicit blocks begin on
+    // multiples of a vector)
+    DeepPlan d;
+    if (p.regular) {
+        for (int32_t i = 0; i < p.k[0]; ++i)
+            for (int32_t x = p.split[0][(size_t)i]; x < p.split[0][(size_t)i + 1]; x += VX) {
+                d.ragged = d.ragged || x + VX > p.split[0][(size_t)i + 1];
+                d.vx.push_back(x);
+                d.vi.push_back(i);
+            }
+    } else {
+        for (int32_t x = 0; x < p.n[0]; x += VX) {
+            d.ragged = d.ragged || x + VX > p.n[0];
+            d.vx.push_back(x);
+            d.vi.push_back(x / p.gran);
         }
     }
+    const int32_t nv = (int32_t)d.vx.size();
+    d.vx.push_back((int32_t)p.n[0]);
+    std::vector<Cut> cx, cy;
+    int64_t best = INT64_MAX, zc = 1;
+    for (int rows : {4, 1}) {
+        int lx, ey;
+        deep_shape(dtype_bytes, rows, &lx, &ey);
+        if (rows > 1 && p.n[1] < ey) continue;   // the last row ends a strip
+        const std::vector<Cut> ax = cut_axis(nv, lx, [&](int32_t i) { return d.vx[(size_t)i]; }),
+                               ay = cut_axis((int32_t)p.n[1], ey, [](int32_t i) { return i; });
+        if (ax.empty() || ay.empty()) continue;
+        // z: as many pieces as fill the chip's 256 CUs in the fewest plane
+        // iterations, a piece of l planes taking l + 8
+        const int64_t xy = (int64_t)ax.size() * (int64_t)ay.size(), slots = 256 * per_cu(dtype_bytes, rows);
+        for (int64_t k = 1; k <= p.n[2]; ++k) {
+            const int64_t len = (p.n[2] + k - 1) / k;
+            const int64_t cost = ((xy * k + slots - 1) / slots) * (len + 2 * kDeepSteps) * plane_cost(dtype_bytes, rows);
+            if (cost < best) {
+                best = cost;
+                zc = k;
+                d.rows = rows;
+                cx = ax;
+                cy = ay;
+            }
+        }
+    }
+    if (d.rows == 0) return out;
     std::vector<DeepTile> list;
     for (int64_t k = 0; k < zc; ++k)
         for (const Cut& b : cy)
@@ -113,25 +157,26 @@ std::vector<DeepTile> deep_tiles(const Plan& p, int dtype_bytes) {
                                 (int32_t)(p.n[2] * (k + 1) / zc)});
     // workgroup w runs on XCD w % 8: give each XCD a contiguous run
     const size_t N = list.size();
-    out.reserve(N);
+    d.tiles.reserve(N);
     std::vector<size_t> at(kNumXcd), end(kNumXcd);
     for (size_t g = 0, o = 0; g < (size_t)kNumXcd; ++g) {
         const size_t cnt = N / kNumXcd + (g < N % kNumXcd ? 1 : 0);
         at[g] = o;
         end[g] = o += cnt;
     }
-    for (size_t i = 0; out.size() < N; ++i) {
+    for (size_t i = 0; d.tiles.size() < N; ++i) {
         const size_t g = i % kNumXcd;
-        if (at[g] < end[g]) out.push_back(list[at[g]++]);
+        if (at[g] < end[g]) d.tiles.push_back(list[at[g]++]);
     }
-    return out;
+    return d;
 }
 
-void deep_deps(const std::vector<DeepTile>& t, int dtype_bytes, std::vector<int32_t>& ptr, std::vector<int32_t>& idx) {
+void deep_deps(const DeepPlan& d, int dtype_bytes, std::vector<int32_t>& ptr, std::vector<int32_t>& idx) {
+    const std::vector<DeepTile>& t = d.tiles;
     int ex, ey;
-    deep_shape(dtype_bytes, &ex, &ey);
+    deep_shape(dtype_bytes, d.rows, &ex, &ey);
     auto reads = [&](const DeepTile& a, const DeepTile& b) {
-        return b.xo0 < a.xs + ex && a.xs < b.xo1 && b.yo0 < a.ys + ey && a.ys < b.yo1 && b.z0 < a.z1 + kDeepSteps &&
+        return b.wo0 < a.ws + ex && a.ws < b.wo1 && b.yo0 < a.ys + ey && a.ys < b.yo1 && b.z0 < a.z1 + kDeepSteps &&
                a.z0 - kDeepSteps < b.z1;
     };
     // boxes by their place on each axis; along an axis only cuts whose lanes and
@@ -140,20 +185,20 @@ void deep_deps(const std::vector<DeepTile>& t, int dtype_bytes, std::vector<int3
         int32_t lo, hi;
     };
     std::array<std::map<int32_t, Span>, 3> cuts;   // first written cell -> reach
-    auto first = [](const DeepTile& b, int d) { return d == 0 ? b.xo0 : (d == 1 ? b.yo0 : b.z0); };
+    auto first = [](const DeepTile& b, int q) { return q == 0 ? b.wo0 : (q == 1 ? b.yo0 : b.z0); };
     std::map<std::array<int32_t, 3>, int32_t> at;
     for (size_t i = 0; i < t.size(); ++i) {
         const DeepTile& b = t[i];
-        cuts[0][b.xo0] = {std::min(b.xs, b.xo0), std::max(b.xs + ex, b.xo1)};
+        cuts[0][b.wo0] = {std::min(b.ws, b.wo0), std::max(b.ws + ex, b.wo1)};
         cuts[1][b.yo0] = {std::min(b.ys, b.yo0), std::max(b.ys + ey, b.yo1)};
         cuts[2][b.z0] = {b.z0 - kDeepSteps, b.z1 + kDeepSteps};
-        at[{b.xo0, b.yo0, b.z0}] = (int32_t)i;
+        at[{b.wo0, b.yo0, b.z0}] = (int32_t)i;
     }
     std::array<std::map<int32_t, std::vector<int32_t>>, 3> near;
-    for (size_t d = 0; d < 3; ++d)
-        for (const auto& a : cuts[d])
-            for (const auto& b : cuts[d])
-                if (a.second.lo < b.second.hi && b.second.lo < a.second.hi) near[d][a.first].push_back(b.first);
+    for (size_t q = 0; q < 3; ++q)
+        for (const auto& a : cuts[q])
+            for (const auto& b : cuts[q])
+                if (a.second.lo < b.second.hi && b.second.lo < a.second.hi) near[q][a.first].push_back(b.first);
     ptr.assign(t.size() + 1, 0);
     idx.clear();
     for (size_t i = 0; i < t.size(); ++i) {
@@ -169,17 +214,20 @@ void deep_deps(const std::vector<DeepTile>& t, int dtype_bytes, std::vector<int3
     }
 }
 
-hipError_t launch_deep(int dtype_bytes, hipStream_t st, const DeepMap& g, const DeepTile* tiles, int32_t ntiles,
+hipError_t launch_deep(int dtype_bytes, const DeepPlan& d, hipStream_t st, const DeepMap& g, const DeepTile* tiles,
                        int parity, unsigned long long* res, int32_t zero_lo, int32_t zero_hi, int hints,
                        bool want_res) {
-    if (ntiles <= 0) return hipErrorInvalidValue;
-    if (dtype_bytes == 8)
-        hipLaunchKernelGGL((k_deep<double, deep_waves(8)>), dim3((unsigned)ntiles), dim3(deep_waves(8) * 64), 0, st, g,
-                           tiles, parity, res, zero_lo, zero_hi, hints, want_res ? 1 : 0);
-    else
-        hipLaunchKernelGGL((k_deep<float, deep_waves(4)>), dim3((unsigned)ntiles), dim3(deep_waves(4) * 64), 0, st, g,
-                           tiles, parity, res, zero_lo, zero_hi, hints, want_res ? 1 : 0);
-    return hipGetLastError();
+    if (d.tiles.empty()) return hipErrorInvalidValue;
+    const unsigned n = (unsigned)d.tiles.size();
+#define OD_LAUNCH(T, R, RAG)                                                                                       \
+    if (dtype_bytes == (int)sizeof(T) && d.rows == R && d.ragged == RAG) {                                         \
+        hipLaunchKernelGGL((k_deep<T, R, RAG>), dim3(n), dim3(Deep<T, R>::NT), 0, st, g, tiles, parity, res,       \
+                           zero_lo, zero_hi, hints, want_res ? 1 : 0);                                             \
+        return hipGetLastError();                                                                                  \
+    }
+    OD_DEEP_VARIANTS(OD_LAUNCH)
+#undef OD_LAUNCH
+    return hipErrorInvalidValue;
 }
 
 }  // namespace od

@@ -2,7 +2,7 @@
 //
 // Tiles are boxes of the whole grid, not of one chare: a workgroup's lanes
 // cover EX x EY cells of the xy-plane, a ring of four cells included, and
-// march z.  Every lane holds kRows rows of one 16-byte vector and computes
+// march z.  Every lane holds R rows of one 16-byte vector and computes
 // every level (step) on all its cells; the outer cells of the ring go stale
 // by one cell a level, and only the cells whose four steps are right are
 // written.  A lane finds its cells' chare when it enters a chare along z
@@ -29,11 +29,14 @@
 // the latency of the plane loaded ahead; with every load hitting the cache it
 // runs 115-120 us per iteration at 512^3 fp64, with the stores too.
 //
+// One row a strip (R = 1) makes a box of 16 rows whose iterations are shorter:
+// what small grids, which wait for one box's planes, are quicker with.
+//
 // Measured, us per iteration, this pass against pairs at the default tile:
 // 512^3 fp64 ODF 4096 153 / 270, fp32 76 / 156; 256^3 fp64 22.6 / 39.3; 64^3
-// fp64 7.3 / 16.8; 1024^3 fp64 1077 / 2221; 768^3 octree fp64 469 / 1021.  No
-// size that the rule (deep_tiles) admits ran slower: (512,512,16) fp32, the
-// worst of those tried, 9.8 / 11.0.
+// fp64 5.1 / 16.8; 1024^3 fp64 1077 / 2221; 768^3 octree fp64 469 / 1021;
+// 211 x 163 x 157 fp32 in 27 chares, whose rows end inside vectors, 10.1 / 28.  No size
+// tried ran slower: (512,512,16) fp32, the nearest, 9.8 / 11.0.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -42,7 +45,7 @@
 
 namespace od {
 
-constexpr int kRows = 4;      // rows of a lane's strip
+constexpr int deep_waves(int dtype_bytes) { return dtype_bytes == 8 ? 8 : 4; }   // of a workgroup
 constexpr int kEX = 64;       // cells of a row: 32 lanes (fp64) or 16 (fp32)
 constexpr int kRing = kDeepSteps + 1;   // planes of boundary values kept in LDS: one per level, one written ahead
 
@@ -132,41 +135,69 @@ __device__ __forceinline__ double lane_shift_or(double v, double alt, unsigned l
     return __hiloint2double(hi, lo);
 }
 
+// A strip's R boundary values; pinned: read by every lane, with no branch
+// around the read.
+template <typename T, int R>
+__device__ __forceinline__ void shell_rows(T (&v)[R], const T* p) {
+    using V = typename DV<T>::t;
+    constexpr int VX = DV<T>::N;
+    if constexpr (R % VX == 0) {
+#pragma unroll
+        for (int q = 0; q < R / VX; ++q) {
+            V t = *reinterpret_cast<const V*>(p + q * VX);
+            asm volatile("" : "+v"(t));
+#pragma unroll
+            for (int i = 0; i < VX; ++i) v[q * VX + i] = t[i];
+        }
+    } else {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            v[r] = p[r];
+            asm volatile("" : "+v"(v[r]));
+        }
+    }
+}
+
 // Chare of a global interior cell from the per-axis index tables.
 __device__ __forceinline__ int32_t deep_owner(const DeepMap& m, int ix, int iy, int iz) {
     const int32_t e = (iz * m.k[1] + iy) * m.k[0] + ix;
     return m.owner ? m.owner[e] : e;
 }
 
-template <typename T, int NW>
+template <typename T, int R>
 struct Deep {
     using V = typename DV<T>::t;
     static constexpr int VX = DV<T>::N;
-    static constexpr int NT = NW * 64;
+    static constexpr int NW = deep_waves((int)sizeof(T)), NT = NW * 64;
     static constexpr int EX = kEX, LX = EX / VX;
-    static constexpr int NS = NT / LX;            // strips
-    static constexpr int EY = NS * kRows;
+    static constexpr int NS = NT / LX;            // strips of R rows
+    static constexpr int EY = NS * R;
+    static constexpr int RE = R > 1 ? 2 : 1;      // outer rows of a strip
     static constexpr int SH = 2 * EY + 2 * EX;    // boundary cells of a plane: x-, x+ rows, y-, y+ columns
     static_assert(SH <= NT, "one lane per boundary cell");
     struct Lds {
-        T edge[2][kDeepSteps][NS][2][EX];         // [buffer][level][strip][first row, last row]
+        T edge[2][kDeepSteps][NS][RE][EX];        // [buffer][level][strip][first row, last row]
         T shell[kRing][SH];
-        uint32_t dst[NT][kRows], dst_pz[NT][kRows];   // each lane's rows of the plane written next
+        uint32_t dst[NT][R], dst_pz[NT][R];       // each lane's rows of the plane written next
         T red[NW];
     };
 };
 
-// XF: the tile touches the grid's x- face (bit 0), its x+ face (bit 1).
-template <typename T, int NW, int XF>
+// R: rows of a lane's strip.  XF: the tile touches the grid's x- face (bit 0),
+// its x+ face (bit 1).  RAG: some vectors are not full (a chare's row, or the
+// grid's, ends inside them): the cells beside their end come from the lane after.
+template <typename T, int R, int XF, bool RAG>
 __device__ __forceinline__ T deep_tile(const DeepMap& g, const DeepTile& t, const int parity,
-                                       typename Deep<T, NW>::Lds& L, const int hints, const bool want_res) {
-    using D = Deep<T, NW>;
+                                       typename Deep<T, R>::Lds& L, const int hints, const bool want_res) {
+    using D = Deep<T, R>;
     using V = typename D::V;
     constexpr int VX = D::VX, EX = D::EX, EY = D::EY;
     const int tid = threadIdx.x, lx = tid & (D::LX - 1), strip = tid / D::LX;
-    const int nx = g.n[0], ny = g.n[1], nz = g.n[2];
-    const int xs = t.xs, ys = t.ys, z0 = t.z0, z1 = t.z1;
-    const int x = xs + lx * VX, y = ys + strip * kRows;
+    const int nv_all = g.nv, ny = g.ny, nz = g.nz;
+    const int ws = t.ws, ys = t.ys, z0 = t.z0, z1 = t.z1;
+    // lanes behind the row's last vector read that again and write nothing
+    const int w = ws + lx, wc = min(w, nv_all - 1), x = g.vx[wc], y = ys + strip * R;
+    const int nv = RAG ? g.vx[wc + 1] - x : VX;   // cells of the lane's vector
     constexpr bool xm_face = (XF & 1) != 0, xp_face = (XF & 2) != 0;
     const bool ym_face = ys == 0, yp_face = ys + EY >= ny;
     char* const ab = reinterpret_cast<char*>(g.arena);
@@ -176,62 +207,66 @@ __device__ __forceinline__ T deep_tile(const DeepMap& g, const DeepTile& t, cons
 
     // boundary cell of this lane (one of the tile's SH, where the tile
     // touches that face; else a cell of its own is read again)
-    int bf = -1, bx = x, by = y;
+    int bf = -1, bw = wc, bi = 0, by = min(y, ny - 1);   // face, vector, cell in it, row
     if (tid < EY) {
         if (xm_face) bf = 0;
-        bx = 0;
-        by = ys + tid;
+        bw = 0;
+        by = min(ys + tid, ny - 1);
     } else if (tid < 2 * EY) {
         if (xp_face) bf = 1;
-        bx = nx - 1;
-        by = ys + tid - EY;
-    } else if (tid < 2 * EY + EX) {
-        if (ym_face) bf = 2;
-        bx = xs + tid - 2 * EY;
-        by = 0;
+        bw = nv_all - 1;
+        by = min(ys + tid - EY, ny - 1);
     } else if (tid < D::SH) {
-        if (yp_face) bf = 3;
-        bx = xs + tid - 2 * EY - EX;
-        by = ny - 1;
+        const int k = tid - 2 * EY, c = k < EX ? k : k - EX;
+        if (k < EX ? ym_face : yp_face) bf = k < EX ? 2 : 3;
+        bw = min(ws + c / VX, nv_all - 1);
+        bi = min(c % VX, g.vx[bw + 1] - g.vx[bw] - 1);
+        by = k < EX ? 0 : ny - 1;
     }
 
-    typedef uint32_t __attribute__((ext_vector_type(4))) U4;
-    static_assert(kRows == 4, "a lane's row positions are one vector");
-    U4& l_dst = *reinterpret_cast<U4*>(&L.dst[tid][0]);
-    U4& l_dst_pz = *reinterpret_cast<U4*>(&L.dst_pz[tid][0]);
     // Positions of the lane's rows in plane q of parity par, and the steps to
-    // the next plane, into the lane's l_dst and l_dst_pz.  Entered once per
+    // the next plane, into the lane's L.dst and L.dst_pz.  Entered once per
     // chare along z; one row at a time and through LDS, so that it takes few
     // registers from the loop around it.
     auto locate = [&](int q, int par) {
         const int zc = q < 0 ? 0 : (q >= nz ? nz - 1 : q);
-        const int ix = g.ix[x], iz = g.iz[zc];
+        const int ix = g.vi[wc], iz = g.iz[zc];
         const bool in = q >= 0 && q < nz;
 #pragma unroll 1
-        for (int r = 0; r < kRows; ++r) {
-            const int32_t c = deep_owner(g, ix, g.iy[y + r], iz);
+        for (int r = 0; r < R; ++r) {
+            const int yr = min(y + r, ny - 1);
+            const int32_t c = deep_owner(g, ix, g.iy[yr], iz);
             const int32_t* o = g.corigin + 3 * c;
             const BlockDev* B = g.blocks + (in ? c : g.dir_pb[6 * c + (q < 0 ? 4 : 5)]);
-            L.dst[tid][r] = (uint32_t)((B->off[par] + (x - o[0]) + (int64_t)(y + r - o[1]) * B->py +
+            L.dst[tid][r] = (uint32_t)((B->off[par] + (x - o[0]) + (int64_t)(yr - o[1]) * B->py +
                                         (in ? (int64_t)(q - o[2]) * B->pz : 0)) / VX);
             L.dst_pz[tid][r] = in ? (uint32_t)(B->pz / VX) : 0u;
         }
     };
-    U4 src, src_pz;       // the plane loaded next
-    const T* bsrc;        // its boundary cell
+    uint32_t src[R], src_pz[R];   // the plane loaded next
+    const T* bsrc;                // its boundary cell
     uint32_t b_pz;
     auto locate_src = [&](int q) {
-        const U4 d = l_dst, d_pz = l_dst_pz;
+        uint32_t d[R], d_pz[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            d[r] = L.dst[tid][r];
+            d_pz[r] = L.dst_pz[tid][r];
+        }
         locate(q, parity);
-        src = l_dst;
-        src_pz = l_dst_pz;
-        l_dst = d;
-        l_dst_pz = d_pz;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            src[r] = L.dst[tid][r];
+            src_pz[r] = L.dst_pz[tid][r];
+            L.dst[tid][r] = d[r];
+            L.dst_pz[tid][r] = d_pz[r];
+        }
         bsrc = reinterpret_cast<const T*>(vec(src[0]));
         b_pz = src_pz[0] * VX;
         if (bf >= 0) {
             const int zc = q < 0 ? 0 : (q >= nz ? nz - 1 : q);
-            const int32_t c = deep_owner(g, g.ix[bx], g.iy[by], g.iz[zc]);
+            const int bx = g.vx[bw] + bi;
+            const int32_t c = deep_owner(g, g.vi[bw], g.iy[by], g.iz[zc]);
             const int32_t* o = g.corigin + 3 * c;
             const BlockDev* B = g.blocks + g.dir_pb[6 * c + bf];
             bsrc = reinterpret_cast<const T*>(ab) + (B->off[parity] + (bf < 2 ? 0 : bx - o[0]) +
@@ -242,23 +277,24 @@ __device__ __forceinline__ T deep_tile(const DeepMap& g, const DeepTile& t, cons
     };
     // first plane behind q's chares (uniform)
     auto next_of = [&](int q) -> int { return q < 0 ? 0 : (q >= nz ? INT32_MAX : g.zn[q]); };
-    const bool st_x = x >= t.xo0 && x < t.xo1;
-    const int r0 = st_x ? t.yo0 - y : kRows, r1 = t.yo1 - y;   // rows r0 <= r < r1 are written
-    const bool x_first = lx == 0, x_last = x + VX == nx;
+    const bool st_x = w >= t.wo0 && w < t.wo1;
+    const int r0 = st_x ? t.yo0 - y : R, r1 = t.yo1 - y;   // rows r0 <= r < r1 are written
+    const bool x_first = w == 0, x_last = w == nv_all - 1, y_first = ym_face && strip == 0, y_last = y + R == ny;
     const unsigned long long m_first = __ballot(x_first), m_last = __ballot(x_last);
 
     const int jlo = max(z0 - kDeepSteps, -1), jhi = z1 - 1 + kDeepSteps;
     const int lmax = min(jhi, nz);
     int lq = jlo, lnext = next_of(jlo), dnext = next_of(z0);
-    l_dst = l_dst_pz = (U4)0u;
+#pragma unroll
+    for (int r = 0; r < R; ++r) L.dst[tid][r] = L.dst_pz[tid][r] = 0u;
     locate_src(jlo);
     locate(z0, parity ^ 1);
 
-    V F[kRows];   // the plane loaded ahead
+    V F[R];   // the plane loaded ahead
     T bv;
     auto load = [&]() {
 #pragma unroll
-        for (int r = 0; r < kRows; ++r) F[r] = *vec(src[r]);
+        for (int r = 0; r < R; ++r) F[r] = *vec(src[r]);
         bv = *bsrc;
         if (lq < lmax) {
             ++lq;
@@ -266,18 +302,19 @@ __device__ __forceinline__ T deep_tile(const DeepMap& g, const DeepTile& t, cons
                 lnext = next_of(lq);
                 locate_src(lq);
             } else {
-                src += src_pz;
+#pragma unroll
+                for (int r = 0; r < R; ++r) src[r] += src_pz[r];
                 bsrc += b_pz;
             }
         }
     };
     load();
 
-    V U[kDeepSteps][kRows], S[kDeepSteps][kRows];
+    V U[kDeepSteps][R], S[kDeepSteps][R];
 #pragma unroll
     for (int s = 0; s < kDeepSteps; ++s)
 #pragma unroll
-        for (int r = 0; r < kRows; ++r) U[s][r] = S[s][r] = (V)(T)1;
+        for (int r = 0; r < R; ++r) U[s][r] = S[s][r] = (V)(T)1;
     T res = 0;
     const int bslot = tid < D::SH ? tid : 0;
 
@@ -286,9 +323,9 @@ __device__ __forceinline__ T deep_tile(const DeepMap& g, const DeepTile& t, cons
     for (int j = jlo; j <= jhi; ++j, slot0 = slot0 + 1 == kRing ? 0 : slot0 + 1) {
         const int b = j & 1;
         // finish each level's plane and stage the strips' outer rows
-        V N[kDeepSteps + 1][kRows];
+        V N[kDeepSteps + 1][R];
 #pragma unroll
-        for (int r = 0; r < kRows; ++r) N[0][r] = F[r];
+        for (int r = 0; r < R; ++r) N[0][r] = F[r];
         if (tid < D::SH) L.shell[slot0][bslot] = bv;
         __builtin_amdgcn_sched_barrier(0);
         load();
@@ -296,25 +333,25 @@ __device__ __forceinline__ T deep_tile(const DeepMap& g, const DeepTile& t, cons
 #pragma unroll
         for (int s = 0; s < kDeepSteps; ++s) {
             *reinterpret_cast<V*>(&L.edge[b][s][strip][0][lx * VX]) = N[s][0];
-            *reinterpret_cast<V*>(&L.edge[b][s][strip][1][lx * VX]) = N[s][kRows - 1];
+            if constexpr (R > 1) *reinterpret_cast<V*>(&L.edge[b][s][strip][1][lx * VX]) = N[s][R - 1];
             const int p = j - 1 - s;
             __builtin_amdgcn_sched_barrier(0);
             if (p == -1 || p == nz) {
                 // a boundary plane keeps its values
 #pragma unroll
-                for (int r = 0; r < kRows; ++r) N[s + 1][r] = U[s][r];
+                for (int r = 0; r < R; ++r) N[s + 1][r] = U[s][r];
             } else {
-                V q[kRows];
+                V q[R];
                 float m = __builtin_huge_valf();
 #pragma unroll
-                for (int r = 0; r < kRows; ++r) {
+                for (int r = 0; r < R; ++r) {
                     q[r] = S[s][r] + N[s][r];
 #pragma unroll
                     for (int i = 0; i < VX; i += 2) m = min3_abs(m, (T)q[r][i], (T)q[r][i + 1]);
                 }
                 auto quick = [&]() {
 #pragma unroll
-                    for (int r = 0; r < kRows; ++r)
+                    for (int r = 0; r < R; ++r)
 #pragma unroll
                         for (int i = 0; i < VX; ++i)
                             N[s + 1][r][i] = fma_((T)q[r][i], Sixth<T>::hi, (T)q[r][i] * Sixth<T>::lo);
@@ -325,7 +362,7 @@ __device__ __forceinline__ T deep_tile(const DeepMap& g, const DeepTile& t, cons
                 if constexpr (sizeof(T) == 8) quick();
                 if (__builtin_expect(divide, 0)) {
 #pragma unroll
-                    for (int r = 0; r < kRows; ++r)
+                    for (int r = 0; r < R; ++r)
 #pragma unroll
                         for (int i = 0; i < VX; ++i) N[s + 1][r][i] = q[r][i] / (T)6;
                 } else if constexpr (sizeof(T) == 4) {
@@ -337,9 +374,11 @@ __device__ __forceinline__ T deep_tile(const DeepMap& g, const DeepTile& t, cons
         // write the fourth step
         const int p4 = j - kDeepSteps;
         if (p4 >= z0) {
-            const U4 d = l_dst;
+            uint32_t d[R];
 #pragma unroll
-            for (int r = 0; r < kRows; ++r)
+            for (int r = 0; r < R; ++r) d[r] = L.dst[tid][r];
+#pragma unroll
+            for (int r = 0; r < R; ++r)
                 if (r >= r0 && r < r1) {
                     V* o = vec(d[r]);
                     if (hints & 1)
@@ -349,11 +388,11 @@ __device__ __forceinline__ T deep_tile(const DeepMap& g, const DeepTile& t, cons
                 }
             if (want_res) {
 #pragma unroll
-                for (int r = 0; r < kRows; ++r)
+                for (int r = 0; r < R; ++r)
                     if (r >= r0 && r < r1) {
 #pragma unroll
                         for (int i = 0; i < VX; ++i)
-                            res = max_abs(res, (T)(N[kDeepSteps][r][i] - U[kDeepSteps - 1][r][i]));
+                            if (!RAG || i < nv) res = max_abs(res, (T)(N[kDeepSteps][r][i] - U[kDeepSteps - 1][r][i]));
                     }
             }
             if (p4 + 1 < z1) {
@@ -361,7 +400,8 @@ __device__ __forceinline__ T deep_tile(const DeepMap& g, const DeepTile& t, cons
                     dnext = next_of(dnext);
                     locate(p4 + 1, parity ^ 1);
                 } else {
-                    l_dst = d + l_dst_pz;
+#pragma unroll
+                    for (int r = 0; r < R; ++r) L.dst[tid][r] = d[r] + L.dst_pz[tid][r];
                 }
             }
         }
@@ -373,49 +413,46 @@ __device__ __forceinline__ T deep_tile(const DeepMap& g, const DeepTile& t, cons
         for (int s = kDeepSteps - 1; s >= 0; --s) {
             const int slot = slot0 >= s ? slot0 - s : slot0 - s + kRing;
             __builtin_amdgcn_sched_barrier(0);
-            const T* ymp = &L.edge[b][s][strip > 0 ? strip - 1 : 0][1][lx * VX];
+            const T* ymp = &L.edge[b][s][strip > 0 ? strip - 1 : 0][D::RE - 1][lx * VX];
             const T* ypp = &L.edge[b][s][strip < D::NS - 1 ? strip + 1 : strip][0][lx * VX];
-            if (ym_face && strip == 0) ymp = &L.shell[slot][2 * EY + lx * VX];
-            if (yp_face && strip == D::NS - 1) ypp = &L.shell[slot][2 * EY + EX + lx * VX];
+            if (y_first) ymp = &L.shell[slot][2 * EY + lx * VX];
+            if (y_last) ypp = &L.shell[slot][2 * EY + EX + lx * VX];
             const V yme = *reinterpret_cast<const V*>(ymp);
             const V ype = *reinterpret_cast<const V*>(ypp);
             // boundary values beside the row's ends, for the strip's rows
-            V bm[kRows / VX], bp[kRows / VX];
+            T bm[R], bp[R];
+            if constexpr (xm_face) shell_rows(bm, &L.shell[slot][strip * R]);
+            if constexpr (xp_face) shell_rows(bp, &L.shell[slot][EY + strip * R]);
 #pragma unroll
-            for (int q = 0; q < kRows / VX; ++q) {
-                // (pinned: read by every lane, with no branch around the read)
-                if constexpr (xm_face) {
-                    bm[q] = *reinterpret_cast<const V*>(&L.shell[slot][strip * kRows + q * VX]);
-                    asm volatile("" : "+v"(bm[q]));
-                }
-                if constexpr (xp_face) {
-                    bp[q] = *reinterpret_cast<const V*>(&L.shell[slot][EY + strip * kRows + q * VX]);
-                    asm volatile("" : "+v"(bp[q]));
-                }
-            }
-#pragma unroll
-            for (int r = 0; r < kRows; ++r) {
+            for (int r = 0; r < R; ++r) {
                 const V c = N[s][r];
+                // the row's last cell in this lane, what the lane after reads
+                T tail = c[VX - 1];
+                if constexpr (RAG) {
+#pragma unroll
+                    for (int i = 0; i < VX - 1; ++i) tail = nv == i + 1 ? (T)c[i] : tail;
+                }
                 T left, right;
                 if constexpr (xm_face && sizeof(T) == 8) {
-                    left = lane_shift_or<kShr1>(c[VX - 1], bm[r / VX][r % VX], m_first);
+                    left = lane_shift_or<kShr1>(tail, bm[r], m_first);
                 } else {
-                    left = lane_shift<kShr1>((T)c[VX - 1]);
-                    if constexpr (xm_face) left = x_first ? (T)bm[r / VX][r % VX] : left;
+                    left = lane_shift<kShr1>(tail);
+                    if constexpr (xm_face) left = x_first ? bm[r] : left;
                 }
                 if constexpr (xp_face && sizeof(T) == 8) {
-                    right = lane_shift_or<kShl1>(c[0], bp[r / VX][r % VX], m_last);
+                    right = lane_shift_or<kShl1>(c[0], bp[r], m_last);
                 } else {
                     right = lane_shift<kShl1>((T)c[0]);
-                    if constexpr (xp_face) right = x_last ? (T)bp[r / VX][r % VX] : right;
+                    if constexpr (xp_face) right = x_last ? bp[r] : right;
                 }
                 const V ym = r > 0 ? N[s][r > 0 ? r - 1 : 0] : yme;
-                const V yp = r < kRows - 1 ? N[s][r < kRows - 1 ? r + 1 : r] : ype;
+                const V yp = r < R - 1 ? N[s][r < R - 1 ? r + 1 : r] : ype;
                 V a;
 #pragma unroll
                 for (int i = 0; i < VX; ++i) {
                     const T xm = i > 0 ? c[i > 0 ? i - 1 : 0] : left;
-                    const T xp = i < VX - 1 ? c[i < VX - 1 ? i + 1 : i] : right;
+                    T xp = i < VX - 1 ? c[i < VX - 1 ? i + 1 : i] : right;
+                    if constexpr (RAG) xp = i < VX - 1 && i + 1 >= nv ? right : xp;
                     T w = xm + xp;
                     w = w + ym[i];
                     w = w + yp[i];
@@ -430,19 +467,21 @@ __device__ __forceinline__ T deep_tile(const DeepMap& g, const DeepTile& t, cons
     return res;
 }
 
-// Waves of a workgroup: 64 x 64 cells either way.  One fp64 workgroup fills a
-// CU's registers and LDS, two fp32 ones do.
-constexpr int deep_waves(int dtype_bytes) { return dtype_bytes == 8 ? 8 : 4; }
-constexpr int deep_per_cu(int dtype_bytes) { return dtype_bytes == 8 ? 1 : 2; }
+// Occupancy the kernels are compiled for: the levels of four rows take half of
+// a SIMD's registers per wave, of one row a quarter of that.
+#define OD_DEEP_OCC(R) __attribute__((amdgpu_waves_per_eu(R == 1 ? 4 : 2, R == 1 ? 4 : 2)))
+#define OD_DEEP_VARIANTS(X)                                                                  \
+    X(double, 4, false) X(double, 4, true) X(double, 1, false) X(double, 1, true)            \
+    X(float, 4, false) X(float, 4, true) X(float, 1, false) X(float, 1, true)
 
-template <typename T, int NW>
-__device__ __forceinline__ T deep_box(const DeepMap& g, const DeepTile& t, int parity, typename Deep<T, NW>::Lds& L,
+template <typename T, int R, bool RAG>
+__device__ __forceinline__ T deep_box(const DeepMap& g, const DeepTile& t, int parity, typename Deep<T, R>::Lds& L,
                                       int hints, bool want_res) {
-    const bool m = t.xs == 0, p = t.xs + Deep<T, NW>::EX >= g.n[0];
-    return m ? (p ? deep_tile<T, NW, 3>(g, t, parity, L, hints, want_res)
-                  : deep_tile<T, NW, 1>(g, t, parity, L, hints, want_res))
-             : (p ? deep_tile<T, NW, 2>(g, t, parity, L, hints, want_res)
-                  : deep_tile<T, NW, 0>(g, t, parity, L, hints, want_res));
+    const bool m = t.ws == 0, p = t.ws + Deep<T, R>::LX >= g.nv;
+    return m ? (p ? deep_tile<T, R, 3, RAG>(g, t, parity, L, hints, want_res)
+                  : deep_tile<T, R, 1, RAG>(g, t, parity, L, hints, want_res))
+             : (p ? deep_tile<T, R, 2, RAG>(g, t, parity, L, hints, want_res)
+                  : deep_tile<T, R, 0, RAG>(g, t, parity, L, hints, want_res));
 }
 
 }  // namespace od

@@ -1936,12 +1936,12 @@ k_msgdriven2(MsgArgs a) {
 // rounds, so a counter would find nothing to balance.  Bound as the pass; us
 // per iteration against pairs from counters: 512^3 fp64 ODF 512 157 / 292,
 // fp32 85 / 166, 256^3 fp64 24.3 / 46.1, 64^3 fp64 8.0 / 18.4.
-template <typename T, int NW>
-__global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
+template <typename T, int R, bool RAG>
+__global__ void __launch_bounds__(deep_waves((int)sizeof(T)) * 64) OD_DEEP_OCC(R)
 k_deep_persistent(DeepMap g, const DeepTile* __restrict__ tiles, int32_t ntiles, int parity, int64_t passes,
                   unsigned long long* __restrict__ res, unsigned int* bar, unsigned int* err, int64_t wait_ticks,
                   int hints, int want_res) {
-    __shared__ __align__(16) typename Deep<T, NW>::Lds L;
+    __shared__ __align__(16) typename Deep<T, R>::Lds L;
     __shared__ int s_xcd;
     __shared__ unsigned int s_xwgs, s_nxcd;
     if (passes > 1 && !persist_register(bar, err, wait_ticks, &s_xcd, &s_xwgs, &s_nxcd)) return;
@@ -1951,11 +1951,11 @@ k_deep_persistent(DeepMap g, const DeepTile* __restrict__ tiles, int32_t ntiles,
         if (blockIdx.x == 0 && threadIdx.x == 0) res[p] = 0ull;
         T r = 0;
         for (int32_t i = (int32_t)blockIdx.x; i < ntiles; i += (int32_t)gridDim.x) {
-            const T b = deep_box<T, NW>(g, tiles[i], p, L, hints, last);
+            const T b = deep_box<T, R, RAG>(g, tiles[i], p, L, hints, last);
             r = b > r ? b : r;
             __syncthreads();   // the LDS is the next box's
         }
-        if (last) wg_residual<T, NW * 64>(r, &res[p ^ 1], L.red);
+        if (last) wg_residual<T, Deep<T, R>::NT>(r, &res[p ^ 1], L.red);
         if (it + 1 < passes && !xcd_barrier(bar, err, wait_ticks, nullptr, s_xcd, s_xwgs, s_nxcd)) return;
     }
     persist_cleanup(bar);
@@ -1965,16 +1965,16 @@ k_deep_persistent(DeepMap g, const DeepTile* __restrict__ tiles, int32_t ntiles,
 // waits for those whose cells its lanes read (the lists reach its whole ring).
 // us per iteration against tasks of two steps: 512^3 fp64 ODF 512 149 / 292,
 // fp32 100 / 166, 256^3 fp64 29 / 52, 64^3 fp64 7.7 / 18.6.
-template <typename T, int NW>
-__global__ void __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 2)))
+template <typename T, int R, bool RAG>
+__global__ void __launch_bounds__(deep_waves((int)sizeof(T)) * 64) OD_DEEP_OCC(R)
 k_deep_msg(MsgArgs a, DeepMap g, const DeepTile* __restrict__ tiles) {
-    __shared__ __align__(16) typename Deep<T, NW>::Lds L;
-    __shared__ double red[NW];
+    __shared__ __align__(16) typename Deep<T, R>::Lds L;
+    __shared__ double red[Deep<T, R>::NW];
     const int32_t tgt = ld_rlx(&a.target[0]);
     auto sweep = [&](int32_t i, int32_t step) -> double {
-        return (double)deep_box<T, NW>(g, tiles[i], step & 1, L, a.hints, step + 1 == tgt);
+        return (double)deep_box<T, R, RAG>(g, tiles[i], step & 1, L, a.hints, step + 1 == tgt);
     };
-    queue_loop<NW * 64>(a, sweep, red);
+    queue_loop<Deep<T, R>::NT>(a, sweep, red);
 }
 
 // Serving: tiles of independent fp64 and fp32 solves in one launch.  The two
@@ -2439,38 +2439,51 @@ int persistent_max_grid(int dtype_bytes, int tx, int ty, int kind, int max_waves
     return 0;
 }
 
-int deep_max_grid(int dtype_bytes) {
+int deep_max_grid(int dtype_bytes, const DeepPlan& d) {
     int dev = 0, ncu = 0;
     if (hipGetDevice(&dev) != hipSuccess) return 0;
     if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-    constexpr int W8 = deep_waves(8), W4 = deep_waves(4);
-    const int a = dtype_bytes == 8 ? coop_cap(k_deep_persistent<double, W8>, W8 * 64, "od::k_deep_persistent<double, " + std::to_string(W8) + ">", 8)
-                                   : coop_cap(k_deep_persistent<float, W4>, W4 * 64, "od::k_deep_persistent<float, " + std::to_string(W4) + ">", 8);
-    const int b = dtype_bytes == 8 ? coop_cap(k_deep_msg<double, W8>, W8 * 64, "od::k_deep_msg<double, " + std::to_string(W8) + ">", 8)
-                                   : coop_cap(k_deep_msg<float, W4>, W4 * 64, "od::k_deep_msg<float, " + std::to_string(W4) + ">", 8);
-    return (a < b ? a : b) * ncu;
+#define OD_OCC(T, R, RAG)                                                                                  \
+    if (dtype_bytes == (int)sizeof(T) && d.rows == R && d.ragged == RAG) {                                 \
+        const std::string args = "<" #T ", " #R ", " #RAG ">";                                             \
+        const int a = coop_cap(k_deep_persistent<T, R, RAG>, Deep<T, R>::NT, "od::k_deep_persistent" + args, 8); \
+        const int b = coop_cap(k_deep_msg<T, R, RAG>, Deep<T, R>::NT, "od::k_deep_msg" + args, 8);         \
+        return (a < b ? a : b) * ncu;                                                                      \
+    }
+    OD_DEEP_VARIANTS(OD_OCC)
+#undef OD_OCC
+    return 0;
 }
 
-hipError_t launch_deep_persistent(int dtype_bytes, hipStream_t st, int grid, const DeepMap& g, const DeepTile* tiles,
-                                  int32_t ntiles, int parity, int64_t passes, unsigned long long* res,
+hipError_t launch_deep_persistent(int dtype_bytes, const DeepPlan& d, hipStream_t st, int grid, const DeepMap& g,
+                                  const DeepTile* tiles, int parity, int64_t passes, unsigned long long* res,
                                   unsigned int* bar, unsigned int* err, int64_t wait_ticks, int hints, bool want_res) {
     if (passes <= 0) return hipSuccess;
     DeepMap m = g;
     int w = want_res ? 1 : 0;
+    int32_t ntiles = (int32_t)d.tiles.size();
     void* args[] = {&m, &tiles, &ntiles, &parity, &passes, &res, &bar, &err, &wait_ticks, &hints, &w};
-    const void* fn = dtype_bytes == 8 ? reinterpret_cast<const void*>(k_deep_persistent<double, deep_waves(8)>)
-                                      : reinterpret_cast<const void*>(k_deep_persistent<float, deep_waves(4)>);
-    return hipLaunchCooperativeKernel(fn, dim3(grid), dim3(deep_waves(dtype_bytes) * 64), args, 0, st);
+#define OD_LAUNCH(T, R, RAG)                                                                               \
+    if (dtype_bytes == (int)sizeof(T) && d.rows == R && d.ragged == RAG)                                   \
+        return hipLaunchCooperativeKernel(reinterpret_cast<const void*>(k_deep_persistent<T, R, RAG>), dim3(grid), \
+                                          dim3(Deep<T, R>::NT), args, 0, st);
+    OD_DEEP_VARIANTS(OD_LAUNCH)
+#undef OD_LAUNCH
+    return hipErrorInvalidValue;
 }
 
-hipError_t launch_deep_msg(int dtype_bytes, hipStream_t st, int grid, const MsgArgs& a, const DeepMap& g,
-                           const DeepTile* tiles) {
+hipError_t launch_deep_msg(int dtype_bytes, const DeepPlan& d, hipStream_t st, int grid, const MsgArgs& a,
+                           const DeepMap& g, const DeepTile* tiles) {
     MsgArgs ma = a;
     DeepMap m = g;
     void* args[] = {&ma, &m, &tiles};
-    const void* fn = dtype_bytes == 8 ? reinterpret_cast<const void*>(k_deep_msg<double, deep_waves(8)>)
-                                      : reinterpret_cast<const void*>(k_deep_msg<float, deep_waves(4)>);
-    return hipLaunchCooperativeKernel(fn, dim3(grid), dim3(deep_waves(dtype_bytes) * 64), args, 0, st);
+#define OD_LAUNCH(T, R, RAG)                                                                               \
+    if (dtype_bytes == (int)sizeof(T) && d.rows == R && d.ragged == RAG)                                   \
+        return hipLaunchCooperativeKernel(reinterpret_cast<const void*>(k_deep_msg<T, R, RAG>), dim3(grid), \
+                                          dim3(Deep<T, R>::NT), args, 0, st);
+    OD_DEEP_VARIANTS(OD_LAUNCH)
+#undef OD_LAUNCH
+    return hipErrorInvalidValue;
 }
 
 __global__ void k_fill_i32(int32_t* p, int32_t n, int32_t v) {

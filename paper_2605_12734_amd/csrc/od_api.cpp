@@ -665,16 +665,15 @@ std::string build_layout(const od_config& cfg, Grid& G) {
     G.L.xexp = cv.take(std::max<size_t>(G.xexp_h.size(), 1) * sizeof(XExpDev));
     G.L.total = G.L.total_pairs = align_up(cv.off, kAlign) + kAlign;
     // four-step passes, behind everything else (a workspace that ends here
-    // runs pairs): tiles, and per axis the index of each coordinate (x, y, z)
-    // and the first plane behind each plane's blocks
-    G.deep_h.clear();
-    if (deep_possible(G) && G.L.field_end / 16 <= UINT32_MAX) G.deep_h = deep_tiles(p, s);
-    if (!G.deep_h.empty()) {
-        G.L.deep = cv.take(G.deep_h.size() * sizeof(DeepTile));
-        G.L.deep_tab = cv.take((size_t)(p.n[0] + p.n[1] + 2 * p.n[2]) * 4);
+    // runs pairs): boxes, and per axis the tables of DeepMap
+    G.deep_plan = DeepPlan{};
+    if (deep_possible(G) && G.L.field_end / 16 <= UINT32_MAX) G.deep_plan = od::deep_plan(p, s);
+    if (!G.deep_plan.tiles.empty()) {
+        G.L.deep = cv.take(G.deep_plan.tiles.size() * sizeof(DeepTile));
+        G.L.deep_tab = cv.take((G.deep_plan.vx.size() + G.deep_plan.vi.size() + (size_t)(p.n[1] + 2 * p.n[2])) * 4);
         if (cfg.exec == OD_MSGDRIVEN) {
-            const size_t nd = G.deep_h.size();
-            deep_deps(G.deep_h, s, G.deep_ptr, G.deep_idx);
+            const size_t nd = G.deep_plan.tiles.size();
+            deep_deps(G.deep_plan, s, G.deep_ptr, G.deep_idx);
             G.L.deep_dep = cv.take((G.deep_ptr.size() + G.deep_idx.size()) * 4);
             G.L.deep_done = cv.take(nd * 4);
             G.L.deep_pend = cv.take(nd * 2 * 4);
@@ -897,13 +896,13 @@ od_status Grid::setup_cooperative(bool fresh_plan) {
     if (grid >= kNumXcd) grid -= grid % kNumXcd;
     grid_wgs = grid;
     if (grid <= 0) return fail(OD_EHIP, "no co-resident workgroups for the cooperative kernel");
-    if (!deep_h.empty() && deep_wgs == 0) {
+    if (!deep_plan.tiles.empty() && deep_wgs == 0) {
         // whole XCD rounds, but never fewer than the boxes where they all fit:
         // 240 workgroups for the 243 boxes of 512^3 take two rounds (238 us per
         // iteration instead of 156)
-        deep_wgs = std::min<int>(deep_max_grid(s), (int)align_up(deep_h.size(), kNumXcd));
+        deep_wgs = std::min<int>(deep_max_grid(s, deep_plan), (int)align_up(deep_plan.tiles.size(), kNumXcd));
         if (deep_wgs >= kNumXcd) deep_wgs -= deep_wgs % kNumXcd;
-        if (deep_wgs <= 0) deep_h.clear();
+        if (deep_wgs <= 0) deep_plan.tiles.clear();
     }
     if (cfg.exec == OD_PERSISTENT) {
         std::vector<TileHost> list = base_tiles;
@@ -971,33 +970,39 @@ od_status Grid::upload() {
     if (e == hipSuccess) e = put(L.dep_ptr, dep_ptr.data(), dep_ptr.size() * 4);
     if (e == hipSuccess) e = put(L.dep_idx, dep_idx.data(), dep_idx.size() * 4);
     std::vector<int32_t> tab;
-    if (!deep_h.empty()) {
-        for (int d = 0; d < 3; ++d)
+    if (!deep_plan.tiles.empty()) {
+        tab = deep_plan.vx;
+        tab.insert(tab.end(), deep_plan.vi.begin(), deep_plan.vi.end());
+        const size_t ty = tab.size();
+        for (int d = 1; d < 3; ++d)
             for (int64_t v = 0; v < p.n[d]; ++v) tab.push_back(p.regular ? cidx[d][(size_t)v] : (int32_t)(v / p.gran));
-        const size_t z = (size_t)(p.n[0] + p.n[1]);
+        const size_t tz = ty + (size_t)p.n[1], tn = tab.size();
         for (int64_t v = 0; v < p.n[2]; ++v) {
             int64_t q = v + 1;
-            while (q < p.n[2] && tab[z + (size_t)q] == tab[z + (size_t)v]) ++q;
+            while (q < p.n[2] && tab[tz + (size_t)q] == tab[tz + (size_t)v]) ++q;
             tab.push_back((int32_t)q);
         }
-        if (e == hipSuccess) e = put(L.deep, deep_h.data(), deep_h.size() * sizeof(DeepTile));
+        if (e == hipSuccess) e = put(L.deep, deep_plan.tiles.data(), deep_plan.tiles.size() * sizeof(DeepTile));
         if (e == hipSuccess) e = put(L.deep_tab, tab.data(), tab.size() * 4);
-        if (cfg.exec == OD_MSGDRIVEN) {
-            if (e == hipSuccess) e = put(L.deep_dep, deep_ptr.data(), deep_ptr.size() * 4);
-            if (e == hipSuccess) e = put(L.deep_dep + deep_ptr.size() * 4, deep_idx.data(), deep_idx.size() * 4);
-        }
         const int32_t* t = reinterpret_cast<const int32_t*>(cp(L.deep_tab));
+        deep_map.vx = t;
+        deep_map.vi = t + deep_plan.vx.size();
+        deep_map.iy = t + ty;
+        deep_map.iz = t + tz;
+        deep_map.zn = t + tn;
+        deep_map.nv = (int32_t)deep_plan.vi.size();
+        deep_map.ny = (int32_t)p.n[1];
+        deep_map.nz = (int32_t)p.n[2];
         deep_map.arena = base;
         deep_map.blocks = reinterpret_cast<const BlockDev*>(cp(L.blocks));
-        deep_map.ix = t;
-        deep_map.iy = t + p.n[0];
-        deep_map.iz = deep_map.iy + p.n[1];
-        deep_map.zn = deep_map.iz + p.n[2];
         deep_map.owner = p.regular ? nullptr : reinterpret_cast<const int32_t*>(cp(L.owner));
         deep_map.corigin = reinterpret_cast<const int32_t*>(cp(L.corigin));
         deep_map.dir_pb = reinterpret_cast<const int32_t*>(cp(L.dir_pb));
         for (int d = 0; d < 2; ++d) deep_map.k[d] = p.regular ? p.k[d] : (int32_t)p.og[d];
-        for (int d = 0; d < 3; ++d) deep_map.n[d] = (int32_t)p.n[d];
+        if (cfg.exec == OD_MSGDRIVEN) {
+            if (e == hipSuccess) e = put(L.deep_dep, deep_ptr.data(), deep_ptr.size() * 4);
+            if (e == hipSuccess) e = put(L.deep_dep + deep_ptr.size() * 4, deep_idx.data(), deep_idx.size() * 4);
+        }
     }
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) return fail(OD_EHIP, std::string("descriptor upload: ") + hipGetErrorString(e));
@@ -1118,8 +1123,11 @@ od_status Grid::fused_deep(hipStream_t s2, int par, int64_t step, bool last) {
                                      res_ptr(), 0, 0, m, step, mode());
         if (e0 != hipSuccess) return fail(OD_EHIP, std::string("re-run launch: ") + hipGetErrorString(e0));
     }
-    hipError_t e = launch_deep(s, s2, deep_map, reinterpret_cast<const DeepTile*>(cp(L.deep)), (int32_t)deep_h.size(),
-                               par, res_ptr(), 0, 1, mode(), last);
+    return fused_deep_pass(s2, par, last);
+}
+
+od_status Grid::fused_deep_pass(hipStream_t s2, int par, bool last) {
+    hipError_t e = launch_deep(s, deep_plan, s2, deep_map, reinterpret_cast<const DeepTile*>(cp(L.deep)), par, res_ptr(), 0, 1, mode(), last);
     if (e != hipSuccess) return fail(OD_EHIP, std::string("four-step sweep launch: ") + hipGetErrorString(e));
     return OD_OK;
 }
@@ -1197,8 +1205,8 @@ od_status Grid::persistent_run(int64_t n) {
     }
     if (deep() && n >= kDeepSteps) {
         const int64_t passes = n / kDeepSteps;
-        hipError_t e = launch_deep_persistent(s, st, deep_wgs, deep_map, reinterpret_cast<const DeepTile*>(cp(L.deep)),
-                                              (int32_t)deep_h.size(), parity, passes, res_ptr(),
+        hipError_t e = launch_deep_persistent(s, deep_plan, st, deep_wgs, deep_map, reinterpret_cast<const DeepTile*>(cp(L.deep)),
+                                              parity, passes, res_ptr(),
                                               reinterpret_cast<unsigned int*>(cp(L.bar)),
                                               reinterpret_cast<unsigned int*>(cp(L.err)),
                                               device_wait_ticks(cfg.wait_s > 0 ? cfg.wait_s : 10.0), mode(),
@@ -1265,7 +1273,7 @@ od_status Grid::msgdriven_run(int64_t n) {
     // one-step launch
     if (deep()) {
         const int64_t per_box = std::max<int64_t>(1, std::min<int64_t>(((int64_t)1 << 16) - 1,
-                                                                       ((int64_t)1 << 23) / (int64_t)deep_h.size()));
+                                                                       ((int64_t)1 << 23) / (int64_t)deep_plan.tiles.size()));
         for (int64_t m = n / kDeepSteps; m > 0;) {
             const int64_t k = std::min(m, per_box);
             od_status st2 = msgdriven_launch(k, kDeepSteps);
@@ -1293,7 +1301,7 @@ od_status Grid::msgdriven_launch(int64_t n, int steps) {
     // between launches every step counter of the kind used last holds flips
     if ((boxes ? 1 : 0) != msg_counters) {
         hipError_t e0 = launch_fill_i32(st, reinterpret_cast<int32_t*>(cp(boxes ? L.deep_done : L.done)),
-                                        (int32_t)(boxes ? deep_h.size() : tiles_h.size()), (int32_t)flips);
+                                        (int32_t)(boxes ? deep_plan.tiles.size() : tiles_h.size()), (int32_t)flips);
         if (e0 != hipSuccess) return fail(OD_EHIP, std::string("step counters: ") + hipGetErrorString(e0));
         msg_counters = boxes ? 1 : 0;
     }
@@ -1329,14 +1337,14 @@ od_status Grid::msgdriven_launch(int64_t n, int steps) {
     a.qhead = reinterpret_cast<unsigned int*>(cp(L.qctl));
     a.qsteps = (int32_t)n;
     if (boxes) {
-        a.ntiles = (int32_t)deep_h.size();
+        a.ntiles = (int32_t)deep_plan.tiles.size();
         a.dep_ptr = reinterpret_cast<const int32_t*>(cp(L.deep_dep));
         a.dep_idx = a.dep_ptr + deep_ptr.size();
         a.done = reinterpret_cast<int32_t*>(cp(L.deep_done));
         a.pend = reinterpret_cast<int32_t*>(cp(L.deep_pend));
         a.xpub = reinterpret_cast<uint8_t*>(cp(L.deep_xpub));
         a.qslots = reinterpret_cast<unsigned long long*>(cp(L.deep_slots));
-        a.pslots = a.qslots + (2 * deep_h.size() + 8);
+        a.pslots = a.qslots + (2 * deep_plan.tiles.size() + 8);
         a.ready = reinterpret_cast<int32_t*>(a.qslots);
         // (the tuner's choices were timed on tiles)
         a.sched = ((cfg.hints & 64) ? 1 : ((cfg.hints & 128) ? 2 : 0)) |
@@ -1346,7 +1354,7 @@ od_status Grid::msgdriven_launch(int64_t n, int steps) {
     // residual pair (kernel arguments: nothing on the host outlives this call)
     hipError_t e = launch_queue_init(st, a, tgt, reinterpret_cast<int32_t*>(cp(L.target)), res_ptr() + 2);
     if (e != hipSuccess) return fail(OD_EHIP, std::string("queue init: ") + hipGetErrorString(e));
-    e = boxes ? launch_deep_msg(s, st, deep_wgs, a, deep_map, reinterpret_cast<const DeepTile*>(cp(L.deep)))
+    e = boxes ? launch_deep_msg(s, deep_plan, st, deep_wgs, a, deep_map, reinterpret_cast<const DeepTile*>(cp(L.deep)))
         : pairs ? launch_msgdriven2(s, plan.tile[0], plan.tile[1], st, grid_wgs, a)
               : launch_msgdriven(s, plan.tile[0], plan.tile[1], st, grid_wgs, a);
     if (e != hipSuccess) return fail(OD_EHIP, std::string("msg-driven launch: ") + hipGetErrorString(e));

@@ -321,12 +321,16 @@ od_status od_pass_info(od_grid* g, int32_t* steps, int64_t* bytes, int32_t* boxe
     const Grid& G = g->g;
     *steps = G.deep() ? od::kDeepSteps : (G.two_step ? 2 : 1);
     *bytes = G.deep() ? 2 * (int64_t)G.s * G.plan.interior : G.bytes_per_pass();
-    *count = (int32_t)G.deep_h.size();
-    int ex, ey;
-    od::deep_shape(G.s, &ex, &ey);
+    const od::DeepPlan& d = G.deep_plan;
+    *count = G.deep() ? (int32_t)d.tiles.size() : 0;
+    int lx, ey;
+    od::deep_shape(G.s, d.rows, &lx, &ey);
+    const int32_t nv = (int32_t)d.vi.size(), ny = (int32_t)G.plan.n[1];
     for (int32_t i = 0; i < *count && i < cap; ++i) {
-        const od::DeepTile& t = G.deep_h[(size_t)i];
-        const int32_t v[10] = {t.xs, t.xs + ex, t.ys, t.ys + ey, t.xo0, t.xo1, t.yo0, t.yo1, t.z0, t.z1};
+        const od::DeepTile& t = d.tiles[(size_t)i];
+        auto x = [&](int32_t w) { return d.vx[(size_t)std::min(w, nv)]; };
+        const int32_t v[10] = {x(t.ws), x(t.ws + lx), t.ys, std::min(t.ys + ey, ny), x(t.wo0), x(t.wo1),
+                               t.yo0, t.yo1, t.z0, t.z1};
         std::copy(v, v + 10, boxes + 10 * (size_t)i);
     }
     return OD_OK;

@@ -61,21 +61,22 @@ struct Grid {
     // tiles' extra line descriptors
     bool two_step = false;
     std::vector<Tile2Dev> tiles2_h;
-    // four steps per pass (fused and graph forms, see deep_possible): tiles
-    // (none: pairs at most) and the device-side map
-    std::vector<DeepTile> deep_h;
+    // four steps per pass (see deep_possible): the boxes (none: pairs at most)
+    // and the device-side map
+    DeepPlan deep_plan;
     DeepMap deep_map{};
     bool user_tile = false;          // the caller fixed the tile shape
-    bool deep() const { return !deep_h.empty() && !tuning; }
+    bool deep() const { return !deep_plan.tiles.empty() && !tuning && !deep_off; }
     // cooperative forms: co-resident workgroups; message-driven: dependency
     // lists and which step counters hold the grid's step (0 = the tiles', 1 =
     // the boxes')
     int deep_wgs = 0;
     std::vector<int32_t> deep_ptr, deep_idx;
     int msg_counters = 0;
+    bool deep_off = false;           // the autotuner found the tiles quicker
     bool tuning = false;             // the autotuner times tiles: no four-step passes
     void drop_deep() {
-        deep_h.clear();
+        deep_plan.tiles.clear();
         L.total = L.total_pairs;
     }
     // passes of an iteration count: fours, pairs, singles
@@ -179,6 +180,7 @@ struct Grid {
     od_status fused_two(hipStream_t s2, int par, int64_t step);   // steps step, step + 1: parity par -> par ^ 1
     od_status fused_deep(hipStream_t s2, int par, int64_t step, bool last);   // kDeepSteps steps: parity par -> par ^ 1
     // k steps (steps_of); last: the residual is wanted
+    od_status fused_deep_pass(hipStream_t s2, int par, bool last = true);   // without imbalance re-runs
     od_status fused_pass(hipStream_t s2, int par, int64_t step, int k, bool last);
     od_status upload_tiles();                      // tile descriptors (and two-step lines) to the device
     int64_t bytes_per_pass() const;

@@ -129,12 +129,16 @@ od_status Grid::retile(const int32_t tile[3]) {
 }
 
 // Schedule state of a grid (persistent: schedule and waves cap;
-// message-driven: scheduler bits and waves cap) as cached.
+// message-driven: scheduler bits and waves cap; kNoDeep: the chosen tile is
+// quicker than four-step passes) as cached.
+constexpr int32_t kNoDeep = 16;
 static void apply_schedule(Grid& G, int32_t sched, int32_t waves) {
-    if (G.cfg.exec == OD_MSGDRIVEN)
+    if (G.cfg.exec == OD_MSGDRIVEN) {
         G.msg_sched = sched;
-    else
-        G.persist_sched = sched;
+    } else {
+        G.persist_sched = sched & (kNoDeep - 1);
+        G.deep_off = (sched & kNoDeep) != 0;
+    }
     G.persist_waves = waves;
 }
 
@@ -388,6 +392,31 @@ static od_status tune(Grid& G, int32_t iters, int32_t out_tile[3]) {
             if (st != OD_OK) break;
         }
         if (st != OD_OK) break;
+    }
+    // four-step passes against the best tile: thin grids can be quicker by tiles
+    // (fp64 (1,300,300) 10.4 against 13.7 us per iteration, (2000,2000,1) 28.7
+    // against 30.5)
+    if (st == OD_OK && !G.deep_plan.tiles.empty()) {
+        const int32_t n = (iters + 1) / 2;   // passes timed
+        float ms = 0;
+        if (pers) {
+            G.tuning = false;
+            st = G.persistent_run(kDeepSteps);
+            he = hipEventRecord(a, G.st);
+            if (st == OD_OK) st = G.persistent_run((int64_t)kDeepSteps * n);
+            G.tuning = true;
+        } else {
+            st = G.fused_deep_pass(G.st, G.parity);
+            he = hipEventRecord(a, G.st);
+            for (int32_t i = 0; i < n && st == OD_OK; ++i) st = G.fused_deep_pass(G.st, G.parity);
+        }
+        if (he == hipSuccess) he = hipEventRecord(b, G.st);
+        if (he == hipSuccess) he = hipEventSynchronize(b);
+        if (he == hipSuccess) he = hipEventElapsedTime(&ms, a, b);
+        if (st == OD_OK && he == hipSuccess && pers) st = G.device_error();
+        if (st == OD_OK && he != hipSuccess) st = fail(OD_EHIP, std::string("tuning launch: ") + hipGetErrorString(he));
+        // (per iteration: best_ms is `iters` iterations, a persistent one twice that)
+        if (ms / (float)(kDeepSteps * n) > best_ms / (float)(pers ? 2 * iters : iters)) best[3] |= kNoDeep;
     }
     hipEventDestroy(a);
     hipEventDestroy(b);

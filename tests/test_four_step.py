@@ -15,15 +15,16 @@ BC6 = (1.0, 0.5, 0.25, 0.125, 2.0, 3.0)
 RING = 4
 
 
-@pytest.mark.parametrize("dtype,vx", [("f64", 2), ("f32", 4)])
-@pytest.mark.parametrize("n", [(64, 64, 1), (64, 65, 2), (68, 64, 9), (120, 120, 3), (124, 121, 4), (176, 177, 5),
-                               (180, 119, 16), (300, 500, 7), (512, 512, 40), (1000, 66, 1)])
-def test_boxes_write_each_cell_once_and_keep_their_ring(dtype, vx, n):
-    p = od.host_plan(n=n, odf=1, dtype=dtype, exec="graph")["pass"]
-    assert p["steps"] == 4 and p["bytes"] == 2 * (16 // vx) * n[0] * n[1] * n[2]
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("n,odf", [((1, 1, 1), 1), ((2, 3, 4), 8), ((9, 8, 7), 27), ((63, 15, 5), 1), ((64, 16, 1), 1),
+                                   ((65, 17, 3), 1), ((64, 65, 2), 1), ((120, 120, 3), 1), ((124, 121, 4), 1),
+                                   ((176, 177, 5), 1), ((180, 119, 16), 27), ((211, 163, 57), 27), ((300, 500, 7), 8),
+                                   ((512, 512, 40), 64), ((1000, 66, 1), 1), ((130, 40, 6), 125)])
+def test_boxes_write_each_cell_once_and_keep_their_ring(dtype, n, odf):
+    p = od.host_plan(n=n, odf=odf, dtype=dtype, exec="graph")["pass"]
+    assert p["steps"] == 4 and p["bytes"] == (8 if dtype == "f32" else 16) * n[0] * n[1] * n[2]
     seen = np.zeros((n[2], n[1], n[0]), dtype=np.int8)
     for cx0, cx1, cy0, cy1, x0, x1, y0, y1, z0, z1 in p["boxes"]:
-        assert cx0 % vx == 0 and x0 % vx == 0 and x1 % vx == 0
         # the lanes stay in the grid, and no written cell is within the ring's
         # reach of the cells computed from nothing
         assert 0 <= cx0 <= x0 < x1 <= cx1 <= n[0] and 0 <= cy0 <= y0 < y1 <= cy1 <= n[1] and 0 <= z0 < z1 <= n[2]
@@ -36,21 +37,21 @@ def test_boxes_write_each_cell_once_and_keep_their_ring(dtype, vx, n):
 
 
 @pytest.mark.parametrize("kw,steps", [
-    (dict(n=(64, 64, 8)), 4), (dict(n=(62, 64, 8)), 2), (dict(n=(64, 63, 8)), 2),
-    (dict(n=(65, 64, 8)), 2),                                  # rows end inside a vector
-    (dict(n=(66, 64, 8), dtype="f32"), 2),
-    (dict(n=(66, 64, 64), odf=8), 2),                          # chares start inside a vector
-    (dict(n=(64, 67, 64), odf=8), 4),                          # along y they may start anywhere
-    (dict(n=64, odf=8, exec="persistent"), 4), (dict(n=64, odf=8, exec="msgdriven"), 4),
-    (dict(n=64, odf=8, exec="persistent", hints=1 << 4), 2),   # a schedule of tiles
-    (dict(n=64, odf=8, exec="persistent", hints=1 << 3), 1),   # the timeline is one of single steps
-    (dict(n=64, odf=8, exec="persistent", imbalance_pct=10, imbalance_max_extra=4), 2),
-    (dict(n=64, odf=8, hints=1 << 14), 2), (dict(n=64, odf=8, hints=1 << 12), 1),
-    (dict(n=64, odf=8, tile=(32, 16, 16)), 2),                 # the caller's tile shape is what runs
-    (dict(n=64, odf=8, exec="fused", imbalance_pct=10, imbalance_max_extra=4), 4),
+    (dict(n=64), 4), (dict(n=(5, 3, 2), odf=1), 4), (dict(n=(65, 64, 8)), 4), (dict(n=(66, 64, 64), dtype="f32"), 4),
+    (dict(n=64, exec="fused"), 4), (dict(n=64, exec="persistent"), 4), (dict(n=64, exec="msgdriven"), 4),
+    (dict(n=64, exec="per_chare"), 1),
+    (dict(n=64, exec="persistent", hints=1 << 4), 2),          # a schedule of tiles
+    (dict(n=64, exec="persistent", hints=1 << 3), 1),          # the timeline is one of single steps
+    (dict(n=64, exec="persistent", imbalance_pct=10, imbalance_max_extra=4), 2),
+    (dict(n=64, exec="fused", imbalance_pct=10, imbalance_max_extra=4), 4),
+    (dict(n=64, hints=1 << 14), 2), (dict(n=64, hints=1 << 12), 1),
+    (dict(n=64, tile=(32, 16, 16)), 2),                        # the caller's tile shape is what runs
+    (dict(n=(64, 1, 64), stencil=5), 2),                       # the 2D stencil
 ])
 def test_which_grids_run_four_steps(kw, steps):
-    kw = dict(dict(odf=1, dtype="f64", exec="graph"), **kw)
+    kw = dict(dict(odf=8, dtype="f64", exec="graph"), **kw)
+    if kw.get("stencil") == 5:
+        kw["odf"] = 1
     assert od.host_plan(**kw)["pass"]["steps"] == steps
 
 
@@ -80,7 +81,13 @@ def _run(n, odf, dtype, iters, exec_="fused", seed=5, write=None, want_steps=4, 
 @pytest.mark.parametrize("dtype", ["f64", "f32"])
 @pytest.mark.parametrize("n,odf", [((64, 64, 1), 1), ((64, 64, 9), 1), ((68, 65, 3), 1), ((120, 121, 4), 1),
                                    ((124, 120, 5), 1), ((176, 70, 12), 1), ((180, 64, 20), 1), ((128, 72, 64), 64),
-                                   ((64, 67, 30), 8), ((192, 130, 33), 27), ((256, 64, 48), 512)])
+                                   ((64, 67, 30), 8), ((192, 130, 33), 27), ((256, 64, 48), 512),
+                                   # vectors cut short by chares and by the grid; grids of one
+                                   # strip, of fewer rows or vectors than lanes, of one cell
+                                   ((211, 163, 37), 27), ((65, 70, 9), 1), ((67, 64, 9), 8), ((66, 130, 20), 8),
+                                   ((1, 1, 1), 1), ((2, 1, 3), 1), ((9, 8, 7), 27), ((3, 40, 5), 1), ((40, 3, 33), 8),
+                                   ((63, 15, 12), 1), ((64, 16, 12), 8), ((65, 17, 12), 8), ((130, 33, 5), 125),
+                                   ((100, 100, 100), 512)])
 def test_edges_of_boxes_and_chares(dtype, n, odf):
     want, _, r = oracle.solve(n, DT[dtype], seed=5, iters=8, bc=BC6)
     U, got = _run(n, odf, dtype, [8])
