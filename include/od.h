@@ -161,10 +161,12 @@ typedef struct {
      * Bit 14 (OD_FUSED, OD_GRAPH, OD_PERSISTENT, OD_MSGDRIVEN): pairs at
      * most.  By default grids that run pairs, with no tile shape fixed by the
      * caller (and in the cooperative forms without imbalance, OD_PERSISTENT
-     * without a schedule forced by bits 4, 5, 11 or 13), run groups of four iterations as one pass over boxes of the whole
-     * grid (od_pass_info; od_autotune may find a thin grid's tiles quicker and
-     * keep them); the values are again the same,
-     * and what is left over of a count runs as pairs and a single sweep.
+     * without a schedule forced by bits 4, 5, 11 or 13), run groups of four
+     * iterations as one pass over boxes of the whole grid (od_pass_info;
+     * od_autotune may find a thin grid's tiles quicker and keep them); the
+     * values are again the same, and what is left over of a count runs as
+     * pairs and a single sweep.  Grids of the 2D stencil run groups of eight
+     * (OD_FUSED, OD_GRAPH).
      * Bit 8 is reserved.  Other bits are ignored. */
     int32_t hints;
     /* 7 (or 0): 3D 7-point stencil.  5: the 2D 5-point stencil of the
@@ -334,9 +336,9 @@ typedef struct {
 od_status od_plan(struct od_grid* g, od_plan_info* info);
 
 /* The longest pass the grid runs: *steps iterations in one pass over the
- * field (4, 2 or 1; hints bits 12 and 14), *bytes its algorithmic HBM bytes
- * (bytes_per_pass, or with four steps one read and one write of the field).
- * Four-step passes cut the whole grid, not each chare, into *count boxes
+ * field (8, 4, 2 or 1; hints bits 12 and 14), *bytes its algorithmic HBM bytes
+ * (bytes_per_pass, or with four or eight steps one read and one write of the
+ * field).  Those passes cut the whole grid, not each chare, into *count boxes
  * (0: none): up to cap of them are written to boxes, 10 values each: the
  * cells [x0, x1), [y0, y1) a workgroup computes, the cells [x0, x1),
  * [y0, y1), [z0, z1) it writes (global interior coordinates). */

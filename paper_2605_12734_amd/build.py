@@ -10,7 +10,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libod.so")
-SOURCES = ["kernels.hip", "deep.hip", "plan.cpp", "od_api.cpp", "od_capi.cpp", "tune.cpp", "server.cpp", "launch_bench.hip"]
+SOURCES = ["kernels.hip", "deep.hip", "deep2d.hip", "plan.cpp", "od_api.cpp", "od_capi.cpp", "tune.cpp", "server.cpp", "launch_bench.hip"]
 
 # Bit-exactness: no contraction into FMA, correctly rounded fp32 division,
 # subnormals kept.  Packed-fp32 instructions are disabled for the device.

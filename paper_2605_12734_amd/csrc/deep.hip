@@ -99,6 +99,23 @@ void deep_shape(int dtype_bytes, int rows, int* lx, int* ey) {
     *ey = deep_waves(dtype_bytes) * 64 / *lx * rows;
 }
 
+std::vector<DeepTile> xcd_runs(const std::vector<DeepTile>& list) {
+    std::vector<DeepTile> out;
+    const size_t N = list.size();
+    out.reserve(N);
+    std::vector<size_t> at(kNumXcd), end(kNumXcd);
+    for (size_t g = 0, o = 0; g < (size_t)kNumXcd; ++g) {
+        const size_t cnt = N / kNumXcd + (g < N % kNumXcd ? 1 : 0);
+        at[g] = o;
+        end[g] = o += cnt;
+    }
+    for (size_t i = 0; out.size() < N; ++i) {
+        const size_t g = i % kNumXcd;
+        if (at[g] < end[g]) out.push_back(list[at[g]++]);
+    }
+    return out;
+}
+
 DeepPlan deep_plan(const Plan& p, int dtype_bytes) {
     DeepPlan out;
     const int32_t VX = 16 / dtype_bytes;
@@ -155,19 +172,7 @@ DeepPlan deep_plan(const Plan& p, int dtype_bytes) {
             for (const Cut& a : cx)
                 list.push_back({a.start, b.start, a.o0, a.o1, b.o0, b.o1, (int32_t)(p.n[2] * k / zc),
                                 (int32_t)(p.n[2] * (k + 1) / zc)});
-    // workgroup w runs on XCD w % 8: give each XCD a contiguous run
-    const size_t N = list.size();
-    d.tiles.reserve(N);
-    std::vector<size_t> at(kNumXcd), end(kNumXcd);
-    for (size_t g = 0, o = 0; g < (size_t)kNumXcd; ++g) {
-        const size_t cnt = N / kNumXcd + (g < N % kNumXcd ? 1 : 0);
-        at[g] = o;
-        end[g] = o += cnt;
-    }
-    for (size_t i = 0; d.tiles.size() < N; ++i) {
-        const size_t g = i % kNumXcd;
-        if (at[g] < end[g]) d.tiles.push_back(list[at[g]++]);
-    }
+    d.tiles = xcd_runs(list);
     return d;
 }
 

@@ -10,7 +10,7 @@
 
 namespace od {
 
-constexpr int kDeepSteps = 4;
+constexpr int kDeepSteps = 4, kDeep2dSteps = 8;
 
 // One workgroup's work: the lanes cover the vectors [ws, ws + LX) along x (see
 // DeepPlan::vx) and the rows [ys, ys + EY), march z and write the vectors
@@ -66,6 +66,15 @@ hipError_t launch_deep_persistent(int dtype_bytes, const DeepPlan& d, hipStream_
 // The message-driven scheduler over boxes: a scheduler step is one pass.
 hipError_t launch_deep_msg(int dtype_bytes, const DeepPlan& d, hipStream_t st, int grid, const MsgArgs& a,
                            const DeepMap& g, const DeepTile* tiles);
+// Eight steps of the 2D 5-point stencil (deep2d.hip); `rows` is 0, and vectors
+// are 32 bytes.
+DeepPlan deep_plan2d(const Plan& p, int dtype_bytes);
+hipError_t launch_deep2d(int dtype_bytes, const DeepPlan& d, hipStream_t st, const DeepMap& g, const DeepTile* tiles,
+                         int parity, unsigned long long* res, int32_t zero_lo, int32_t zero_hi, int hints,
+                         bool want_res);
+// Boxes in launch order: workgroup w runs on XCD w % 8, each XCD a contiguous run.
+std::vector<DeepTile> xcd_runs(const std::vector<DeepTile>& list);
+
 // Workgroups of either cooperative form that are co-resident on the device.
 int deep_max_grid(int dtype_bytes, const DeepPlan& d);
 hipError_t launch_fill_i32(hipStream_t st, int32_t* p, int32_t n, int32_t v);

@@ -200,7 +200,8 @@ bool two_step_room(const Grid& G) {
 
 // Four steps per pass: the batched forms where they can pair steps (the
 // persistent form with no schedule forced by hints and no timeline), the 3D
-// stencil, unless hints bit 14 or a tile shape fixed by the caller
+// stencil (eight steps of the 2D one, fused and graph forms without imbalance),
+// unless hints bit 14 or a tile shape fixed by the caller
 // (whose passes then run that shape).  Under load imbalance the heavy chares'
 // re-runs of the four steps are a launch of their own before the pass (fused
 // form; the cooperative forms keep pairs there).
@@ -210,7 +211,8 @@ bool deep_possible(const Grid& G) {
                       (cfg.exec == OD_PERSISTENT && G.imb.heavy == 0 &&
                        !(cfg.hints & (kHintTimeline | 16 | 32 | 2048 | 8192))) ||
                       (cfg.exec == OD_MSGDRIVEN && G.imb.heavy == 0);
-    return form && cfg.stencil != 5 && !G.plan.multires && !(cfg.hints & (4096 | 16384)) && !G.user_tile;
+    if (cfg.stencil == 5 && ((cfg.exec != OD_FUSED && cfg.exec != OD_GRAPH) || G.imb.heavy != 0)) return false;
+    return form && !G.plan.multires && !(cfg.hints & (4096 | 16384)) && !G.user_tile;
 }
 
 // Block and local coordinates of global cell (x, y, z) as a FaceDev: its
@@ -667,7 +669,7 @@ std::string build_layout(const od_config& cfg, Grid& G) {
     // four-step passes, behind everything else (a workspace that ends here
     // runs pairs): boxes, and per axis the tables of DeepMap
     G.deep_plan = DeepPlan{};
-    if (deep_possible(G) && G.L.field_end / 16 <= UINT32_MAX) G.deep_plan = od::deep_plan(p, s);
+    if (deep_possible(G) && G.L.field_end / 16 <= UINT32_MAX) G.deep_plan = cfg.stencil == 5 ? deep_plan2d(p, s) : od::deep_plan(p, s);
     if (!G.deep_plan.tiles.empty()) {
         G.L.deep = cv.take(G.deep_plan.tiles.size() * sizeof(DeepTile));
         G.L.deep_tab = cv.take((G.deep_plan.vx.size() + G.deep_plan.vi.size() + (size_t)(p.n[1] + 2 * p.n[2])) * 4);
@@ -1127,13 +1129,13 @@ od_status Grid::fused_deep(hipStream_t s2, int par, int64_t step, bool last) {
 }
 
 od_status Grid::fused_deep_pass(hipStream_t s2, int par, bool last) {
-    hipError_t e = launch_deep(s, deep_plan, s2, deep_map, reinterpret_cast<const DeepTile*>(cp(L.deep)), par, res_ptr(), 0, 1, mode(), last);
+    hipError_t e = (cfg.stencil == 5 ? launch_deep2d : launch_deep)(s, deep_plan, s2, deep_map, reinterpret_cast<const DeepTile*>(cp(L.deep)), par, res_ptr(), 0, 1, mode(), last);
     if (e != hipSuccess) return fail(OD_EHIP, std::string("four-step sweep launch: ") + hipGetErrorString(e));
     return OD_OK;
 }
 
 od_status Grid::fused_pass(hipStream_t s2, int par, int64_t step, int k, bool last) {
-    return k == kDeepSteps ? fused_deep(s2, par, step, last) : (k == 2 ? fused_two(s2, par, step) : fused_one(s2, par, step));
+    return k > 2 ? fused_deep(s2, par, step, last) : (k == 2 ? fused_two(s2, par, step) : fused_one(s2, par, step));
 }
 
 od_status Grid::upload_tiles() {

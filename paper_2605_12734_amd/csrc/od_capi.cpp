@@ -319,16 +319,16 @@ od_status od_plan(od_grid* g, od_plan_info* info) {
 od_status od_pass_info(od_grid* g, int32_t* steps, int64_t* bytes, int32_t* boxes, int32_t cap, int32_t* count) {
     if (!g || !steps || !bytes || !count || cap < 0 || (cap > 0 && !boxes)) return fail(OD_EINVAL, "NULL argument");
     const Grid& G = g->g;
-    *steps = G.deep() ? od::kDeepSteps : (G.two_step ? 2 : 1);
+    *steps = G.deep() ? G.deep_steps() : (G.two_step ? 2 : 1);
     *bytes = G.deep() ? 2 * (int64_t)G.s * G.plan.interior : G.bytes_per_pass();
     const od::DeepPlan& d = G.deep_plan;
     *count = G.deep() ? (int32_t)d.tiles.size() : 0;
-    int lx, ey;
-    od::deep_shape(G.s, d.rows, &lx, &ey);
+    int lx = 64, ey = 1;   // the 2D stencil's waves
+    if (d.rows > 0) od::deep_shape(G.s, d.rows, &lx, &ey);
     const int32_t nv = (int32_t)d.vi.size(), ny = (int32_t)G.plan.n[1];
     for (int32_t i = 0; i < *count && i < cap; ++i) {
         const od::DeepTile& t = d.tiles[(size_t)i];
-        auto x = [&](int32_t w) { return d.vx[(size_t)std::min(w, nv)]; };
+        auto x = [&](int32_t w) { return d.vx[(size_t)std::max(0, std::min(w, nv))]; };
         const int32_t v[10] = {x(t.ws), x(t.ws + lx), t.ys, std::min(t.ys + ey, ny), x(t.wo0), x(t.wo1),
                                t.yo0, t.yo1, t.z0, t.z1};
         std::copy(v, v + 10, boxes + 10 * (size_t)i);

@@ -79,8 +79,9 @@ struct Grid {
         deep_plan.tiles.clear();
         L.total = L.total_pairs;
     }
-    // passes of an iteration count: fours, pairs, singles
-    int steps_of(int64_t left) const { return deep() && left >= kDeepSteps ? kDeepSteps : (two_step && left >= 2 ? 2 : 1); }
+    // passes of an iteration count: fours (eights of the 2D stencil), pairs, singles
+    int deep_steps() const { return cfg.stencil == 5 ? kDeep2dSteps : kDeepSteps; }
+    int steps_of(int64_t left) const { return deep() && left >= deep_steps() ? deep_steps() : (two_step && left >= 2 ? 2 : 1); }
     int64_t halo2_cells = 0;         // cells of other chares within two steps of each chare
     std::vector<int32_t> dep_ptr, dep_idx;
     ImbDev imb{};                    // load-imbalance draw (heavy == 0: none)

@@ -401,9 +401,9 @@ static od_status tune(Grid& G, int32_t iters, int32_t out_tile[3]) {
         float ms = 0;
         if (pers) {
             G.tuning = false;
-            st = G.persistent_run(kDeepSteps);
+            st = G.persistent_run(G.deep_steps());
             he = hipEventRecord(a, G.st);
-            if (st == OD_OK) st = G.persistent_run((int64_t)kDeepSteps * n);
+            if (st == OD_OK) st = G.persistent_run((int64_t)G.deep_steps() * n);
             G.tuning = true;
         } else {
             st = G.fused_deep_pass(G.st, G.parity);
@@ -416,7 +416,7 @@ static od_status tune(Grid& G, int32_t iters, int32_t out_tile[3]) {
         if (st == OD_OK && he == hipSuccess && pers) st = G.device_error();
         if (st == OD_OK && he != hipSuccess) st = fail(OD_EHIP, std::string("tuning launch: ") + hipGetErrorString(he));
         // (per iteration: best_ms is `iters` iterations, a persistent one twice that)
-        if (ms / (float)(kDeepSteps * n) > best_ms / (float)(pers ? 2 * iters : iters)) best[3] |= kNoDeep;
+        if (ms / (float)(G.deep_steps() * n) > best_ms / (float)(pers ? 2 * iters : iters)) best[3] |= kNoDeep;
     }
     hipEventDestroy(a);
     hipEventDestroy(b);

@@ -46,7 +46,8 @@ def test_boxes_write_each_cell_once_and_keep_their_ring(dtype, n, odf):
     (dict(n=64, exec="fused", imbalance_pct=10, imbalance_max_extra=4), 4),
     (dict(n=64, hints=1 << 14), 2), (dict(n=64, hints=1 << 12), 1),
     (dict(n=64, tile=(32, 16, 16)), 2),                        # the caller's tile shape is what runs
-    (dict(n=(64, 1, 64), stencil=5), 2),                       # the 2D stencil
+    (dict(n=(64, 1, 64), stencil=5), 8),                       # the 2D stencil
+    (dict(n=(64, 1, 64), stencil=5, exec="persistent"), 1),
 ])
 def test_which_grids_run_four_steps(kw, steps):
     kw = dict(dict(odf=8, dtype="f64", exec="graph"), **kw)
@@ -210,3 +211,39 @@ def test_a_workspace_of_the_pairs_size_runs_pairs():
     finally:
         od.check(od.lib().od_destroy(h), "od_destroy")
     assert B.OD_F64 == 8
+
+
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("n,odf", [((1, 1), 1), ((5, 9), 1), ((252, 3), 1), ((253, 20), 1), ((256, 16), 4), ((257, 17), 9),
+                                   ((512, 64), 16), ((1000, 700), 9), ((2048, 10), 64)])
+def test_boxes_of_the_2d_stencil(dtype, n, odf):
+    p = od.host_plan(n=(n[0], 1, n[1]), odf=odf, dtype=dtype, exec="graph", stencil=5)["pass"]
+    assert p["steps"] == 8
+    seen = np.zeros((n[1], n[0]), dtype=np.int8)
+    for cx0, cx1, _, _, x0, x1, _, _, z0, z1 in p["boxes"]:
+        assert 0 <= cx0 <= x0 < x1 <= cx1 <= n[0] and 0 <= z0 < z1 <= n[1]
+        assert cx0 == 0 or x0 - cx0 >= 8
+        assert cx1 == n[0] or cx1 - x1 >= 8
+        seen[z0:z1, x0:x1] += 1
+    assert (seen == 1).all()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("exec_", ["fused", "graph"])
+@pytest.mark.parametrize("n,odf,iters", [((1, 1), 1, [8]), ((5, 9), 1, [16]), ((252, 30), 1, [8, 3]), ((253, 20), 1, [8]),
+                                         ((256, 16), 4, [19]), ((257, 170), 9, [16]), ((512, 64), 16, [8, 8]),
+                                         ((1000, 700), 9, [24]), ((500, 40), 1, [13])])
+def test_2d_stencil(dtype, exec_, n, odf, iters):
+    bc = (1.0, 0.5, 2.0, 3.0)
+    want, _, r = oracle.solve2d(n, DT[dtype], 5, sum(iters), bc)
+    g = od.Grid2D(n, odf=odf, dtype=dtype, exec=exec_, bc=bc, seed=5, hints=1)
+    try:
+        assert g.pass_info()["steps"] == 8
+        for k in iters:
+            g.iterate(k)
+        U, got = g.read(), g.residual()
+    finally:
+        g.close()
+    _same(U, want)
+    assert got == r
