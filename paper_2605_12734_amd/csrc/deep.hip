@@ -48,6 +48,15 @@ k_deep(DeepMap g, const DeepTile* __restrict__ tiles, int parity, unsigned long 
 // levels), LDS at one.
 int per_cu(int dtype_bytes, int rows) { return (dtype_bytes == 8 ? 1 : 2) * (rows == 1 ? 2 : 1); }
 
+// Planes of a served solve's box at least: fewer make a solve alone quicker and
+// leave less of a shared chip to the others, each box computing eight more.  ms
+// for 600 iterations checked every 10, without a least / 8 / 12 / 16 planes: 16
+// solves of 32-48 cells an edge 42 / 11.7 / 12.0 / 13.8, of 32-256 120 / 80 / 75 / 70;
+// fp64 64^3 alone 7.2 / 10.7 / 13.4 / 14.6, 128^3 10.4 / 10.9 / 12.4 / 14.5.  At 12 a
+// solve of one-step tasks that is checked at every iteration was quicker (64^3 20.7
+// against 23.2), at 8 none is.
+constexpr int64_t kServePlanes = 8;
+
 struct Cut {
     int32_t start, o0, o1;
 };
@@ -94,9 +103,9 @@ std::vector<Cut> cut_axis(int32_t n, int32_t L, Cells cells) {
 
 }  // namespace
 
-void deep_shape(int dtype_bytes, int rows, int* lx, int* ey) {
+void deep_shape(int dtype_bytes, const DeepPlan& d, int* lx, int* ey) {
     *lx = kEX * dtype_bytes / 16;
-    *ey = deep_waves(dtype_bytes) * 64 / *lx * rows;
+    *ey = d.waves * 64 / *lx * d.rows;
 }
 
 std::vector<DeepTile> xcd_runs(const std::vector<DeepTile>& list) {
@@ -116,7 +125,9 @@ std::vector<DeepTile> xcd_runs(const std::vector<DeepTile>& list) {
     return out;
 }
 
-DeepPlan deep_plan(const Plan& p, int dtype_bytes) {
+namespace {
+
+DeepPlan plan_boxes(const Plan& p, int dtype_bytes, bool serve) {
     DeepPlan out;
     const int32_t VX = 16 / dtype_bytes;
     if (p.multires || p.chares.empty()) return out;
@@ -143,18 +154,25 @@ DeepPlan deep_plan(const Plan& p, int dtype_bytes) {
     d.vx.push_back((int32_t)p.n[0]);
     std::vector<Cut> cx, cy;
     int64_t best = INT64_MAX, zc = 1;
-    for (int rows : {4, 1}) {
+    d.waves = serve ? kServeWaves : deep_waves(dtype_bytes);
+    for (int rows : {serve && dtype_bytes == 4 ? 2 : 4, 1}) {
+        if (serve && best != INT64_MAX) continue;   // solves share the chip: the boxes of least work
         int lx, ey;
-        deep_shape(dtype_bytes, rows, &lx, &ey);
+        DeepPlan shape;
+        shape.rows = rows;
+        shape.waves = d.waves;
+        deep_shape(dtype_bytes, shape, &lx, &ey);
         if (rows > 1 && p.n[1] < ey) continue;   // the last row ends a strip
         const std::vector<Cut> ax = cut_axis(nv, lx, [&](int32_t i) { return d.vx[(size_t)i]; }),
                                ay = cut_axis((int32_t)p.n[1], ey, [](int32_t i) { return i; });
         if (ax.empty() || ay.empty()) continue;
         // z: as many pieces as fill the chip's 256 CUs in the fewest plane
         // iterations, a piece of l planes taking l + 8
-        const int64_t xy = (int64_t)ax.size() * (int64_t)ay.size(), slots = 256 * per_cu(dtype_bytes, rows);
-        for (int64_t k = 1; k <= p.n[2]; ++k) {
+        const int64_t xy = (int64_t)ax.size() * (int64_t)ay.size(),
+                      slots = 256 * (serve ? 1 : per_cu(dtype_bytes, rows));
+        for (int64_t k = 1; k <= p.n[2] && (!serve || xy * k <= kServeBoxes); ++k) {
             const int64_t len = (p.n[2] + k - 1) / k;
+            if (serve && k > 1 && len < kServePlanes) break;
             const int64_t cost = ((xy * k + slots - 1) / slots) * (len + 2 * kDeepSteps) * plane_cost(dtype_bytes, rows);
             if (cost < best) {
                 best = cost;
@@ -165,7 +183,7 @@ DeepPlan deep_plan(const Plan& p, int dtype_bytes) {
             }
         }
     }
-    if (d.rows == 0) return out;
+    if (best == INT64_MAX) return out;
     std::vector<DeepTile> list;
     for (int64_t k = 0; k < zc; ++k)
         for (const Cut& b : cy)
@@ -176,10 +194,37 @@ DeepPlan deep_plan(const Plan& p, int dtype_bytes) {
     return d;
 }
 
+}  // namespace
+
+DeepPlan deep_plan(const Plan& p, int dtype_bytes) { return plan_boxes(p, dtype_bytes, false); }
+DeepPlan deep_plan_serve(const Plan& p, int dtype_bytes) { return plan_boxes(p, dtype_bytes, true); }
+
+std::vector<int32_t> deep_tables(const Plan& p, const DeepPlan& d, size_t at[5]) {
+    std::vector<int32_t> tab(d.vx);
+    at[0] = 0;
+    at[1] = tab.size();
+    tab.insert(tab.end(), d.vi.begin(), d.vi.end());
+    for (int q = 1; q < 3; ++q) {
+        at[q + 1] = tab.size();
+        for (int64_t v = 0, i = 0; v < p.n[q]; ++v) {
+            if (p.regular)
+                while (v >= p.split[q][(size_t)i + 1]) ++i;
+            tab.push_back((int32_t)(p.regular ? i : v / p.gran));
+        }
+    }
+    at[4] = tab.size();
+    for (int64_t v = 0; v < p.n[2]; ++v) {
+        int64_t q = v + 1;
+        while (q < p.n[2] && tab[at[3] + (size_t)q] == tab[at[3] + (size_t)v]) ++q;
+        tab.push_back((int32_t)q);
+    }
+    return tab;
+}
+
 void deep_deps(const DeepPlan& d, int dtype_bytes, std::vector<int32_t>& ptr, std::vector<int32_t>& idx) {
     const std::vector<DeepTile>& t = d.tiles;
     int ex, ey;
-    deep_shape(dtype_bytes, d.rows, &ex, &ey);
+    deep_shape(dtype_bytes, d, &ex, &ey);
     auto reads = [&](const DeepTile& a, const DeepTile& b) {
         return b.wo0 < a.ws + ex && a.ws < b.wo1 && b.yo0 < a.ys + ey && a.ys < b.yo1 && b.z0 < a.z1 + kDeepSteps &&
                a.z0 - kDeepSteps < b.z1;

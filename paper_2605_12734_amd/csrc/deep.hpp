@@ -41,15 +41,43 @@ struct DeepMap {
 };
 
 struct DeepPlan {
-    int rows = 0;                      // rows of a lane's strip: 4, or 1 for small grids
+    int rows = 0;                      // rows of a lane's strip: 4 (serving fp32: 2), 1 for small grids, 0 in 2D
+    int waves = 0;                     // of a workgroup
     bool ragged = false;               // some vectors are not full
     std::vector<DeepTile> tiles;       // in launch order; empty: the grid has no four-step passes
     std::vector<int32_t> vx, vi;       // as in DeepMap
 };
 
 // Lane coverage: LX vectors of 16 bytes by EY rows.
-void deep_shape(int dtype_bytes, int rows, int* lx, int* ey);
+void deep_shape(int dtype_bytes, const DeepPlan& d, int* lx, int* ey);
 DeepPlan deep_plan(const Plan& p, int dtype_bytes);
+// The boxes of a served solve: workgroups of kServeWaves waves in either type,
+// at most kServeBoxes of them (a slot's dependency lists hold 26 for each).
+constexpr int kServeWaves = 8, kServeBoxes = 2048;
+DeepPlan deep_plan_serve(const Plan& p, int dtype_bytes);
+// vx, vi, iy, iz and zn of DeepMap one after another; `at`: where each begins.
+std::vector<int32_t> deep_tables(const Plan& p, const DeepPlan& d, size_t at[5]);
+
+// What a served solve's tasks read, in its slot of the control region:
+// positions are bytes from the server's arena.
+struct ServeSolve {
+    int64_t arena, blocks, corigin, dir_pb, tiles, tab[5];
+    int32_t k[2], nv, ny, nz;
+    int32_t rows, ragged;
+    int32_t check_every, max_iters, passes;   // steps between checks, at most; passes between checks
+};
+static_assert(sizeof(ServeSolve) == 120, "ServeSolve layout");
+// Passes of a solve: every interval between checks (the last one ends at the
+// cap) takes the fewest, its first one the steps that fours leave over.
+inline int32_t serve_passes(int32_t steps) { return steps > 0 ? 1 + (steps - 1) / kDeepSteps : 0; }
+inline int32_t serve_target(int32_t check_every, int32_t max_iters) {
+    return check_every > 0 ? max_iters / check_every * serve_passes(check_every) + serve_passes(max_iters % check_every)
+                           : serve_passes(max_iters);
+}
+// Iterations done after a decision pass.
+inline int32_t serve_iters(int32_t check_every, int32_t max_iters, int32_t pass) {
+    return pass >= serve_target(check_every, max_iters) ? max_iters : pass / serve_passes(check_every) * check_every;
+}
 
 // One pass: reads parity `parity`, writes the field four steps later into
 // parity ^ 1; res zeroing as launch_sweep, and with want_res the residual of

@@ -164,11 +164,12 @@ __device__ __forceinline__ int32_t deep_owner(const DeepMap& m, int ix, int iy, 
     return m.owner ? m.owner[e] : e;
 }
 
-template <typename T, int R>
+// R rows a strip, W waves a workgroup.
+template <typename T, int R, int W = deep_waves((int)sizeof(T))>
 struct Deep {
     using V = typename DV<T>::t;
     static constexpr int VX = DV<T>::N;
-    static constexpr int NW = deep_waves((int)sizeof(T)), NT = NW * 64;
+    static constexpr int NW = W, NT = NW * 64;
     static constexpr int EX = kEX, LX = EX / VX;
     static constexpr int NS = NT / LX;            // strips of R rows
     static constexpr int EY = NS * R;
@@ -186,10 +187,13 @@ struct Deep {
 // R: rows of a lane's strip.  XF: the tile touches the grid's x- face (bit 0),
 // its x+ face (bit 1).  RAG: some vectors are not full (a chare's row, or the
 // grid's, ends inside them): the cells beside their end come from the lane after.
-template <typename T, int R, int XF, bool RAG>
+// ST: steps of the pass (one of four at most).  skip (uniform): that many fewer;
+// the first levels copy, so that the last step is still the last level's.
+template <typename T, int R, int XF, bool RAG, int W, int ST = kDeepSteps>
 __device__ __forceinline__ T deep_tile(const DeepMap& g, const DeepTile& t, const int parity,
-                                       typename Deep<T, R>::Lds& L, const int hints, const bool want_res) {
-    using D = Deep<T, R>;
+                                       typename Deep<T, R, W>::Lds& L, const int hints, const bool want_res,
+                                       const int skip) {
+    using D = Deep<T, R, W>;
     using V = typename D::V;
     constexpr int VX = D::VX, EX = D::EX, EY = D::EY;
     const int tid = threadIdx.x, lx = tid & (D::LX - 1), strip = tid / D::LX;
@@ -282,7 +286,7 @@ __device__ __forceinline__ T deep_tile(const DeepMap& g, const DeepTile& t, cons
     const bool x_first = w == 0, x_last = w == nv_all - 1, y_first = ym_face && strip == 0, y_last = y + R == ny;
     const unsigned long long m_first = __ballot(x_first), m_last = __ballot(x_last);
 
-    const int jlo = max(z0 - kDeepSteps, -1), jhi = z1 - 1 + kDeepSteps;
+    const int jlo = max(z0 - ST, -1), jhi = z1 - 1 + ST;
     const int lmax = min(jhi, nz);
     int lq = jlo, lnext = next_of(jlo), dnext = next_of(z0);
 #pragma unroll
@@ -310,9 +314,9 @@ __device__ __forceinline__ T deep_tile(const DeepMap& g, const DeepTile& t, cons
     };
     load();
 
-    V U[kDeepSteps][R], S[kDeepSteps][R];
+    V U[ST][R], S[ST][R];
 #pragma unroll
-    for (int s = 0; s < kDeepSteps; ++s)
+    for (int s = 0; s < ST; ++s)
 #pragma unroll
         for (int r = 0; r < R; ++r) U[s][r] = S[s][r] = (V)(T)1;
     T res = 0;
@@ -323,7 +327,7 @@ __device__ __forceinline__ T deep_tile(const DeepMap& g, const DeepTile& t, cons
     for (int j = jlo; j <= jhi; ++j, slot0 = slot0 + 1 == kRing ? 0 : slot0 + 1) {
         const int b = j & 1;
         // finish each level's plane and stage the strips' outer rows
-        V N[kDeepSteps + 1][R];
+        V N[ST + 1][R];
 #pragma unroll
         for (int r = 0; r < R; ++r) N[0][r] = F[r];
         if (tid < D::SH) L.shell[slot0][bslot] = bv;
@@ -331,12 +335,12 @@ __device__ __forceinline__ T deep_tile(const DeepMap& g, const DeepTile& t, cons
         load();
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int s = 0; s < kDeepSteps; ++s) {
+        for (int s = 0; s < ST; ++s) {
             *reinterpret_cast<V*>(&L.edge[b][s][strip][0][lx * VX]) = N[s][0];
             if constexpr (R > 1) *reinterpret_cast<V*>(&L.edge[b][s][strip][1][lx * VX]) = N[s][R - 1];
             const int p = j - 1 - s;
             __builtin_amdgcn_sched_barrier(0);
-            if (p == -1 || p == nz) {
+            if (p == -1 || p == nz || s < skip) {
                 // a boundary plane keeps its values
 #pragma unroll
                 for (int r = 0; r < R; ++r) N[s + 1][r] = U[s][r];
@@ -372,7 +376,7 @@ __device__ __forceinline__ T deep_tile(const DeepMap& g, const DeepTile& t, cons
         }
         __builtin_amdgcn_sched_barrier(0);
         // write the fourth step
-        const int p4 = j - kDeepSteps;
+        const int p4 = j - ST;
         if (p4 >= z0) {
             uint32_t d[R];
 #pragma unroll
@@ -382,9 +386,9 @@ __device__ __forceinline__ T deep_tile(const DeepMap& g, const DeepTile& t, cons
                 if (r >= r0 && r < r1) {
                     V* o = vec(d[r]);
                     if (hints & 1)
-                        __builtin_nontemporal_store(N[kDeepSteps][r], o);
+                        __builtin_nontemporal_store(N[ST][r], o);
                     else
-                        *o = N[kDeepSteps][r];
+                        *o = N[ST][r];
                 }
             if (want_res) {
 #pragma unroll
@@ -392,7 +396,7 @@ __device__ __forceinline__ T deep_tile(const DeepMap& g, const DeepTile& t, cons
                     if (r >= r0 && r < r1) {
 #pragma unroll
                         for (int i = 0; i < VX; ++i)
-                            if (!RAG || i < nv) res = max_abs(res, (T)(N[kDeepSteps][r][i] - U[kDeepSteps - 1][r][i]));
+                            if (!RAG || i < nv) res = max_abs(res, (T)(N[ST][r][i] - U[ST - 1][r][i]));
                     }
             }
             if (p4 + 1 < z1) {
@@ -410,7 +414,7 @@ __device__ __forceinline__ T deep_tile(const DeepMap& g, const DeepTile& t, cons
 
         // S of every level's new plane
 #pragma unroll
-        for (int s = kDeepSteps - 1; s >= 0; --s) {
+        for (int s = ST - 1; s >= 0; --s) {
             const int slot = slot0 >= s ? slot0 - s : slot0 - s + kRing;
             __builtin_amdgcn_sched_barrier(0);
             const T* ymp = &L.edge[b][s][strip > 0 ? strip - 1 : 0][D::RE - 1][lx * VX];
@@ -474,14 +478,14 @@ __device__ __forceinline__ T deep_tile(const DeepMap& g, const DeepTile& t, cons
     X(double, 4, false) X(double, 4, true) X(double, 1, false) X(double, 1, true)            \
     X(float, 4, false) X(float, 4, true) X(float, 1, false) X(float, 1, true)
 
-template <typename T, int R, bool RAG>
-__device__ __forceinline__ T deep_box(const DeepMap& g, const DeepTile& t, int parity, typename Deep<T, R>::Lds& L,
-                                      int hints, bool want_res) {
-    const bool m = t.ws == 0, p = t.ws + Deep<T, R>::LX >= g.nv;
-    return m ? (p ? deep_tile<T, R, 3, RAG>(g, t, parity, L, hints, want_res)
-                  : deep_tile<T, R, 1, RAG>(g, t, parity, L, hints, want_res))
-             : (p ? deep_tile<T, R, 2, RAG>(g, t, parity, L, hints, want_res)
-                  : deep_tile<T, R, 0, RAG>(g, t, parity, L, hints, want_res));
+template <typename T, int R, bool RAG, int W = deep_waves((int)sizeof(T))>
+__device__ __forceinline__ T deep_box(const DeepMap& g, const DeepTile& t, int parity,
+                                      typename Deep<T, R, W>::Lds& L, int hints, bool want_res, int skip = 0) {
+    const bool m = t.ws == 0, p = t.ws + Deep<T, R, W>::LX >= g.nv;
+    return m ? (p ? deep_tile<T, R, 3, RAG, W>(g, t, parity, L, hints, want_res, skip)
+                  : deep_tile<T, R, 1, RAG, W>(g, t, parity, L, hints, want_res, skip))
+             : (p ? deep_tile<T, R, 2, RAG, W>(g, t, parity, L, hints, want_res, skip)
+                  : deep_tile<T, R, 0, RAG, W>(g, t, parity, L, hints, want_res, skip));
 }
 
 }  // namespace od

@@ -1859,19 +1859,9 @@ __device__ __forceinline__ void serve_loop(const MsgArgs& a, SweepFn sweep, doub
 // fits 80 VGPRs with a few spills instead of taking 93-97 (5 or 4 waves),
 // and the extra wave per SIMD measured 2 % faster (512^3 fp64 ODF 4096,
 // 277 -> 283 GLUP/s; measured again with the current scheduler: 270 at 5
-// waves, 290 at 6).  The serving kernel asks for 5: on its own it took 116 VGPRs and
-// 4 waves; at 5 (96 VGPRs, no scratch) a saturated stream of 64 mixed
-// requests ran 228.6 -> 236 GLUP/s (p50 4.28 -> 4.15 s at 1000 requests/s).
-#ifndef OD_SCHED_WAVES
-#define OD_SCHED_WAVES 5
-#endif
+// waves, 290 at 6).
 #ifndef OD_MSG_WAVES
 #define OD_MSG_WAVES 6
-#endif
-#if OD_SCHED_WAVES > 0
-#define OD_SCHED_OCC __attribute__((amdgpu_waves_per_eu(OD_SCHED_WAVES, 8)))
-#else
-#define OD_SCHED_OCC
 #endif
 #if OD_MSG_WAVES > 0
 #define OD_MSG_OCC __attribute__((amdgpu_waves_per_eu(OD_MSG_WAVES, 8)))
@@ -1977,28 +1967,98 @@ k_deep_msg(MsgArgs a, DeepMap g, const DeepTile* __restrict__ tiles) {
     queue_loop<Deep<T, R>::NT>(a, sweep, red);
 }
 
-// Serving: tiles of independent fp64 and fp32 solves in one launch.  The two
-// tile variants have the same thread count; each task runs the variant of
-// its solve's dtype on a shared LDS buffer.  Block offsets are in elements
-// of the block's own dtype from the (256-byte aligned) arena base.
-template <int TX8, int TY8, int TX4, int TY4>
-__global__ void __launch_bounds__((TX8 / 2) * TY8) OD_SCHED_OCC k_serve(MsgArgs a) {
-    using S8 = SW<double, TX8, TY8>;
-    using S4 = SW<float, TX4, TY4>;
-    static_assert(S8::NT == S4::NT, "fp64 and fp32 serving tiles need the same thread count");
-    constexpr int LDSB = S8::LDS * 8 > S4::LDS * 4 ? S8::LDS * 8 : S4::LDS * 4;
-    __shared__ __attribute__((aligned(16))) unsigned char lds_raw[LDSB];
-    __shared__ double red[S8::NT / 64];
-    auto sweep = [&](int32_t gid, int32_t step) -> double {
-        const TileDev& t = a.tiles[gid];
-        const int32_t sv = a.tile_solve[gid];
-        if (a.solve_dtype[sv] == 8)
-            return (double)sweep_tile<double, TX8, TY8>(reinterpret_cast<double*>(a.arena), a.blocks, t, step & 1,
-                                                        reinterpret_cast<double*>(lds_raw), a.hints);
-        return (double)sweep_tile<float, TX4, TY4>(reinterpret_cast<float*>(a.arena), a.blocks, t, step & 1,
-                                                   reinterpret_cast<float*>(lds_raw), a.hints);
+// Serving: boxes of independent fp64 and fp32 solves in one launch, a task
+// being one pass (up to four steps) of one box.  The variants have the same
+// thread count and share the LDS; a solve's descriptor is read into scalar
+// registers, and its positions are offsets from the arena's base.
+// Tasks of one step were bound by memory (18 bytes per update fp64); these by the
+// pass, whose boxes fill a CU each, and by the box's planes where few solves
+// are in flight.  ms against tasks of one step: 16 solves of 32-256 cells an edge,
+// mixed types, 600 iterations checked every 10 80 / 168, of 32-48 11.7 / 35.1; one
+// of 256^3 fp64 24.2 / 54.0, of 64^3 10.7 / 20.1.  Checked at every iteration, where
+// each pass is one step: 205 / 211, 22.6 / 36.4, 57.8 / 60.9, 17.5 / 20.7.
+constexpr size_t serve_lds() {
+    size_t m = sizeof(typename Deep<double, 4, kServeWaves>::Lds);
+    m = m > sizeof(typename Deep<double, 1, kServeWaves>::Lds) ? m : sizeof(typename Deep<double, 1, kServeWaves>::Lds);
+    m = m > sizeof(typename Deep<float, 2, kServeWaves>::Lds) ? m : sizeof(typename Deep<float, 2, kServeWaves>::Lds);
+    return m > sizeof(typename Deep<float, 1, kServeWaves>::Lds) ? m : sizeof(typename Deep<float, 1, kServeWaves>::Lds);
+}
+
+// A uniform struct of 32-bit words in scalar registers.
+template <typename S>
+__device__ __forceinline__ S load_uniform(const char* p) {
+    static_assert(sizeof(S) % 4 == 0, "whole words");
+    union {
+        S v;
+        int32_t w[sizeof(S) / 4];
+    } u;
+#pragma unroll
+    for (size_t i = 0; i < sizeof(S) / 4; ++i) u.w[i] = __builtin_amdgcn_readfirstlane(reinterpret_cast<const int32_t*>(p)[i]);
+    return u.v;
+}
+
+__global__ void __launch_bounds__(kServeWaves * 64) OD_DEEP_OCC(4)
+k_serve(MsgArgs a, int64_t slots, int64_t slot_bytes, int32_t slot_tiles) {
+    __shared__ __align__(16) unsigned char lds_raw[serve_lds()];
+    __shared__ double red[kServeWaves];
+    auto sweep = [&](int32_t gid, int32_t pass) -> double {
+        const int32_t sv = __builtin_amdgcn_readfirstlane(a.tile_solve[gid]);
+        char* const ab = reinterpret_cast<char*>(a.arena);
+        const ServeSolve s = load_uniform<ServeSolve>(ab + slots + sv * slot_bytes);
+        const DeepTile t = load_uniform<DeepTile>(ab + s.tiles + (int64_t)(gid - sv * slot_tiles) * sizeof(DeepTile));
+        DeepMap g;
+        g.arena = ab + s.arena;
+        g.blocks = reinterpret_cast<const BlockDev*>(ab + s.blocks);
+        g.vx = reinterpret_cast<const int32_t*>(ab + s.tab[0]);
+        g.vi = reinterpret_cast<const int32_t*>(ab + s.tab[1]);
+        g.iy = reinterpret_cast<const int32_t*>(ab + s.tab[2]);
+        g.iz = reinterpret_cast<const int32_t*>(ab + s.tab[3]);
+        g.zn = reinterpret_cast<const int32_t*>(ab + s.tab[4]);
+        g.owner = nullptr;
+        g.corigin = reinterpret_cast<const int32_t*>(ab + s.corigin);
+        g.dir_pb = reinterpret_cast<const int32_t*>(ab + s.dir_pb);
+        g.k[0] = s.k[0];
+        g.k[1] = s.k[1];
+        g.nv = s.nv;
+        g.ny = s.ny;
+        g.nz = s.nz;
+        // steps of this pass: four, or an interval's first pass what fours leave over
+        const int32_t ce = s.check_every, q = ce > 0 ? pass / s.passes : 0, i = ce > 0 ? pass % s.passes : pass;
+        const int32_t left = ce > 0 ? min(ce, s.max_iters - q * ce) : s.max_iters;
+        const int32_t skip = i == 0 ? (kDeepSteps - left % kDeepSteps) % kDeepSteps : 0;
+        const bool dec = serve_decision(a, sv, pass + 1);
+        double r = 0;
+        const int dt = __builtin_amdgcn_readfirstlane(a.solve_dtype[sv]);
+        if (skip == kDeepSteps - 1) {
+            // one step: a pass of one level (the form with every boundary select
+            // serves all boxes); as four levels, three of them copies, the 16
+            // solves checked at every iteration took 396 ms
+#define OD_BOX1(T, R)                                                                                              \
+    if (dt == (int)sizeof(T) && s.rows == R)                                                                       \
+        return (double)deep_tile<T, R, 3, true, kServeWaves, 1>(                                                   \
+            g, t, pass & 1, *reinterpret_cast<typename Deep<T, R, kServeWaves>::Lds*>(lds_raw), 0, dec, 0);
+            OD_BOX1(double, 4)
+            OD_BOX1(double, 1)
+            OD_BOX1(float, 2)
+            OD_BOX1(float, 1)
+#undef OD_BOX1
+        }
+#define OD_BOX(T, R, RAG)                                                                                          \
+    if (dt == (int)sizeof(T) && s.rows == R && (s.ragged != 0) == RAG)                                             \
+        r = (double)deep_box<T, R, RAG, kServeWaves>(                                                              \
+            g, t, pass & 1, *reinterpret_cast<typename Deep<T, R, kServeWaves>::Lds*>(lds_raw), 0, dec, skip);
+        OD_BOX(double, 4, false)
+        OD_BOX(double, 4, true)
+        OD_BOX(double, 1, false)
+        OD_BOX(double, 1, true)
+        OD_BOX(float, 2, false)
+        OD_BOX(float, 2, true)
+        OD_BOX(float, 1, false)
+        OD_BOX(float, 1, true)
+#undef OD_BOX
+        return r;
     };
-    serve_loop<S8::NT>(a, sweep, red);
+    serve_loop<kServeWaves * 64>(a, sweep, red);
 }
 
 // ---------------------------------------------------------------------------
@@ -2567,20 +2627,16 @@ int serve_max_grid() {
     int dev = 0, ncu = 0, per = 0;
     if (hipGetDevice(&dev) != hipSuccess) return 0;
     if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_serve<kServeTx8, kServeTy8, kServeTx4, kServeTy4>,
-                                                     SW<double, kServeTx8, kServeTy8>::NT, 0) != hipSuccess)
-        return 0;
-    const std::string name = "od::k_serve<" + std::to_string(kServeTx8) + ", " + std::to_string(kServeTy8) + ", " +
-                             std::to_string(kServeTx4) + ", " + std::to_string(kServeTy4) + ">";
-    return coop_per_cu(per, SW<double, kServeTx8, kServeTy8>::NT, name.c_str(), 8) * ncu;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, k_serve, kServeWaves * 64, 0) != hipSuccess) return 0;
+    return coop_per_cu(per, kServeWaves * 64, "od::k_serve", 8) * ncu;
 }
 
-hipError_t launch_serve(hipStream_t st, int grid, const MsgArgs& a) {
+hipError_t launch_serve(hipStream_t st, int grid, const MsgArgs& a, int64_t slots, int64_t slot_bytes,
+                        int32_t slot_tiles) {
     MsgArgs ac = a;
-    void* args[] = {&ac};
-    return hipLaunchCooperativeKernel(
-        reinterpret_cast<const void*>(k_serve<kServeTx8, kServeTy8, kServeTx4, kServeTy4>), dim3(grid),
-        dim3(SW<double, kServeTx8, kServeTy8>::NT), args, 0, st);
+    void* args[] = {&ac, &slots, &slot_bytes, &slot_tiles};
+    return hipLaunchCooperativeKernel(reinterpret_cast<const void*>(k_serve), dim3(grid), dim3(kServeWaves * 64), args,
+                                      0, st);
 }
 
 hipError_t launch_msgdriven(int dtype_bytes, int tx, int ty, hipStream_t st, int grid, const MsgArgs& a) {

@@ -304,14 +304,14 @@ hipError_t launch_queue_init(hipStream_t st, const MsgArgs& a, int32_t target = 
 hipError_t launch_serve_positions(hipStream_t st, const int32_t* list, int32_t n, int32_t stride, int32_t* tpos,
                                   int32_t* sbase);
 
-// Serving kernel: fp64 tiles of (kServeTx8, kServeTy8) and fp32 tiles of
-// (kServeTx4, kServeTy4) columns, same thread count, one cooperative launch.
-#ifndef OD_SERVE_TY8
-#define OD_SERVE_TY8 16    // rows of an fp64 serving tile (fp32 tiles have twice as many)
-#endif
-constexpr int kServeTx8 = 32, kServeTy8 = OD_SERVE_TY8, kServeTx4 = 32, kServeTy4 = 2 * OD_SERVE_TY8;
+// Columns of the tiles a request is planned in (its storage and the limits on
+// what a slot takes).
+constexpr int kServeTx8 = 32, kServeTy8 = 16, kServeTx4 = 32, kServeTy4 = 32;
 int serve_max_grid();
-hipError_t launch_serve(hipStream_t st, int grid, const MsgArgs& a);
+// Serving kernel, one cooperative launch: solve i's descriptor (ServeSolve) at
+// byte slots + i * slot_bytes of the arena, its boxes' ids from i * slot_tiles.
+hipError_t launch_serve(hipStream_t st, int grid, const MsgArgs& a, int64_t slots, int64_t slot_bytes,
+                        int32_t slot_tiles);
 
 // Multi-resolution ghost fill: one rectangle of a chare face's ghost buffer
 // read from one neighbour chare of another cell size.  Ghost cell (c1, c2)

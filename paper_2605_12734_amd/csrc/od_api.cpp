@@ -973,25 +973,16 @@ od_status Grid::upload() {
     if (e == hipSuccess) e = put(L.dep_idx, dep_idx.data(), dep_idx.size() * 4);
     std::vector<int32_t> tab;
     if (!deep_plan.tiles.empty()) {
-        tab = deep_plan.vx;
-        tab.insert(tab.end(), deep_plan.vi.begin(), deep_plan.vi.end());
-        const size_t ty = tab.size();
-        for (int d = 1; d < 3; ++d)
-            for (int64_t v = 0; v < p.n[d]; ++v) tab.push_back(p.regular ? cidx[d][(size_t)v] : (int32_t)(v / p.gran));
-        const size_t tz = ty + (size_t)p.n[1], tn = tab.size();
-        for (int64_t v = 0; v < p.n[2]; ++v) {
-            int64_t q = v + 1;
-            while (q < p.n[2] && tab[tz + (size_t)q] == tab[tz + (size_t)v]) ++q;
-            tab.push_back((int32_t)q);
-        }
+        size_t at[5];
+        tab = deep_tables(p, deep_plan, at);
         if (e == hipSuccess) e = put(L.deep, deep_plan.tiles.data(), deep_plan.tiles.size() * sizeof(DeepTile));
         if (e == hipSuccess) e = put(L.deep_tab, tab.data(), tab.size() * 4);
         const int32_t* t = reinterpret_cast<const int32_t*>(cp(L.deep_tab));
-        deep_map.vx = t;
-        deep_map.vi = t + deep_plan.vx.size();
-        deep_map.iy = t + ty;
-        deep_map.iz = t + tz;
-        deep_map.zn = t + tn;
+        deep_map.vx = t + at[0];
+        deep_map.vi = t + at[1];
+        deep_map.iy = t + at[2];
+        deep_map.iz = t + at[3];
+        deep_map.zn = t + at[4];
         deep_map.nv = (int32_t)deep_plan.vi.size();
         deep_map.ny = (int32_t)p.n[1];
         deep_map.nz = (int32_t)p.n[2];
@@ -1129,7 +1120,8 @@ od_status Grid::fused_deep(hipStream_t s2, int par, int64_t step, bool last) {
 }
 
 od_status Grid::fused_deep_pass(hipStream_t s2, int par, bool last) {
-    hipError_t e = (cfg.stencil == 5 ? launch_deep2d : launch_deep)(s, deep_plan, s2, deep_map, reinterpret_cast<const DeepTile*>(cp(L.deep)), par, res_ptr(), 0, 1, mode(), last);
+    hipError_t e = (cfg.stencil == 5 ? launch_deep2d : launch_deep)(
+        s, deep_plan, s2, deep_map, reinterpret_cast<const DeepTile*>(cp(L.deep)), par, res_ptr(), 0, 1, mode(), last);
     if (e != hipSuccess) return fail(OD_EHIP, std::string("four-step sweep launch: ") + hipGetErrorString(e));
     return OD_OK;
 }

@@ -324,7 +324,7 @@ od_status od_pass_info(od_grid* g, int32_t* steps, int64_t* bytes, int32_t* boxe
     const od::DeepPlan& d = G.deep_plan;
     *count = G.deep() ? (int32_t)d.tiles.size() : 0;
     int lx = 64, ey = 1;   // the 2D stencil's waves
-    if (d.rows > 0) od::deep_shape(G.s, d.rows, &lx, &ey);
+    if (d.rows > 0) od::deep_shape(G.s, d, &lx, &ey);
     const int32_t nv = (int32_t)d.vi.size(), ny = (int32_t)G.plan.n[1];
     for (int32_t i = 0; i < *count && i < cap; ++i) {
         const od::DeepTile& t = d.tiles[(size_t)i];

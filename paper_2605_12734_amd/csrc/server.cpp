@@ -2,6 +2,10 @@
 // admitted as they arrive under a device-memory budget and run together by
 // the message-driven device scheduler (continuous batching).
 //
+// A task is one pass of up to four iterations over one box; between two
+// decision steps the first pass takes what fours leave over, and the scheduler
+// counts passes (serve_passes and the functions beside it).
+//
 // A worker thread owns the device.  Each round it admits queued requests
 // (FIFO) while a slot and arena space are free, then launches one
 // scheduling epoch: a cooperative kernel over the tiles of every resident
@@ -43,6 +47,10 @@ constexpr int32_t kMaxTiles = 8192;                 // tiles per solve
 constexpr int32_t kTileStride = kMaxTiles + 1;      // per-slot stride of per-tile arrays
 constexpr int32_t kMaxBlocks = 256;                 // chares + Dirichlet faces per solve
 constexpr int32_t kMaxDeps = 8 * kMaxTiles;         // dependency entries per solve
+// A slot's part of c_slots: descriptor, tables of up to 1024 cells an axis, boxes.
+constexpr size_t kSlotBytes = 128 + (5 * 1024 + 4) * 4 + kServeBoxes * sizeof(DeepTile);
+static_assert(kSlotBytes % 16 == 0 && kSlotBytes <= kTileStride * sizeof(TileDev), "slot layout");
+static_assert(kServeBoxes <= kMaxTiles && 26 * kServeBoxes <= kMaxDeps, "boxes fit a slot's lists");
 constexpr size_t kMaxQueue = 1 << 16;
 
 double now_s() {
@@ -58,8 +66,8 @@ od_config request_config(const od_request& r) {
     for (int i = 0; i < 6; ++i) c.bc[i] = r.bc[i];
     c.seed = r.seed;
     c.exec = OD_MSGDRIVEN;
-    // the serving kernel runs tasks of one step (a solve may stop at any
-    // step): its dependency lists reach one cell
+    // storage and tables of a grid of one step per pass (the serving kernel
+    // has boxes of its own, Request::boxes)
     c.hints = 4096;
     if (r.dtype == OD_F64) {
         c.tile[0] = kServeTx8;
@@ -84,6 +92,8 @@ struct Request {
     int64_t iters = 0;
     double residual = 0;
     std::unique_ptr<Grid> grid;
+    DeepPlan boxes;
+    std::vector<int32_t> dep_ptr, dep_idx;   // of the boxes
     size_t off = 0;
     bool finished = false;           // final step reached; waiting to be copied out
     std::vector<char> result;
@@ -96,7 +106,7 @@ struct Server {
     size_t arena_bytes = 0;
     int32_t max_slots = 0;
     // control region (byte offsets from arena)
-    size_t c_blocks = 0, c_tiles = 0, c_done = 0, c_dep_ptr = 0, c_dep_idx = 0, c_tile_solve = 0;
+    size_t c_slots = 0, c_done = 0, c_dep_ptr = 0, c_dep_idx = 0, c_tile_solve = 0;
     size_t c_target = 0, c_final = 0, c_gate = 0, c_count = 0, c_res = 0, c_ce = 0, c_tol = 0, c_ntiles = 0;
     size_t c_dtype = 0, c_list = 0, c_err = 0, c_yield = 0, c_xpub = 0, c_tpos = 0, c_bar = 0;
     size_t c_sbase = 0, c_pend = 0, c_qslots = 0, c_qctl = 0;
@@ -202,33 +212,46 @@ od_status Server::setup_slot(Request& R, int32_t slot) {
     if (s == OD_OK) s = G.reset_state();
     if (s == OD_OK) s = G.init_field();
     if (s != OD_OK) return s;
-    const int32_t ntiles = (int32_t)G.tiles_h.size();
-    const int sb = G.s;
-    std::vector<BlockDev> blocks(G.blocks_h);
-    for (BlockDev& b : blocks) {
-        b.off[0] += (int64_t)(R.off / (size_t)sb);
-        b.off[1] += (int64_t)(R.off / (size_t)sb);
-    }
-    std::vector<TileDev> tiles(G.tiles_h);
-    for (TileDev& t : tiles) {
-        t.blk += slot * kMaxBlocks;
-        for (int f = 0; f < 6; ++f) t.f[f].src += slot * kMaxBlocks;
-        t.rslot = slot;
-    }
+    const Plan& p = G.plan;
+    const int32_t ntiles = (int32_t)R.boxes.tiles.size();
+    // descriptor, per-axis tables and boxes, in the slot's part of c_slots
+    ServeSolve sd{};
+    size_t at[5];
+    const std::vector<int32_t> tab = deep_tables(p, R.boxes, at);
+    const size_t o_solve = c_slots + (size_t)slot * kSlotBytes, o_tab = o_solve + align_up(sizeof(ServeSolve), 16),
+                 o_tiles = o_tab + align_up(tab.size() * 4, 16);
+    if (o_tiles + (size_t)ntiles * sizeof(DeepTile) > o_solve + kSlotBytes)
+        return fail(OD_EINVAL, "serving admission: tables larger than a slot");
+    sd.arena = (int64_t)R.off;
+    sd.blocks = (int64_t)(R.off + G.L.blocks);
+    sd.corigin = (int64_t)(R.off + G.L.corigin);
+    sd.dir_pb = (int64_t)(R.off + G.L.dir_pb);
+    sd.tiles = (int64_t)o_tiles;
+    for (int q = 0; q < 5; ++q) sd.tab[q] = (int64_t)(o_tab + at[q] * 4);
+    for (int q = 0; q < 2; ++q) sd.k[q] = p.k[q];
+    sd.nv = (int32_t)R.boxes.vi.size();
+    sd.ny = (int32_t)p.n[1];
+    sd.nz = (int32_t)p.n[2];
+    sd.rows = R.boxes.rows;
+    sd.ragged = R.boxes.ragged ? 1 : 0;
+    sd.check_every = R.req.check_every;
+    sd.max_iters = (int32_t)R.req.max_iters;
+    sd.passes = serve_passes(sd.check_every);
     const int32_t tbase = slot * kTileStride;
-    std::vector<int32_t> dep_ptr((size_t)ntiles + 1), dep_idx(G.dep_idx.size());
-    for (int32_t i = 0; i <= ntiles; ++i) dep_ptr[(size_t)i] = slot * kMaxDeps + G.dep_ptr[(size_t)i];
-    for (size_t q = 0; q < G.dep_idx.size(); ++q) dep_idx[q] = tbase + G.dep_idx[q];
+    std::vector<int32_t> dep_ptr((size_t)ntiles + 1), dep_idx(R.dep_idx.size());
+    for (int32_t i = 0; i <= ntiles; ++i) dep_ptr[(size_t)i] = slot * kMaxDeps + R.dep_ptr[(size_t)i];
+    for (size_t q = 0; q < R.dep_idx.size(); ++q) dep_idx[q] = tbase + R.dep_idx[q];
     std::vector<int32_t> zeros((size_t)ntiles, 0), owner((size_t)ntiles, slot);
-    const int32_t tgt = (int32_t)R.req.max_iters, zero = 0, ce = R.req.check_every, dt = (int32_t)R.req.dtype;
+    // (the scheduler counts passes)
+    const int32_t tgt = serve_target(sd.check_every, sd.max_iters), zero = 0, ce = sd.passes, dt = (int32_t)R.req.dtype;
     const unsigned long long zr = 0;
     const double tol = R.req.tol;
     auto put = [&](size_t off, const void* src, size_t n) -> hipError_t {
         return n ? hipMemcpyAsync(arena + off, src, n, hipMemcpyHostToDevice, st) : hipSuccess;
     };
-    hipError_t e = put(c_blocks + (size_t)slot * kMaxBlocks * sizeof(BlockDev), blocks.data(),
-                       blocks.size() * sizeof(BlockDev));
-    if (e == hipSuccess) e = put(c_tiles + (size_t)tbase * sizeof(TileDev), tiles.data(), tiles.size() * sizeof(TileDev));
+    hipError_t e = put(o_solve, &sd, sizeof(sd));
+    if (e == hipSuccess) e = put(o_tab, tab.data(), tab.size() * 4);
+    if (e == hipSuccess) e = put(o_tiles, R.boxes.tiles.data(), (size_t)ntiles * sizeof(DeepTile));
     if (e == hipSuccess) e = put(c_done + (size_t)tbase * 4, zeros.data(), zeros.size() * 4);
     if (e == hipSuccess) e = put(c_tile_solve + (size_t)tbase * 4, owner.data(), owner.size() * 4);
     if (e == hipSuccess) e = put(c_dep_ptr + (size_t)tbase * 4, dep_ptr.data(), dep_ptr.size() * 4);
@@ -255,11 +278,11 @@ void Server::retire(Request& R) {
     // engine while the next epoch runs, lay it out as the padded global
     // field (Dirichlet shell from the request), free the arena space.
     Grid& G = *R.grid;
-    const int32_t fs = __atomic_load_n(&h_done[R.slot], __ATOMIC_ACQUIRE);
+    const int32_t passes = __atomic_load_n(&h_done[R.slot], __ATOMIC_ACQUIRE);
     unsigned long long rb = __atomic_load_n(&h_res[R.slot], __ATOMIC_ACQUIRE);
     double r;
     std::memcpy(&r, &rb, 8);
-    const int par = fs & 1;
+    const int par = passes & 1;
     const int64_t n = R.req.n, P = n + 2;
     const size_t s = (size_t)G.s;
     std::vector<char> host((size_t)P * P * P * s, 0);
@@ -302,7 +325,7 @@ void Server::retire(Request& R) {
         }
     }
     std::lock_guard<std::mutex> lk(mu);
-    R.iters = fs;
+    R.iters = serve_iters(R.req.check_every, (int32_t)R.req.max_iters, passes);
     R.residual = r;
     if (e == hipSuccess) {
         R.result.swap(host);
@@ -374,7 +397,7 @@ void Server::run() {
                 Request& R = *reqs[t];
                 if (R.state != OD_REQ_RUNNING || R.finished) continue;
                 active.push_back(&R);
-                const int32_t nt = (int32_t)R.grid->tiles_h.size();
+                const int32_t nt = (int32_t)R.boxes.tiles.size();
                 for (int32_t i = 0; i < nt; ++i) list.push_back(s2 * kTileStride + i);
                 // keep every solve's XCD groups aligned to launch positions mod 8
                 while (list.size() % kNumXcd) list.push_back(-1);
@@ -402,8 +425,6 @@ void Server::run() {
         a.tile_list = reinterpret_cast<const int32_t*>(arena + c_list);
         a.solve_dtype = reinterpret_cast<const int32_t*>(arena + c_dtype);
         a.arena = arena;
-        a.blocks = reinterpret_cast<const BlockDev*>(arena + c_blocks);
-        a.tiles = reinterpret_cast<const TileDev*>(arena + c_tiles);
         a.ntiles = (int32_t)list.size();
         a.dep_ptr = reinterpret_cast<const int32_t*>(arena + c_dep_ptr);
         a.dep_idx = reinterpret_cast<const int32_t*>(arena + c_dep_idx);
@@ -441,7 +462,7 @@ void Server::run() {
         if (grid >= kNumXcd) grid -= grid % kNumXcd;
         if (e == hipSuccess) e = launch_queue_init(st, a);
         t_epoch = now_s();
-        if (e == hipSuccess) e = launch_serve(st, grid, a);
+        if (e == hipSuccess) e = launch_serve(st, grid, a, (int64_t)c_slots, (int64_t)kSlotBytes, kTileStride);
         if (e == hipSuccess) e = hipEventRecord(ev, st);
         launched = e == hipSuccess;
         }
@@ -558,8 +579,7 @@ size_t control_layout(Server& S, int32_t max_slots) {
         return r;
     };
     const size_t ms = (size_t)max_slots;
-    S.c_blocks = take(ms * kMaxBlocks * sizeof(BlockDev));
-    S.c_tiles = take(ms * kTileStride * sizeof(TileDev));
+    S.c_slots = take(ms * kMaxBlocks * sizeof(BlockDev) + ms * kTileStride * sizeof(TileDev));
     S.c_done = take(ms * kTileStride * 4);
     S.c_tile_solve = take(ms * kTileStride * 4);
     S.c_dep_ptr = take(ms * kTileStride * 4);
@@ -610,7 +630,7 @@ od_status validate_request(const od_request* r) {
 }
 
 // Plan of a request: its grid (host side) and the arena bytes it needs.
-od_status plan_request(const od_request* r, std::unique_ptr<od::Grid>& G) {
+od_status plan_request(const od_request* r, std::unique_ptr<od::Grid>& G, od::Request* R = nullptr) {
     od_status s = validate_request(r);
     if (s != OD_OK) return s;
     G.reset(new od::Grid);
@@ -620,6 +640,13 @@ od_status plan_request(const od_request* r, std::unique_ptr<od::Grid>& G) {
     if (G->tiles_h.size() > (size_t)od::kMaxTiles || G->blocks_h.size() > (size_t)od::kMaxBlocks ||
         G->dep_idx.size() > (size_t)od::kMaxDeps)
         return fail(OD_EINVAL, "request too large for a serving slot (tiles/blocks/dependencies)");
+    if (R) {
+        R->boxes = od::deep_plan_serve(G->plan, G->s);
+        od::deep_deps(R->boxes, G->s, R->dep_ptr, R->dep_idx);
+        if (R->boxes.tiles.empty() || R->boxes.tiles.size() > (size_t)od::kServeBoxes ||
+            R->dep_idx.size() > (size_t)od::kMaxDeps)
+            return fail(OD_EINVAL, "request too large for a serving slot (boxes)");
+    }
     return OD_OK;
 }
 
@@ -712,11 +739,11 @@ od_status od_submit(od_server* sv, const od_request* req, uint64_t* ticket) {
     try {
         if (!sv || !ticket) return fail(OD_EINVAL, "NULL argument");
         std::unique_ptr<od::Grid> G;
-        od_status s = plan_request(req, G);
+        std::unique_ptr<od::Request> R(new od::Request);
+        od_status s = plan_request(req, G, R.get());
         if (s != OD_OK) return s;
         od::Server& S = sv->s;
         const size_t bytes = od::align_up(G->L.total, od::kAlign);
-        std::unique_ptr<od::Request> R(new od::Request);
         R->req = *req;
         R->bytes = bytes;
         R->grid = std::move(G);

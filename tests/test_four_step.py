@@ -247,3 +247,26 @@ def test_2d_stencil(dtype, exec_, n, odf, iters):
         g.close()
     _same(U, want)
     assert got == r
+
+
+# Served solves: passes of up to four steps.  Sizes at the edges of the boxes
+# (one row a strip below 64, the lanes' 64 cells, full and partial vectors) and
+# every remainder of the interval between checks; the reference is the oracle's
+# solve with the same stopping rule, the tolerance 0.
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("check_every", [0, 1, 2, 3, 4, 6, 9])
+def test_served_passes_match_oracle(dtype, check_every):
+    from paper_2605_12734_amd.serving import Server
+
+    reqs = [dict(n=n, dtype=dtype, odf=odf, tol=tol, max_iters=iters, check_every=check_every, seed=n)
+            for n, odf, tol, iters in [(1, 1, 0.0, 5), (4, 1, 0.0, 1), (31, 8, 0.0, 13), (63, 27, 2e-3, 40), (64, 8, 0.0, 7),
+                                       (65, 1, 2e-3, 22), (96, 8, 0.0, 11), (130, 64, 0.0, 6)]]
+    with Server(arena_bytes=1 << 30, max_slots=16) as srv:
+        tickets = [srv.submit(**q) for q in reqs]
+        for t, q in zip(tickets, reqs):
+            res, field = srv.wait(t), srv.fetch(t)
+            want, it, r = oracle.solve(q["n"], DT[dtype], seed=q["seed"], iters=q["max_iters"], tol=q["tol"],
+                                       check_every=check_every)
+            assert (res["iters"], res["residual"]) == (it, r), q
+            assert np.array_equal(field, want), q
