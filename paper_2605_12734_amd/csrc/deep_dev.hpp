@@ -21,7 +21,7 @@
 // order, so the result is the same bits.
 //
 // Bound: a pair of steps per pass is bound by HBM (9.45 bytes per update at
-// 512^3 fp64, 5.2 TB/s), so the passes got longer: 4.4 bytes per update here,
+// 512^3 fp64, 5.2 TB/s), so the passes got longer: 4.5 bytes per update here,
 // counters included.  64 x 64 cells are what a CU can hold: 128 VGPRs of
 // levels per lane at two waves per SIMD in fp64, and 128 KB of LDS for the outer
 // rows; fp32 holds two such tiles.  The lanes' overlap computes 1.3 times the

@@ -352,11 +352,6 @@ __device__ __forceinline__ T sweep_tile(T* __restrict__ arena, const BlockDev* _
     return r;
 }
 
-// imb.only: the re-runs that go ahead of a four-step pass, as a launch of
-// their own.  (512^3 fp64, 10 % of 512 chares re-running 1-4 times a step,
-// us per iteration: 318, of which the pass takes 154, against 455 with pairs
-// that run each tile's re-runs and pass in one workgroup; ODF 8 319 / 446,
-// 4096 332 / 449.)
 template <typename T, int TX, int TY, bool XEXP = false>
 __global__ void __launch_bounds__((TX / V16<T>::N) * TY)
 k_sweep(T* __restrict__ arena, const BlockDev* __restrict__ blocks, const TileDev* __restrict__ tiles,
@@ -365,15 +360,9 @@ k_sweep(T* __restrict__ arena, const BlockDev* __restrict__ blocks, const TileDe
     using S = SW<T, TX, TY>;
     __shared__ T lds[S::LDS];
     __shared__ T red[S::NT / 64];
-    const TileDev& t = tiles[blockIdx.x];
-    if (imb.only > 0) {
-        int extra = 0;
-        for (int k = 0; k < imb.only; ++k) extra += imb_extra(imb, step + k, t.blk);
-        for (int e = 0; e < extra; ++e) (void)sweep_tile<T, TX, TY>(arena, blocks, t, parity, lds, hints);
-        return;
-    }
     if (blockIdx.x == 0)
         for (int s = zero_lo + (int)threadIdx.x; s < zero_hi; s += S::NT) res[2 * s + parity] = 0ull;
+    const TileDev& t = tiles[blockIdx.x];
     const int reps = 1 + imb_extra(imb, step, t.blk);
     T r = 0;
     for (int rep = 0; rep < reps; ++rep)
@@ -1920,6 +1909,22 @@ k_msgdriven2(MsgArgs a) {
     queue_loop<S::NT>(a, sweep, red);
 }
 
+// The re-runs that go ahead of a four-step pass under load imbalance, as a
+// launch of their own.  (512^3 fp64, 10 % of 512 chares re-running 1-4 times a
+// step, us per iteration: 318, of which the pass takes 154, against 455 with
+// pairs that run each tile's re-runs and pass in one workgroup; ODF 8 319 / 446,
+// 4096 332 / 449.)
+template <typename T, int TX, int TY>
+__global__ void __launch_bounds__((TX / V16<T>::N) * TY)
+k_rerun(T* __restrict__ arena, const BlockDev* __restrict__ blocks, const TileDev* __restrict__ tiles, int parity,
+        ImbDev imb, int64_t step, int steps, int hints) {
+    __shared__ T lds[SW<T, TX, TY>::LDS];
+    const TileDev& t = tiles[blockIdx.x];
+    int extra = 0;
+    for (int k = 0; k < steps; ++k) extra += imb_extra(imb, step + k, t.blk);
+    for (int e = 0; e < extra; ++e) (void)sweep_tile<T, TX, TY>(arena, blocks, t, parity, lds, hints);
+}
+
 // Four-step passes (deep_dev.hpp) of a persistent grid: every pass in one
 // cooperative launch, boxes dealt to the workgroups by a fixed stride, the
 // per-XCD barrier between passes.  The boxes are cut to fill the chip in whole
@@ -2311,6 +2316,22 @@ hipError_t launch_sweep(int dtype_bytes, int tx, int ty, hipStream_t st, void* a
             hipLaunchKernelGGL((k_sweep<T, TX, TY, false>), dim3(ntiles), dim3(SW<T, TX, TY>::NT), 0, st, \
                                reinterpret_cast<T*>(arena), blocks, tiles, parity, res, zero_lo, zero_hi, \
                                imb, step, hints, xexp);                                               \
+        return hipGetLastError();                                                                     \
+    }
+    OD_VARIANTS_F64(OD_LAUNCH)
+    OD_VARIANTS_F32(OD_LAUNCH)
+#undef OD_LAUNCH
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_rerun(int dtype_bytes, int tx, int ty, hipStream_t st, void* arena, const BlockDev* blocks,
+                        const TileDev* tiles, int32_t ntiles, int parity, const ImbDev& imb, int64_t step,
+                        int steps, int hints) {
+    if (ntiles <= 0) return hipSuccess;
+#define OD_LAUNCH(T, TX, TY)                                                                          \
+    if (dtype_bytes == (int)sizeof(T) && tx == TX && ty == TY) {                                      \
+        hipLaunchKernelGGL((k_rerun<T, TX, TY>), dim3(ntiles), dim3(SW<T, TX, TY>::NT), 0, st,        \
+                           reinterpret_cast<T*>(arena), blocks, tiles, parity, imb, step, steps, hints); \
         return hipGetLastError();                                                                     \
     }
     OD_VARIANTS_F64(OD_LAUNCH)

@@ -39,7 +39,7 @@ struct ImbDev {
     int32_t nchares;
     int32_t heavy;     // chares drawn per step (0 = no imbalance)
     int32_t maxe;      // largest number of extra re-runs
-    int32_t only;      // launch_sweep: 0 = a sweep with its re-runs; k > 0 = only the re-runs of k steps
+    int32_t pad_;
 };
 
 __host__ __device__ inline uint64_t imb_mix(uint64_t seed, uint64_t idx) {
@@ -101,10 +101,7 @@ int sweep_threads(int dtype_bytes, int tx, int ty);
 // `parity`, writing parity^1.  Residual of tile t goes (atomic max of the
 // value's bit pattern) into res[2*rslot + (parity^1)]; workgroup 0 first
 // zeroes res[2*s + parity] for s in [zero_lo, zero_hi).  `imb`, `step`:
-// the load-imbalance draw of this step (imb.heavy == 0: none).  With imb.only
-// the launch runs nothing but the re-runs of steps step .. step + only - 1,
-// from `parity` into the tiles' own cells of parity ^ 1, ahead of a pass that
-// overwrites them; res is left alone.
+// the load-imbalance draw of this step (imb.heavy == 0: none).
 // xexp (may be null): multi-resolution x-column exports (XExpDev, per chare).
 struct XExpDev;
 struct FillSeg;
@@ -112,6 +109,11 @@ hipError_t launch_sweep(int dtype_bytes, int tx, int ty, hipStream_t st, void* a
                         const BlockDev* blocks, const TileDev* tiles, int32_t ntiles, int parity,
                         unsigned long long* res, int32_t zero_lo, int32_t zero_hi,
                         const ImbDev& imb, int64_t step, int hints, const XExpDev* xexp = nullptr);
+// Nothing but the re-runs of steps step .. step + steps - 1, from `parity` into
+// the tiles' own cells of parity ^ 1, ahead of a pass that overwrites them.
+hipError_t launch_rerun(int dtype_bytes, int tx, int ty, hipStream_t st, void* arena, const BlockDev* blocks,
+                        const TileDev* tiles, int32_t ntiles, int parity, const ImbDev& imb, int64_t step,
+                        int steps, int hints);
 
 // Two Jacobi steps per pass (regular grids at one resolution, 3D 7-point
 // stencil): each tile reads the time-t field once, computes the first step

@@ -1108,12 +1108,10 @@ od_status Grid::fused_two(hipStream_t s2, int par, int64_t step) {
 
 od_status Grid::fused_deep(hipStream_t s2, int par, int64_t step, bool last) {
     if (imb.heavy > 0) {
-        ImbDev m = imb;
-        m.only = kDeepSteps;
-        hipError_t e0 = launch_sweep(s, plan.tile[0], plan.tile[1], s2, base,
+        hipError_t e0 = launch_rerun(s, plan.tile[0], plan.tile[1], s2, base,
                                      reinterpret_cast<const BlockDev*>(cp(L.blocks)),
                                      reinterpret_cast<const TileDev*>(cp(L.tiles)), (int32_t)tiles_h.size(), par,
-                                     res_ptr(), 0, 0, m, step, mode());
+                                     imb, step, kDeepSteps, mode());
         if (e0 != hipSuccess) return fail(OD_EHIP, std::string("re-run launch: ") + hipGetErrorString(e0));
     }
     return fused_deep_pass(s2, par, last);
