@@ -2825,6 +2825,21 @@ __global__ void k_gather(GridDev g, int parity, int64_t kz_lo, int64_t kz_hi, T*
     }
 }
 
+// A block's cells, rows packed, into host memory that the device can write, and
+// the grid's error word behind them.  A small block's read is bound by its round
+// trips (a copy of the error word, a copy of the block); this is one.  us with the
+// two copies and so: 16^3 fp64 30.4 / 15.5, 4^3 25.1 / 14.2, 50^3 91 / 55, fp32 64^3 77 / 71.
+template <typename T>
+__global__ void k_read_block(const T* src, int32_t ex, int32_t ey, int32_t ez, int64_t py, int64_t pz, T* dst,
+                             const unsigned int* err, unsigned int* err_dst) {
+    const int32_t total = ex * ey * ez;
+    for (int32_t e = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x); e < total; e += (int32_t)(gridDim.x * blockDim.x)) {
+        const int32_t x = e % ex, y = e / ex % ey, z = e / ex / ey;
+        dst[e] = src[z * pz + y * py + x];
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) *err_dst = *err;
+}
+
 template <typename T>
 __global__ void k_scatter(GridDev g, int parity, int64_t kz_lo, int64_t kz_hi, const T* src) {
     T* arena = reinterpret_cast<T*>(g.arena);
@@ -2939,6 +2954,21 @@ hipError_t launch_gather(int dtype_bytes, hipStream_t st, const GridDev& g, int 
     else
         hipLaunchKernelGGL(k_gather<float>, dim3(io_grid(total)), dim3(256), 0, st, g, parity, kz_lo, kz_hi,
                            reinterpret_cast<float*>(dst));
+    return hipGetLastError();
+}
+
+hipError_t launch_read_block(int dtype_bytes, hipStream_t st, const void* src, const int32_t cells[3], int64_t py,
+                             int64_t pz, void* dst, const unsigned int* err, unsigned int* err_dst) {
+    const int64_t total = (int64_t)cells[0] * cells[1] * cells[2];
+    if (total <= 0 || total > INT32_MAX / 2) return hipErrorInvalidValue;
+    if (dtype_bytes == 8)
+        hipLaunchKernelGGL(k_read_block<double>, dim3(io_grid(total)), dim3(256), 0, st,
+                           reinterpret_cast<const double*>(src), cells[0], cells[1], cells[2], py, pz,
+                           reinterpret_cast<double*>(dst), err, err_dst);
+    else
+        hipLaunchKernelGGL(k_read_block<float>, dim3(io_grid(total)), dim3(256), 0, st,
+                           reinterpret_cast<const float*>(src), cells[0], cells[1], cells[2], py, pz,
+                           reinterpret_cast<float*>(dst), err, err_dst);
     return hipGetLastError();
 }
 

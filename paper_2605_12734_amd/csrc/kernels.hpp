@@ -378,6 +378,8 @@ hipError_t launch_init(int dtype_bytes, hipStream_t st, const GridDev& g, int32_
 // host-mapped), plane kz_lo at dst[0].  scatter: the inverse.
 hipError_t launch_gather(int dtype_bytes, hipStream_t st, const GridDev& g, int parity,
                          int64_t kz_lo, int64_t kz_hi, void* dst);
+hipError_t launch_read_block(int dtype_bytes, hipStream_t st, const void* src, const int32_t cells[3], int64_t py,
+                             int64_t pz, void* dst, const unsigned int* err, unsigned int* err_dst);
 hipError_t launch_scatter(int dtype_bytes, hipStream_t st, const GridDev& g, int parity,
                           int64_t kz_lo, int64_t kz_hi, const void* src);
 hipError_t launch_points(int dtype_bytes, hipStream_t st, const GridDev& g, int parity,

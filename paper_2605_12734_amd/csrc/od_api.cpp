@@ -1482,18 +1482,24 @@ od_status Grid::iterate(int64_t n) {
     return fail(OD_EINVAL, "unknown exec mode");
 }
 
-od_status Grid::device_error() {
-    hipError_t e = hipStreamSynchronize(st);
-    if (e != hipSuccess) return fail(OD_EHIP, std::string("sync: ") + hipGetErrorString(e));
-    unsigned int err = 0;
-    e = hipMemcpy(&err, cp(L.err), 4, hipMemcpyDeviceToHost);
-    if (e != hipSuccess) return fail(OD_EHIP, std::string("read error flag: ") + hipGetErrorString(e));
+namespace {
+od_status error_status(unsigned int err) {
     if (err & kErrSchedule)
         return fail(OD_ESCHED, "message-driven schedule check failed: a tile's step counter did not advance by one, "
                                "or a tile ran while a neighbour was not within one step (flag " +
                                    std::to_string(err) + ")");
     if (err != 0) return fail(OD_ETIMEDOUT, "a device-side wait exceeded its bound (flag " + std::to_string(err) + ")");
     return OD_OK;
+}
+}  // namespace
+
+od_status Grid::device_error() {
+    hipError_t e = hipStreamSynchronize(st);
+    if (e != hipSuccess) return fail(OD_EHIP, std::string("sync: ") + hipGetErrorString(e));
+    unsigned int err = 0;
+    e = hipMemcpy(&err, cp(L.err), 4, hipMemcpyDeviceToHost);
+    if (e != hipSuccess) return fail(OD_EHIP, std::string("read error flag: ") + hipGetErrorString(e));
+    return error_status(err);
 }
 
 od_status Grid::residual(double* r) {
@@ -1697,12 +1703,35 @@ od_status Grid::io(void* host, size_t bytes, bool to_host) {
     return OD_OK;
 }
 
+// Blocks up to this size are read by a kernel that writes host memory; larger
+// ones by the copy engine, behind a copy of the error word: at 1 MiB the two
+// round trips that the kernel saves are 8 % (fp32 64^3 77 / 71 us).
+constexpr size_t kSmallBlock = (size_t)1 << 20;
+
 od_status Grid::block_io(int32_t b, void* host, size_t bytes, bool to_host) {
     if (b < 0 || b >= (int32_t)plan.chares.size()) return fail(OD_EINVAL, "block index out of range");
     const BlockDev& B = blocks_h[(size_t)b];
     const size_t row = (size_t)B.ex * s, need = row * B.ey * B.ez;
     if (bytes < need) return fail(OD_EINVAL, "buffer of " + std::to_string(bytes) + " bytes, need " + std::to_string(need));
     hipError_t e = hipSuccess;
+    // a small block comes with the error word in one launch (see kSmallBlock)
+    const size_t at_err = align_up(need, 16), one = at_err + 16;
+    if (to_host && need <= kSmallBlock && (!pinned_borrowed || pinned_bytes >= one)) {
+        od_status os = ensure_pinned(one);
+        if (os != OD_OK) return os;
+        char* pin = static_cast<char*>(pinned);
+        const int32_t cells[3] = {B.ex, B.ey, B.ez};
+        e = launch_read_block(s, st, base + (size_t)(parity ? B.off[1] : B.off[0]) * s, cells, B.py, B.pz, pin,
+                              reinterpret_cast<const unsigned int*>(cp(L.err)),
+                              reinterpret_cast<unsigned int*>(pin + at_err));
+        if (e == hipSuccess) e = hipStreamSynchronize(st);
+        if (e != hipSuccess) return fail(OD_EHIP, std::string("read block: ") + hipGetErrorString(e));
+        unsigned int err;
+        std::memcpy(&err, pin + at_err, 4);
+        od_status es = error_status(err);
+        if (es == OD_OK) std::memcpy(host, pin, need);
+        return es;
+    }
     if (to_host) {
         od_status es = device_error();
         if (es != OD_OK) return es;

@@ -22,3 +22,17 @@ def test_read_returns_what_was_written(n, odf, dtype):
         g.write(U)
         for _ in range(2):
             assert np.array_equal(g.read(), U)
+
+
+# Blocks on both sides of the size (1 MiB) up to which a block is read in one
+# launch, rows that fill no vector among them.
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("n", [1, 5, 50, 51, 64, 65])
+def test_read_block_is_the_fields(n, dtype):
+    g = od.Grid(n, odf=1, dtype=dtype, exec="fused", seed=3)
+    try:
+        g.iterate(3)
+        assert np.array_equal(g.read_block(0), g.read()[1:-1, 1:-1, 1:-1])
+    finally:
+        g.close()
