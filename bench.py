@@ -2,8 +2,9 @@
 
 Headline workload (one "step" = one pass of the whole hot path): a 512^3
 fp64 interior split into 4096 chares of 32^3, 200 Jacobi iterations with the
-halo exchange fused into the sweep, graph-captured, autotuned tile, residual
-of the last sweep read back.  value = GLUP/s (10^9 lattice-site updates/s).
+halo exchange fused into the sweep, graph-captured, four iterations per pass
+over memory (or two on an autotuned tile where that is quicker), residual of
+the last sweep read back.  value = GLUP/s (10^9 lattice-site updates/s).
 
 Prints ONE JSON line: the headline, the roofline of the sweep kernel (its
 average launch time measured live with HIP events on the grid's stream),
@@ -48,11 +49,19 @@ def log(*a):
     print(*a, file=sys.stderr, flush=True)
 
 
-def kernel_source_hash() -> str:
-    """Hash of the fused sweeps' source: the prefetch-depth and halo-load
-    settings and everything from the tile geometry to the end of k_sweep2
-    (edits elsewhere in kernels.hip leave measured traffic valid)."""
-    with open(os.path.join(ROOT, "paper_2605_12734_amd", "csrc", "kernels.hip")) as f:
+def kernel_source_hash(steps: int = 2) -> str:
+    """Hash of the fused sweeps' source.  Passes of one or two steps: the
+    prefetch-depth and halo-load settings and everything from the tile
+    geometry to the end of k_sweep2 (edits elsewhere in kernels.hip leave
+    measured traffic valid); passes of four: the pass and its boxes."""
+    csrc = os.path.join(ROOT, "paper_2605_12734_amd", "csrc")
+    if steps == 4:
+        h = hashlib.sha256()
+        for name in ("deep_dev.hpp", "deep.hip"):
+            with open(os.path.join(csrc, name), "rb") as f:
+                h.update(f.read())
+        return h.hexdigest()[:16]
+    with open(os.path.join(csrc, "kernels.hip")) as f:
         src = f.read()
     a = src.index("#ifndef OD_PREFETCH")
     b = src.index("namespace od {", a)
@@ -76,7 +85,7 @@ KERNEL_OF_EXEC = {
 }
 
 
-def load_traffic(key: str):
+def load_traffic(key: str, steps: int = 2):
     """HBM bytes per sweep launch from the committed rocprofv3 counter runs,
     if they were taken on the current kernel source; else None."""
     path = os.path.join(ROOT, "profiles", "sweep_traffic.json")
@@ -85,7 +94,7 @@ def load_traffic(key: str):
     except (OSError, ValueError):
         return None
     e = d.get(key)
-    if not e or e.get("kernel_hash") != kernel_source_hash():
+    if not e or e.get("kernel_hash") != kernel_source_hash(steps):
         return None
     return e.get("bytes_per_launch")
 
@@ -393,7 +402,7 @@ def jacobi2d_leg(n=32768, iters=100, odfs=(1, 4, 16, 64, 256, 1024)):
             t.close()
         row = {"n": n, "odf": odf, "tile": list(tile)}
         for exec_, it, steps in (("graph", iters, 2), ("per_chare", 10 if odf <= 64 else 4, 1)):
-            g = od.Grid2D(n, odf=odf, dtype="f64", exec=exec_, tile=tile, hints=1)
+            g = od.Grid2D(n, odf=odf, dtype="f64", exec=exec_, tile=tile if exec_ == "per_chare" else None, hints=1)
             try:
                 plan = grid_plan(g)
                 tm = timed(g, it, steps, 1)
@@ -593,11 +602,11 @@ def main():
         log("bench: ceilings", ceil)
 
     k = round(plan["nchares"] ** (1 / 3))
-    workload = (f"{args.n}^3 {args.dtype} odf{plan['nchares']} tile{'x'.join(map(str, plan['tile']))} "
-                f"hints{args.hints} steps{spp}")
+    shape = "boxes" if spp == 4 else "tile" + "x".join(map(str, plan["tile"]))
+    workload = f"{args.n}^3 {args.dtype} odf{plan['nchares']} {shape} hints{args.hints} steps{spp}"
     roof = {"bound": "hbm", "achieved": round(achieved, 1), "peak": PEAK_HBM_GBPS, "unit": "GB/s",
             "frac": round(achieved / PEAK_HBM_GBPS, 4),
-            "traffic": load_traffic(workload) if args.exec in ("graph", "fused") else None,
+            "traffic": load_traffic(workload, spp) if args.exec in ("graph", "fused") else None,
             "kernel": ("k_deep (four 7-point steps per pass over boxes of the whole grid)" if spp == 4
                        else ("k_persistent2 (every pass of two fused 7-point steps in one cooperative launch; "
                         "time per pass)" if args.exec == "persistent"
