@@ -83,15 +83,21 @@ struct Sixth<float> {
 __device__ __forceinline__ double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
 __device__ __forceinline__ float fma_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 // Smallest of m, |a| and |b| in one instruction; doubles by their high words,
-// which order like the doubles when read as floats.  A NaN (a float's, or the
-// high word of a double from 2^1017 on) may make the result NaN.
+// which order like the doubles when read as floats.  The high word of a double
+// from 2^1017 on reads as a NaN, signalling up to 2^1021: v_min3 would make that
+// a quiet one and then drop it with the value beside it, however small that is,
+// so doubles take v_minimum3, whose result stays a NaN (and the wave divides).
+// Sums of floats hold quiet NaNs only, which v_min3 leaves out.
 __device__ __forceinline__ float min3_abs(float m, float a, float b) {
     float r;
     asm("v_min3_f32 %0, |%1|, |%2|, %3" : "=v"(r) : "v"(a), "v"(b), "v"(m));
     return r;
 }
 __device__ __forceinline__ float min3_abs(float m, double a, double b) {
-    return min3_abs(m, __int_as_float(__double2hiint(a)), __int_as_float(__double2hiint(b)));
+    float r;
+    asm("v_minimum3_f32 %0, |%1|, |%2|, %3"
+        : "=v"(r) : "v"(__int_as_float(__double2hiint(a))), "v"(__int_as_float(__double2hiint(b))), "v"(m));
+    return r;
 }
 // larger of m and |v| (a NaN v leaves m)
 __device__ __forceinline__ double max_abs(double m, double v) { return __builtin_fmax(m, __builtin_fabs(v)); }

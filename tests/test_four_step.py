@@ -186,6 +186,33 @@ def test_values_the_division_and_the_boundary_can_go_wrong_on(dtype, field):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("scale", [1018, 1016, 1020])
+def test_sums_below_the_quick_division_beside_huge_ones(scale):
+    # odd in x about a plane of nearly subnormal values: in that plane the huge
+    # x neighbours cancel, so each small sum stays beside one of 2^1017 and more,
+    # whose high word reads as a signalling NaN
+    n, c = (65, 64, 12), 33
+    rng = np.random.default_rng(3)
+    U = np.zeros((n[2] + 2, n[1] + 2, n[0] + 2))
+    for d in range(1, 34):
+        U[:, :, c + d] = 2.0 ** scale * (1 + rng.random(U.shape[:2]) / 8)
+        U[:, :, c - d] = -U[:, :, c + d]
+    U[:, :, c] = (rng.random(U.shape[:2]) - 0.3) * 2.0 ** -1018
+    for a in (0, 1, 2):   # shell edges and corners read back as 0
+        for b in range(a):
+            for i in (0, -1):
+                for j in (0, -1):
+                    at = [slice(None)] * 3
+                    at[a], at[b] = i, j
+                    U[tuple(at)] = 0
+    want, _, r = oracle.jacobi(U.copy(), 8)
+    assert 0 < np.abs(want[1:-1, 1:-1, c]).max() < 2.0 ** -1016
+    got, gr = _run(n, 1, "f64", [8], write=U)
+    _same(got, want)
+    assert gr == r
+
+
+@pytest.mark.gpu
 def test_a_workspace_of_the_pairs_size_runs_pairs():
     import ctypes
 
