@@ -149,7 +149,7 @@ struct SavedState {
     std::vector<char> ctrl;
     size_t fbytes = 0;
     int64_t iters = 0, flips = 0;
-    int parity = 0;
+    int parity = 0, msg_counters = 0;
     bool msg_final = false;
 };
 
@@ -166,6 +166,7 @@ static od_status save_state(Grid& G, SavedState& S) {
     S.iters = G.iters;
     S.flips = G.flips;
     S.parity = G.parity;
+    S.msg_counters = G.msg_counters;   // which of the saved step counters are current
     S.msg_final = G.msg_final;
     return OD_OK;
 }
@@ -177,6 +178,7 @@ static hipError_t restore_state(Grid& G, const SavedState& S) {
     G.iters = S.iters;
     G.flips = S.flips;
     G.parity = S.parity;
+    G.msg_counters = S.msg_counters;
     G.msg_final = S.msg_final;
     return he;
 }

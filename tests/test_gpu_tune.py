@@ -49,6 +49,22 @@ def test_msgdriven_autotune_restores_state(dtype, n, odf):
         g.close()
 
 
+@pytest.mark.parametrize("before", [4, 5])
+@pytest.mark.parametrize("after", [1, 2, 3, 4, 7])
+def test_msgdriven_autotune_between_boxes_and_tiles(before, after):
+    # 4 iterations leave the step counters of the boxes current, 5 those of
+    # the tiles; what follows starts with either.  (a size of its own for each:
+    # tuned sizes are kept in the process)
+    n = (64, 40 + 8 * after, 24 + 8 * before)
+    g = od.Grid(n, odf=8, dtype="f64", exec="msgdriven", hints=1)
+    try:
+        g.iterate(before)
+        g.autotune(1)
+        _check(n, "f64", g, before, after)
+    finally:
+        g.close()
+
+
 @pytest.mark.parametrize("claim", [64, 128])
 @pytest.mark.parametrize("pub", [512, 1024])
 def test_msgdriven_forced_schedules(claim, pub):
