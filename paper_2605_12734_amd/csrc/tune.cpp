@@ -142,6 +142,10 @@ static void apply_schedule(Grid& G, int32_t sched, int32_t waves) {
     G.persist_waves = waves;
 }
 
+static int32_t schedule_of(const Grid& G) {
+    return G.cfg.exec == OD_MSGDRIVEN ? G.msg_sched : G.persist_sched | (G.deep_off ? kNoDeep : 0);
+}
+
 // The grid's whole device state (field storage and control regions) and
 // its iteration state, kept in host memory while tuning candidates run real
 // iterations on the grid, then put back.
@@ -254,9 +258,20 @@ static od_status tune(Grid& G, int32_t iters, int32_t out_tile[3]) {
         auto it = g_cache.find(key);
         if (it != g_cache.end()) {
             const std::array<int32_t, 5> c = it->second;
+            const bool coop = G.cfg.exec == OD_PERSISTENT || G.cfg.exec == OD_MSGDRIVEN;
+            const int32_t old_sched = schedule_of(G), old_waves = G.persist_waves;
             apply_schedule(G, c[3], c[4]);
             od_status s = G.cfg.exec == OD_MSGDRIVEN ? G.setup_cooperative(false) : G.retile(c.data());
-            if (s == OD_OK && out_tile)
+            if (s != OD_OK) {
+                // an entry that this grid cannot take (a tile that is not compiled,
+                // more tiles than it has room for) changes nothing: captured
+                // graphs, for one, are of the passes of the old schedule
+                const std::string why = g_last_error;
+                apply_schedule(G, old_sched, old_waves);
+                if (coop) G.setup_cooperative(false);
+                return fail(s, why);
+            }
+            if (out_tile)
                 for (int d = 0; d < 3; ++d) out_tile[d] = G.plan.tile[d];
             return s;
         }
@@ -311,7 +326,7 @@ static od_status tune(Grid& G, int32_t iters, int32_t out_tile[3]) {
     if (he != hipSuccess) return fail(OD_EHIP, std::string("event: ") + hipGetErrorString(he));
     od_status st = OD_OK;
     const int32_t start_tile[3] = {G.plan.tile[0], G.plan.tile[1], G.plan.tile[2]};
-    const int32_t start_sched = G.persist_sched, start_waves = G.persist_waves;
+    const int32_t start_sched = schedule_of(G), start_waves = G.persist_waves;
     float best_ms = 1e30f;
     std::array<int32_t, 5> best = {start_tile[0], start_tile[1], start_tile[2], start_sched, start_waves};
     st = OD_OK;
