@@ -213,10 +213,10 @@ std::vector<int32_t> deep_tables(const Plan& p, const DeepPlan& d, size_t at[5])
         }
     }
     at[4] = tab.size();
-    for (int64_t v = 0; v < p.n[2]; ++v) {
-        int64_t q = v + 1;
-        while (q < p.n[2] && tab[at[3] + (size_t)q] == tab[at[3] + (size_t)v]) ++q;
-        tab.push_back((int32_t)q);
+    tab.resize(at[4] + (size_t)p.n[2]);
+    for (int64_t v = p.n[2] - 1; v >= 0; --v) {
+        const bool same = v + 1 < p.n[2] && tab[at[3] + (size_t)v + 1] == tab[at[3] + (size_t)v];
+        tab[at[4] + (size_t)v] = same ? tab[at[4] + (size_t)v + 1] : (int32_t)(v + 1);
     }
     return tab;
 }

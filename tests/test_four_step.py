@@ -3,6 +3,8 @@
 The pass cuts the whole grid into boxes of 64 x 64 lanes that cross chares;
 each computes a ring of four cells more than it writes, except at the grid's
 faces.  Everything is compared with the CPU oracle bit for bit."""
+import time
+
 import numpy as np
 import pytest
 
@@ -210,6 +212,22 @@ def test_sums_below_the_quick_division_beside_huge_ones(scale):
     got, gr = _run(n, 1, "f64", [8], write=U)
     _same(got, want)
     assert gr == r
+
+
+@pytest.mark.gpu
+def test_a_long_axis_does_not_make_creation_long():
+    # the table of planes behind a chare's: quadratic work on it took 0.36 s for a
+    # chare of 60000 planes, so 16 s here, what is linear takes hundredths
+    n = (8, 8, 400000)
+    t0 = time.monotonic()
+    g = od.Grid(n, odf=1, dtype="f64", exec="fused", bc=BC6, seed=5)
+    took = time.monotonic() - t0
+    try:
+        assert took < 5, took
+        g.iterate(8)
+        _same(g.read(), oracle.solve(n, np.float64, seed=5, iters=8, bc=BC6)[0])
+    finally:
+        g.close()
 
 
 @pytest.mark.gpu
