@@ -1,72 +1,61 @@
 """Tuning results kept in a file (OD_TUNE_CACHE): what a grid does with entries
-it can take and with entries it cannot.  The file is read once per process, so
-each step is a process of its own; the entries under test are those a first
-process wrote, changed here."""
+it can take and with entries it cannot.  The library reads the file at the
+process's first od_autotune, so the entries are written here when the tests are
+collected; each is of a grid size that no other test tunes."""
+import atexit
 import os
-import subprocess
-import sys
+import tempfile
 
+import numpy as np
 import pytest
+
+import oracle
+import paper_2605_12734_amd as od
 
 pytestmark = pytest.mark.gpu
 
-ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 NO_BOXES = 16   # in the schedule column: tiles were quicker than passes over boxes
-HEAD = """
-import numpy as np
-import oracle
-import paper_2605_12734_amd as od
-N = (96, 64, 40)
-def grid(exec_, **kw):
-    return od.Grid(N, odf=8, dtype="f64", exec=exec_, hints=1, seed=3, **kw)
-def check(g, iters):
-    want, _, r = oracle.solve(N, np.float64, seed=3, iters=iters)
+REFUSED = (104, 64, 40)
+
+
+def _key(n, exec_):
+    """The key of a grid of n, 8 chares, fp64, hints bit 0."""
+    cfg, _keep = od.make_config(n=n, odf=8, dtype="f64", exec=exec_, hints=1)
+    half = "x".join(str(v // 2) for v in n)
+    return f"s8/e{cfg.exec}/n{n[0]}x{n[1]}x{n[2]}/{half}:8/h0/i0x0"
+
+
+def _grid(n, exec_):
+    return od.Grid(n, odf=8, dtype="f64", exec=exec_, hints=1, seed=3)
+
+
+def _check(g, n, iters):
+    want, _, r = oracle.solve(n, np.float64, seed=3, iters=iters)
     assert g.iterations() == iters and g.residual() == r
     assert np.array_equal(g.read(), want)
-"""
 
 
-def _child(cache, body):
-    p = subprocess.run([sys.executable, "-c", HEAD + body], cwd=ROOT, timeout=100, capture_output=True, text=True,
-                       env=dict(os.environ, OD_TUNE_CACHE=str(cache)))
-    assert p.returncode == 0, p.stdout + p.stderr
+if "OD_TUNE_CACHE" not in os.environ:
+    _fd, _path = tempfile.mkstemp(prefix="od_tune_")
+    with os.fdopen(_fd, "w") as _f:
+        for _e in ("fused", "graph", "persistent"):
+            _f.write(f"{_key(REFUSED, _e)} 7 7 7 {NO_BOXES | (1 if _e == 'persistent' else 0)} 0\n")   # no such tile
+    os.environ["OD_TUNE_CACHE"] = _path
+    atexit.register(os.unlink, _path)
 
 
-def _entries(cache, execs):
-    """One entry for each form, as a process that tunes writes them."""
-    _child(cache, f"""
-for e in {execs!r}:
-    g = grid(e)
-    g.autotune(1)
-    g.close()
-""")
-    rows = [ln.split() for ln in cache.read_text().splitlines()]
-    assert len(rows) == len(execs)
-    return rows
-
-
-def test_an_entry_that_cannot_be_applied_changes_nothing(tmp_path):
-    cache = tmp_path / "tune"
-    rows = _entries(cache, ["fused", "graph", "persistent"])
-    for r in rows:
-        r[1:4] = ["7", "7", "7"]   # not a compiled tile
-        r[4] = str(int(r[4]) | NO_BOXES)
-    cache.write_text("".join(" ".join(r) + "\n" for r in rows))
-    _child(cache, """
-for e in ("fused", "graph", "persistent"):
-    g = grid(e)
-    before = g.plan()
-    g.iterate(4)
-    g.iterate(4)   # (a graph for either parity)
+@pytest.mark.parametrize("exec_", ["fused", "graph", "persistent"])
+def test_an_entry_that_cannot_be_applied_changes_nothing(exec_):
+    g = _grid(REFUSED, exec_)
     try:
-        g.autotune(1)
-    except Exception as ex:
-        assert "compiled variant" in str(ex), ex
-    else:
-        raise AssertionError("a tile that is not compiled was taken")
-    assert g.pass_info()["steps"] == 4 and g.plan() == before
-    g.iterate(4)
-    g.iterate(3)
-    check(g, 15)
-    g.close()
-""")
+        before = g.plan()
+        g.iterate(4)
+        g.iterate(4)   # (a graph for either parity)
+        with pytest.raises(Exception, match="compiled variant"):
+            g.autotune(1)
+        assert g.pass_info()["steps"] == 4 and g.plan() == before
+        g.iterate(4)
+        g.iterate(3)
+        _check(g, REFUSED, 15)
+    finally:
+        g.close()
