@@ -12,14 +12,23 @@ namespace od {
 
 namespace {
 
-// A plane iteration of a full chip, in units of 50 ns: measured over cubes from
+// A plane iteration of a full chip, in units of 10 ns: measured over cubes from
 // 64^3 to 512^3 as 2.5 (four rows) and 1.55 us (one) in fp64, 3.2 and 1.65 us in
 // fp32, whose CUs hold twice the workgroups.  us per iteration with four / one
 // rows: fp64 64^3 7.4 / 5.1, 128^3 9.9 / 9.0, 160^3 10.5 / 11.6, 256^3 22.6 / 34.7;
 // fp32 64^3 6.4 / 3.6, 192^3 11.1 / 10.5, 224^3 11.8 / 13.0, 512^3 89 / 115.
 int64_t plane_cost(int dtype_bytes, int rows) {
-    return dtype_bytes == 8 ? (rows == 1 ? 31 : 50) : (rows == 1 ? 33 : 65);
+    return dtype_bytes == 8 ? (rows == 1 ? 155 : 250) : (rows == 1 ? 165 : 325);
 }
+
+// What a task of the message-driven scheduler adds to its pass, in the same
+// units: queueing it and counting its finish for up to 26 others goes through
+// few words per XCD.  us per iteration with 0 / 1 / 2 / 3: fp32 300 x 300 x 4 11.9 /
+// 7.0 / 5.1 / 5.1 (888 to 222 boxes; pairs 8.0), 250 x 250 x 12 13.7 / 10.8 / 8.5 / 7.3
+// (pairs 11.8), 128^3 14.2 / 14.2 / 12.2 / 11.6, 64^3 7.3 / 5.7 / 5.7 / 5.6, 400 x 400
+// x 20 12.8 / 12.6 / 13.6 / 13.4; fp64 64^3 7.6 / 6.0 / 6.1 / 5.9, 300 x 300 x 16 10.4 /
+// 10.5 / 11.0 / 11.0, 96^3 9.0 / 9.2 / 8.9 / 9.5, 512^3 the same boxes.
+constexpr int64_t kTaskCost = 2;
 
 template <typename T, int R, bool RAG>
 __global__ void __launch_bounds__(deep_waves((int)sizeof(T)) * 64) OD_DEEP_OCC(R)
@@ -127,7 +136,7 @@ std::vector<DeepTile> xcd_runs(const std::vector<DeepTile>& list) {
 
 namespace {
 
-DeepPlan plan_boxes(const Plan& p, int dtype_bytes, bool serve) {
+DeepPlan plan_boxes(const Plan& p, int dtype_bytes, bool serve, bool tasks) {
     DeepPlan out;
     const int32_t VX = 16 / dtype_bytes;
     if (p.multires || p.chares.empty()) return out;
@@ -173,7 +182,8 @@ DeepPlan plan_boxes(const Plan& p, int dtype_bytes, bool serve) {
         for (int64_t k = 1; k <= p.n[2] && (!serve || xy * k <= kServeBoxes); ++k) {
             const int64_t len = (p.n[2] + k - 1) / k;
             if (serve && k > 1 && len < kServePlanes) break;
-            const int64_t cost = ((xy * k + slots - 1) / slots) * (len + 2 * kDeepSteps) * plane_cost(dtype_bytes, rows);
+            const int64_t cost = ((xy * k + slots - 1) / slots) * (len + 2 * kDeepSteps) * plane_cost(dtype_bytes, rows) +
+                                 (tasks ? xy * k * kTaskCost : 0);
             if (cost < best) {
                 best = cost;
                 zc = k;
@@ -196,8 +206,8 @@ DeepPlan plan_boxes(const Plan& p, int dtype_bytes, bool serve) {
 
 }  // namespace
 
-DeepPlan deep_plan(const Plan& p, int dtype_bytes) { return plan_boxes(p, dtype_bytes, false); }
-DeepPlan deep_plan_serve(const Plan& p, int dtype_bytes) { return plan_boxes(p, dtype_bytes, true); }
+DeepPlan deep_plan(const Plan& p, int dtype_bytes, bool tasks) { return plan_boxes(p, dtype_bytes, false, tasks); }
+DeepPlan deep_plan_serve(const Plan& p, int dtype_bytes) { return plan_boxes(p, dtype_bytes, true, false); }
 
 std::vector<int32_t> deep_tables(const Plan& p, const DeepPlan& d, size_t at[5]) {
     std::vector<int32_t> tab(d.vx);

@@ -50,7 +50,8 @@ struct DeepPlan {
 
 // Lane coverage: LX vectors of 16 bytes by EY rows.
 void deep_shape(int dtype_bytes, const DeepPlan& d, int* lx, int* ey);
-DeepPlan deep_plan(const Plan& p, int dtype_bytes);
+// tasks: the boxes are tasks of the message-driven scheduler.
+DeepPlan deep_plan(const Plan& p, int dtype_bytes, bool tasks);
 // The boxes of a served solve: workgroups of kServeWaves waves in either type,
 // at most kServeBoxes of them (a slot's dependency lists hold 26 for each).
 constexpr int kServeWaves = 8, kServeBoxes = 2048;

@@ -38,6 +38,23 @@ def test_boxes_write_each_cell_once_and_keep_their_ring(dtype, n, odf):
     assert (seen == 1).all()
 
 
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("n", [(300, 300, 4), (250, 250, 12), (100, 100, 30), (64, 64, 64), (225, 391, 6)])
+def test_boxes_of_message_driven_tasks(dtype, n):
+    # a task costs more than its planes: fewer boxes of more planes where a pass
+    # launched by itself takes as many as the chip holds; each cell once as ever
+    one = od.host_plan(n=n, odf=1, dtype=dtype, exec="fused")["pass"]
+    p = od.host_plan(n=n, odf=1, dtype=dtype, exec="msgdriven")["pass"]
+    assert p["steps"] == 4 and len(p["boxes"]) <= len(one["boxes"])
+    assert dtype == "f64" or len(p["boxes"]) <= 512 < len(one["boxes"]) or n == (64, 64, 64)
+    seen = np.zeros((n[2], n[1], n[0]), dtype=np.int8)
+    for cx0, cx1, cy0, cy1, x0, x1, y0, y1, z0, z1 in p["boxes"]:
+        assert (cx0 == 0 or x0 - cx0 >= RING) and (cx1 == n[0] or cx1 - x1 >= RING)
+        assert (cy0 == 0 or y0 - cy0 >= RING) and (cy1 == n[1] or cy1 - y1 >= RING)
+        seen[z0:z1, y0:y1, x0:x1] += 1
+    assert (seen == 1).all()
+
+
 @pytest.mark.parametrize("kw,steps", [
     (dict(n=64), 4), (dict(n=(5, 3, 2), odf=1), 4), (dict(n=(65, 64, 8)), 4), (dict(n=(66, 64, 64), dtype="f32"), 4),
     (dict(n=64, exec="fused"), 4), (dict(n=64, exec="persistent"), 4), (dict(n=64, exec="msgdriven"), 4),
