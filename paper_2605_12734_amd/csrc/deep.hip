@@ -23,12 +23,13 @@ int64_t plane_cost(int dtype_bytes, int rows) {
 
 // What a task of the message-driven scheduler adds to its pass, in the same
 // units: queueing it and counting its finish for up to 26 others goes through
-// few words per XCD.  us per iteration with 0 / 1 / 2 / 3: fp32 300 x 300 x 4 11.9 /
-// 7.0 / 5.1 / 5.1 (888 to 222 boxes; pairs 8.0), 250 x 250 x 12 13.7 / 10.8 / 8.5 / 7.3
-// (pairs 11.8), 128^3 14.2 / 14.2 / 12.2 / 11.6, 64^3 7.3 / 5.7 / 5.7 / 5.6, 400 x 400
-// x 20 12.8 / 12.6 / 13.6 / 13.4; fp64 64^3 7.6 / 6.0 / 6.1 / 5.9, 300 x 300 x 16 10.4 /
-// 10.5 / 11.0 / 11.0, 96^3 9.0 / 9.2 / 8.9 / 9.5, 512^3 the same boxes.
-constexpr int64_t kTaskCost = 2;
+// few words per XCD; and a box of four rows a strip starts more slowly.  us per
+// iteration with nothing added and so: fp32 300 x 300 x 4 11.8 / 5.2 (888 and 222
+// boxes; pairs 8.1), 250 x 250 x 12 13.9 / 8.6 (pairs 11.9), 225 x 391 x 6 9.3 / 7.5
+// (pairs 8.3), 128^3 14.0 / 12.2, 64^3 7.1 / 5.7; fp64 64^3 7.7 / 6.0, 512^3 the same
+// boxes.  Twice as much in fp64 took 237 x 747 x 6 from 11.2 to 14.3.
+int64_t task_cost(int dtype_bytes) { return dtype_bytes == 8 ? 1 : 2; }
+constexpr int64_t kTaskRows = 600;
 
 template <typename T, int R, bool RAG>
 __global__ void __launch_bounds__(deep_waves((int)sizeof(T)) * 64) OD_DEEP_OCC(R)
@@ -183,7 +184,7 @@ DeepPlan plan_boxes(const Plan& p, int dtype_bytes, bool serve, bool tasks) {
             const int64_t len = (p.n[2] + k - 1) / k;
             if (serve && k > 1 && len < kServePlanes) break;
             const int64_t cost = ((xy * k + slots - 1) / slots) * (len + 2 * kDeepSteps) * plane_cost(dtype_bytes, rows) +
-                                 (tasks ? xy * k * kTaskCost : 0);
+                                 (tasks ? xy * k * task_cost(dtype_bytes) + (rows > 1 ? kTaskRows : 0) : 0);
             if (cost < best) {
                 best = cost;
                 zc = k;
