@@ -163,7 +163,8 @@ typedef struct {
      * caller (and in the cooperative forms without imbalance, OD_PERSISTENT
      * without a schedule forced by bits 4, 5, 11 or 13), run groups of four
      * iterations as one pass over boxes of the whole grid (od_pass_info;
-     * od_autotune may find a thin grid's tiles quicker and keep them); the
+     * large grids only a few cells thick, whose boxes would be mostly idle,
+     * do not, and od_autotune may find a tuned tile quicker and keep it); the
      * values are again the same, and what is left over of a count runs as
      * pairs and a single sweep.  Grids of the 2D stencil run groups of eight
      * (OD_FUSED, OD_GRAPH).

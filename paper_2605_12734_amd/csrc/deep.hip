@@ -137,7 +137,7 @@ std::vector<DeepTile> xcd_runs(const std::vector<DeepTile>& list) {
 
 namespace {
 
-DeepPlan plan_boxes(const Plan& p, int dtype_bytes, bool serve, bool tasks) {
+DeepPlan plan_boxes(const Plan& p, int dtype_bytes, bool serve, bool tasks, int64_t* pass_cost) {
     DeepPlan out;
     const int32_t VX = 16 / dtype_bytes;
     if (p.multires || p.chares.empty()) return out;
@@ -202,13 +202,53 @@ DeepPlan plan_boxes(const Plan& p, int dtype_bytes, bool serve, bool tasks) {
                 list.push_back({a.start, b.start, a.o0, a.o1, b.o0, b.o1, (int32_t)(p.n[2] * k / zc),
                                 (int32_t)(p.n[2] * (k + 1) / zc)});
     d.tiles = xcd_runs(list);
+    if (pass_cost) *pass_cost = best;
     return d;
+}
+
+// Thin grids, whose boxes are mostly lanes outside the grid (three quarters at
+// least): four steps by passes of the planned tiles, `steps` steps a pass, are
+// estimated to take no longer than a pass over the boxes (`cost`, in units of
+// 10 ns).  A tile's march of tz planes takes lat * (tz + 2) and a start-up; a full
+// chip's tiles go through at `rate` per plane, start-up counted as ten planes,
+// more the more of a tile's row is cells (measured over 1 to 8000 cells an axis).
+// us per iteration by boxes / by tiles, fused: fp64 (1,2000,2000) 223 / 170,
+// (16,2000,2000) 195 / 184 but (32,2000,2000) 195 / 230 and (8,300,300) 12.2 / 17.4;
+// (8000,1,8000) 716 / 415 but (1000,1,1000) 18 / 52, whose 64 tiles leave most of the
+// chip idle; (1,1,100000) 85 / 67; fp32 (8000,1,8000) 397 / 212, (4,8000,2000)
+// 423 / 384.  Of 600 random grids with an axis of 1 to 40, in all forms, boxes cost
+// 13 more than 5 % and half a microsecond without the rule, 1 with it.
+bool tiles_quicker(const Plan& p, int dtype_bytes, const DeepPlan& d, int64_t cost, od_exec exec, int steps) {
+    int lx, ey;
+    deep_shape(dtype_bytes, d, &lx, &ey);
+    if (cost < 4000) return false;   // 40 us a pass: either is mostly start-up
+    if (4 * std::min<int64_t>(p.n[0], kEX) * std::min<int64_t>(p.n[1], ey) > (int64_t)kEX * ey) return false;
+    int32_t ex = 1, ez = 1;
+    for (const Chare& c : p.chares) {
+        ex = std::max(ex, c.e[0]);
+        ez = std::max(ez, c.e[2]);
+    }
+    const double f = std::min(1.0, (double)ex / p.tile[0]), tz = std::min(p.tile[2], ez), n = (double)p.tiles.size() / 256;
+    const bool f64 = dtype_bytes == 8, row = p.tile[1] == 1;
+    const double lat = row ? (f64 ? 0.8 : 1.13) * (tz + 6) : 4.8 + (f64 ? 1.0 : 1.25) * (tz + 2);
+    const double rate = row ? (f64 ? 0.15 + 0.33 * f : 0.19 + 0.18 * f) : (f64 ? 0.24 + 0.11 * f : 0.29 + 0.12 * f);
+    // (the cooperative forms' barrier or queue, per pass over the tiles)
+    const double coop = row ? (exec == OD_FUSED || exec == OD_GRAPH ? 1.0 : 1.08)
+                            : (exec == OD_PERSISTENT ? 1.13 : (exec == OD_MSGDRIVEN ? (f64 ? 1.3 : 1.5) : 1.0));
+    // (rows of one cache line or less: the boxes were 5-25 % over the estimate)
+    const double boxes = (double)cost * (p.n[0] * dtype_bytes <= 64 ? 1.1 : 1.0);
+    return 100.0 * kDeepSteps / steps * coop * std::max(lat, n * (tz + 10) * rate) <= boxes;
 }
 
 }  // namespace
 
-DeepPlan deep_plan(const Plan& p, int dtype_bytes, bool tasks) { return plan_boxes(p, dtype_bytes, false, tasks); }
-DeepPlan deep_plan_serve(const Plan& p, int dtype_bytes) { return plan_boxes(p, dtype_bytes, true, false); }
+DeepPlan deep_plan(const Plan& p, int dtype_bytes, od_exec exec, int tile_steps) {
+    int64_t cost = 0;
+    DeepPlan d = plan_boxes(p, dtype_bytes, false, exec == OD_MSGDRIVEN, &cost);
+    if (!d.tiles.empty() && tiles_quicker(p, dtype_bytes, d, cost, exec, tile_steps)) d.tiles.clear();
+    return d;
+}
+DeepPlan deep_plan_serve(const Plan& p, int dtype_bytes) { return plan_boxes(p, dtype_bytes, true, false, nullptr); }
 
 std::vector<int32_t> deep_tables(const Plan& p, const DeepPlan& d, size_t at[5]) {
     std::vector<int32_t> tab(d.vx);

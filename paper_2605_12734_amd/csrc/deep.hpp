@@ -50,8 +50,9 @@ struct DeepPlan {
 
 // Lane coverage: LX vectors of 16 bytes by EY rows.
 void deep_shape(int dtype_bytes, const DeepPlan& d, int* lx, int* ey);
-// tasks: the boxes are tasks of the message-driven scheduler.
-DeepPlan deep_plan(const Plan& p, int dtype_bytes, bool tasks);
+// Boxes for a grid of that form, whose passes by tiles are of tile_steps steps;
+// none where the planned tiles are estimated to be quicker.
+DeepPlan deep_plan(const Plan& p, int dtype_bytes, od_exec exec, int tile_steps);
 // The boxes of a served solve: workgroups of kServeWaves waves in either type,
 // at most kServeBoxes of them (a slot's dependency lists hold 26 for each).
 constexpr int kServeWaves = 8, kServeBoxes = 2048;

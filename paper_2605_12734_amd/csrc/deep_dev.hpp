@@ -35,8 +35,9 @@
 // Measured, us per iteration, this pass against pairs at the default tile:
 // 512^3 fp64 ODF 4096 153 / 270, fp32 76 / 156; 256^3 fp64 22.6 / 39.3; 64^3
 // fp64 5.1 / 16.8; 1024^3 fp64 1077 / 2221; 768^3 octree fp64 469 / 1021;
-// 211 x 163 x 157 fp32 in 27 chares, whose rows end inside vectors, 10.1 / 28.  No size
-// tried ran slower: (512,512,16) fp32, the nearest, 9.8 / 11.0.
+// 211 x 163 x 157 fp32 in 27 chares, whose rows end inside vectors, 10.1 / 28.
+// (512,512,16) fp32 9.8 / 11.0.  Thin grids, whose lanes lie mostly outside the
+// grid, can be slower: where that is estimated the grid runs by tiles (deep.hip).
 #pragma once
 
 #include <hip/hip_runtime.h>

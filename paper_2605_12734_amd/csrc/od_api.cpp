@@ -669,8 +669,10 @@ std::string build_layout(const od_config& cfg, Grid& G) {
     // four-step passes, behind everything else (a workspace that ends here
     // runs pairs): boxes, and per axis the tables of DeepMap
     G.deep_plan = DeepPlan{};
-    if (deep_possible(G) && G.L.field_end / 16 <= UINT32_MAX)
-        G.deep_plan = cfg.stencil == 5 ? deep_plan2d(p, s) : od::deep_plan(p, s, cfg.exec == OD_MSGDRIVEN);
+    if (deep_possible(G) && G.L.field_end / 16 <= UINT32_MAX) {
+        const bool pairs = two_step_possible(G) && sweep2_variant_ok(s, p.tile[0], p.tile[1]) && ntiles <= G.tile2_cap;
+        G.deep_plan = cfg.stencil == 5 ? deep_plan2d(p, s) : od::deep_plan(p, s, cfg.exec, pairs ? 2 : 1);
+    }
     if (!G.deep_plan.tiles.empty()) {
         G.L.deep = cv.take(G.deep_plan.tiles.size() * sizeof(DeepTile));
         G.L.deep_tab = cv.take((G.deep_plan.vx.size() + G.deep_plan.vi.size() + (size_t)(p.n[1] + 2 * p.n[2])) * 4);

@@ -75,6 +75,38 @@ def test_which_grids_run_four_steps(kw, steps):
     assert od.host_plan(**kw)["pass"]["steps"] == steps
 
 
+@pytest.mark.parametrize("dtype,exec_,n,odf,steps", [
+    # most of a box's lanes outside the grid and enough tiles to fill the chip
+    ("f64", "fused", (1, 2000, 2000), 1, 2), ("f64", "graph", (4, 8000, 2000), 1, 2), ("f64", "fused", (8, 2000, 2000), 1, 2),
+    ("f64", "persistent", (1, 2000, 2000), 1, 2), ("f64", "msgdriven", (1, 2000, 2000), 1, 2),
+    ("f64", "fused", (8000, 1, 8000), 1, 1), ("f32", "fused", (8000, 1, 8000), 1, 1), ("f64", "fused", (1, 1, 100000), 1, 1),
+    ("f32", "fused", (4, 8000, 2000), 1, 2), ("f64", "fused", (1, 1000, 1000), 8, 2), ("f32", "msgdriven", (100000, 1, 1), 1, 1),
+    # enough cells in the lanes, or too few tiles
+    ("f64", "fused", (32, 2000, 2000), 1, 4), ("f64", "fused", (2000, 2000, 1), 1, 4), ("f64", "fused", (2000, 2, 2000), 1, 4),
+    ("f64", "fused", (8, 300, 300), 1, 4), ("f64", "fused", (300, 1, 300), 1, 4), ("f64", "fused", (1, 300, 300), 1, 4),
+    ("f32", "fused", (2000, 1, 2000), 1, 4), ("f64", "fused", (16, 16, 4096), 1, 4), ("f64", "fused", (4, 1000, 1000), 64, 4),
+    ("f32", "msgdriven", (4, 2000, 2000), 1, 4)])
+def test_thin_grids_run_the_quicker_passes(dtype, exec_, n, odf, steps):
+    assert od.host_plan(n=n, odf=odf, dtype=dtype, exec=exec_)["pass"]["steps"] == steps
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("exec_", ["fused", "graph", "persistent", "msgdriven"])
+@pytest.mark.parametrize("dtype,n", [("f64", (1, 700, 900)), ("f64", (1500, 1, 3000)), ("f32", (3000, 1, 5000))])
+def test_thin_grids(exec_, dtype, n):
+    # whichever passes the rule takes
+    want, _, r = oracle.solve(n, DT[dtype], seed=5, iters=11, bc=BC6)
+    g = od.Grid(n, odf=1, dtype=dtype, exec=exec_, bc=BC6, seed=5, hints=1)
+    try:
+        g.iterate(4)
+        g.iterate(7)
+        U, got = g.read(), g.residual()
+    finally:
+        g.close()
+    _same(U, want)
+    assert got == r
+
+
 def _same(U, want):
     if not np.array_equal(U, want):
         d = np.argwhere(~((U == want) | (np.isnan(U) & np.isnan(want))))
