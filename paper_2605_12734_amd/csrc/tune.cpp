@@ -11,8 +11,8 @@
 // kernel's register limit or one less); message-driven grids keep their
 // tile (the dependency lists are built for it) and time their scheduler
 // choices over real steps.  For both, the grid's state is saved to host
-// memory before the search and restored after it.  Results are cached per (dtype, exec
-// mode, grid and chare-shape histogram) in the process and, if
+// memory before the search and restored after it.  Results are cached per (dtype, stencil,
+// exec mode, grid, boxes and chare-shape histogram) in the process and, if
 // OD_TUNE_CACHE names a file, on disk.
 #include <hip/hip_runtime.h>
 
@@ -46,7 +46,12 @@ std::string signature(const Grid& G) {
     std::map<std::array<int32_t, 3>, int64_t> hist;
     for (const Chare& c : G.plan.chares) hist[{c.e[0], c.e[1], c.e[2]}]++;
     std::ostringstream os;
-    os << "s" << G.s << "/e" << (int)G.cfg.exec << "/n" << G.plan.n[0] << "x" << G.plan.n[1] << "x" << G.plan.n[2];
+    // v2: entries that say whether passes over boxes are quicker than the tile,
+    // so the stencil and the grid's boxes (a caller's tile or a small workspace
+    // leaves none) are part of the key; older files' entries don't match
+    os << "v2/s" << G.s << "/k" << (G.cfg.stencil == 5 ? 5 : 7) << "/e" << (int)G.cfg.exec << "/n" << G.plan.n[0] << "x"
+       << G.plan.n[1] << "x" << G.plan.n[2] << "/b" << (G.deep_plan.tiles.empty() ? 0 : G.deep_steps()) << "x"
+       << G.deep_plan.tiles.size();
     for (const auto& kv : hist) os << "/" << kv.first[0] << "x" << kv.first[1] << "x" << kv.first[2] << ":" << kv.second;
     // message-driven grids tune the scheduler at their own tile; schedule
     // checks and load imbalance change what is timed
