@@ -354,6 +354,20 @@ static od_status tune(Grid& G, int32_t iters, int32_t out_tile[3]) {
             return st;
         }
     }
+    // a candidate with a two-step variant is timed as the grid would run
+    // it (pairs of steps per pass), per step
+    auto launch = [&]() {
+        if (G.two_step)
+            return launch_sweep2(G.s, G.plan.tile[0], G.plan.tile[1], G.st, G.base,
+                                 reinterpret_cast<const BlockDev*>(G.cp(G.L.blocks)),
+                                 reinterpret_cast<const TileDev*>(G.cp(G.L.tiles)),
+                                 reinterpret_cast<const Tile2Dev*>(G.cp(G.L.tiles2)), (int32_t)G.tiles_h.size(),
+                                 G.parity, G.res_ptr(), 0, 1, G.mode(), ImbDev{}, 0);
+        return launch_sweep(G.s, G.plan.tile[0], G.plan.tile[1], G.st, G.base,
+                            reinterpret_cast<const BlockDev*>(G.cp(G.L.blocks)),
+                            reinterpret_cast<const TileDev*>(G.cp(G.L.tiles)), (int32_t)G.tiles_h.size(),
+                            G.parity, G.res_ptr(), 0, 1, ImbDev{}, 0, G.mode(), G.xexp_dev());
+    };
     auto time_it = [&](float* ms_out) -> hipError_t {
         if (pers) {
             od_status ps = G.persistent_run(2);   // warm-up
@@ -366,20 +380,6 @@ static od_status tune(Grid& G, int32_t iters, int32_t out_tile[3]) {
             if (e == hipSuccess && G.device_error() != OD_OK) e = hipErrorLaunchFailure;
             return e;
         }
-        // a candidate with a two-step variant is timed as the grid would run
-        // it (pairs of steps per pass), per step
-        auto launch = [&]() {
-            if (G.two_step)
-                return launch_sweep2(G.s, G.plan.tile[0], G.plan.tile[1], G.st, G.base,
-                                     reinterpret_cast<const BlockDev*>(G.cp(G.L.blocks)),
-                                     reinterpret_cast<const TileDev*>(G.cp(G.L.tiles)),
-                                     reinterpret_cast<const Tile2Dev*>(G.cp(G.L.tiles2)), (int32_t)G.tiles_h.size(),
-                                     G.parity, G.res_ptr(), 0, 1, G.mode(), ImbDev{}, 0);
-            return launch_sweep(G.s, G.plan.tile[0], G.plan.tile[1], G.st, G.base,
-                                reinterpret_cast<const BlockDev*>(G.cp(G.L.blocks)),
-                                reinterpret_cast<const TileDev*>(G.cp(G.L.tiles)), (int32_t)G.tiles_h.size(),
-                                G.parity, G.res_ptr(), 0, 1, ImbDev{}, 0, G.mode(), G.xexp_dev());
-        };
         hipError_t e = launch();   // warm-up
         if (e == hipSuccess) e = hipEventRecord(a, G.st);
         for (int32_t i = 0; i < iters && e == hipSuccess; ++i) e = launch();
@@ -415,30 +415,41 @@ static od_status tune(Grid& G, int32_t iters, int32_t out_tile[3]) {
         }
         if (st != OD_OK) break;
     }
-    // four-step passes against the best tile: thin grids can be quicker by tiles
-    // (fp64 (1,300,300) 10.4 against 13.7 us per iteration, (2000,2000,1) 28.7
-    // against 30.5)
+    // passes over boxes against the best tile: the same iterations on both sides,
+    // in turn, two passes at least (a persistent grid's barriers are part of them)
+    // and half a millisecond of them, the quickest of three
     if (st == OD_OK && !G.deep_plan.tiles.empty()) {
-        const int32_t n = (iters + 1) / 2;   // passes timed
-        float ms = 0;
-        if (pers) {
-            G.tuning = false;
-            st = G.persistent_run(G.deep_steps());
-            he = hipEventRecord(a, G.st);
-            if (st == OD_OK) st = G.persistent_run((int64_t)G.deep_steps() * n);
-            G.tuning = true;
-        } else {
-            st = G.fused_deep_pass(G.st, G.parity);
-            he = hipEventRecord(a, G.st);
-            for (int32_t i = 0; i < n && st == OD_OK; ++i) st = G.fused_deep_pass(G.st, G.parity);
-        }
-        if (he == hipSuccess) he = hipEventRecord(b, G.st);
-        if (he == hipSuccess) he = hipEventSynchronize(b);
-        if (he == hipSuccess) he = hipEventElapsedTime(&ms, a, b);
-        if (st == OD_OK && he == hipSuccess && pers) st = G.device_error();
-        if (st == OD_OK && he != hipSuccess) st = fail(OD_EHIP, std::string("tuning launch: ") + hipGetErrorString(he));
-        // (per iteration: best_ms is `iters` iterations, a persistent one twice that)
-        if (ms / (float)(G.deep_steps() * n) > best_ms / (float)(pers ? 2 * iters : iters)) best[3] |= kNoDeep;
+        best[3] &= kNoDeep - 1;
+        apply_schedule(G, best[3], best[4]);
+        st = G.retile(best.data());
+        int64_t passes = std::max<int64_t>(2, iters), n = passes * G.deep_steps();
+        float least[2] = {1e30f, 1e30f};   // tiles, boxes
+        for (int rep = 0; rep < 4 && st == OD_OK; ++rep)   // (the first is the warm-up)
+            for (int boxes = 0; boxes < 2 && st == OD_OK; ++boxes) {
+                he = hipEventRecord(a, G.st);
+                if (pers) {
+                    G.tuning = boxes == 0;
+                    st = G.persistent_run(n);
+                    G.tuning = true;
+                } else if (boxes) {
+                    for (int64_t i = 0; i < passes && st == OD_OK; ++i) st = G.fused_deep_pass(G.st, G.parity);
+                } else {
+                    for (int64_t i = 0; i < n && he == hipSuccess; i += G.two_step ? 2 : 1) he = launch();
+                }
+                float ms = 0;
+                if (he == hipSuccess) he = hipEventRecord(b, G.st);
+                if (he == hipSuccess) he = hipEventSynchronize(b);
+                if (he == hipSuccess) he = hipEventElapsedTime(&ms, a, b);
+                if (st == OD_OK && he == hipSuccess && pers) st = G.device_error();
+                if (st == OD_OK && he != hipSuccess) st = fail(OD_EHIP, std::string("tuning launch: ") + hipGetErrorString(he));
+                if (rep > 0) {
+                    least[boxes] = std::min(least[boxes], ms);
+                } else if (boxes && st == OD_OK && ms < 0.5f) {
+                    passes = std::min<int64_t>(64, (int64_t)(passes * 0.5f / std::max(ms, 0.005f)) + 1);
+                    n = passes * G.deep_steps();
+                }
+            }
+        if (least[1] > least[0]) best[3] |= kNoDeep;
     }
     hipEventDestroy(a);
     hipEventDestroy(b);
