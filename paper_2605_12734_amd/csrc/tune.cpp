@@ -10,7 +10,8 @@
 // counters, counters with a guided tail) and waves-per-SIMD cap (the
 // kernel's register limit or one less); message-driven grids keep their
 // tile (the dependency lists are built for it) and time their scheduler
-// choices over real steps.  For both, the grid's state is saved to host
+// choices over real steps.  Passes over boxes, where the grid has them, are
+// then timed against the best.  For both, the grid's state is saved to host
 // memory before the search and restored after it.  Results are cached per (dtype, stencil,
 // exec mode, grid, boxes and chare-shape histogram) in the process and, if
 // OD_TUNE_CACHE names a file, on disk.
@@ -138,17 +139,13 @@ od_status Grid::retile(const int32_t tile[3]) {
 // quicker than four-step passes) as cached.
 constexpr int32_t kNoDeep = 16;
 static void apply_schedule(Grid& G, int32_t sched, int32_t waves) {
-    if (G.cfg.exec == OD_MSGDRIVEN) {
-        G.msg_sched = sched;
-    } else {
-        G.persist_sched = sched & (kNoDeep - 1);
-        G.deep_off = (sched & kNoDeep) != 0;
-    }
+    (G.cfg.exec == OD_MSGDRIVEN ? G.msg_sched : G.persist_sched) = sched & (kNoDeep - 1);
+    G.deep_off = (sched & kNoDeep) != 0;
     G.persist_waves = waves;
 }
 
 static int32_t schedule_of(const Grid& G) {
-    return G.cfg.exec == OD_MSGDRIVEN ? G.msg_sched : G.persist_sched | (G.deep_off ? kNoDeep : 0);
+    return (G.cfg.exec == OD_MSGDRIVEN ? G.msg_sched : G.persist_sched) | (G.deep_off ? kNoDeep : 0);
 }
 
 // The grid's whole device state (field storage and control regions) and
@@ -192,11 +189,38 @@ static hipError_t restore_state(Grid& G, const SavedState& S) {
     return he;
 }
 
+// Passes over boxes against passes by the chosen tile: the same iterations on both
+// sides, in turn, two passes at least (a cooperative grid's barriers or queues
+// are part of them) and half a millisecond of them, the quickest of three.
+// run(boxes, n) enqueues n iterations.
+template <class Run>
+static od_status boxes_or_tiles(Grid& G, int32_t iters, hipEvent_t a, hipEvent_t b, int32_t& sched, Run run) {
+    int64_t passes = std::max<int64_t>(2, iters);
+    float least[2] = {1e30f, 1e30f};   // tiles, boxes
+    for (int rep = 0; rep < 4; ++rep)   // (the first is the warm-up)
+        for (int boxes = 0; boxes < 2; ++boxes) {
+            float ms = 0;
+            hipError_t he = hipEventRecord(a, G.st);
+            od_status st = run(boxes != 0, passes * G.deep_steps());
+            if (st != OD_OK) return st;
+            if (he == hipSuccess) he = hipEventRecord(b, G.st);
+            if (he == hipSuccess) he = hipEventSynchronize(b);
+            if (he == hipSuccess) he = hipEventElapsedTime(&ms, a, b);
+            if (he != hipSuccess) return fail(OD_EHIP, std::string("tuning launch: ") + hipGetErrorString(he));
+            if (G.cfg.exec == OD_PERSISTENT || G.cfg.exec == OD_MSGDRIVEN) st = G.device_error();
+            if (st != OD_OK) return st;
+            if (rep > 0) least[boxes] = std::min(least[boxes], ms);
+            else if (boxes && ms < 0.5f) passes = std::min<int64_t>(64, (int64_t)(passes * 0.5f / std::max(ms, 0.005f)) + 1);
+        }
+    if (least[1] > least[0]) sched |= kNoDeep;
+    return OD_OK;
+}
+
 // Message-driven grids: the scheduler choices (claims from the per-XCD
 // cursor or from ready queues; a publisher workgroup per XCD or none) and
-// the waves-per-SIMD cap, at the grid's tile.  Each candidate runs a launch
-// of 2 * iters steps on the grid itself, between save_state and
-// restore_state.
+// the waves-per-SIMD cap, at the grid's tile, then tasks over boxes against
+// the best.  Each candidate runs a launch of 2 * iters steps on the grid itself,
+// between save_state and restore_state.
 static od_status tune_msgdriven(Grid& G, int32_t iters, std::array<int32_t, 5>& best) {
     SavedState S;
     od_status st = save_state(G, S);
@@ -227,6 +251,19 @@ static od_status tune_msgdriven(Grid& G, int32_t iters, std::array<int32_t, 5>& 
                     best = {G.plan.tile[0], G.plan.tile[1], G.plan.tile[2], claim | (pub << 2), w};
                 }
             }
+    // tasks over boxes (at the scheduler's own choices) against the best of them
+    if (he == hipSuccess && st == OD_OK && !G.deep_plan.tiles.empty()) {
+        best[3] &= kNoDeep - 1;
+        apply_schedule(G, best[3], best[4]);
+        st = G.setup_cooperative(false);
+        if (st == OD_OK)
+            st = boxes_or_tiles(G, iters, a, b, best[3], [&](bool boxes, int64_t n) {
+                G.tuning = !boxes;
+                od_status s = G.msgdriven_run(n);
+                G.tuning = true;
+                return s;
+            });
+    }
     if (a) hipEventDestroy(a);
     if (b) hipEventDestroy(b);
     // restore the grid as it was, with the chosen schedule
@@ -415,41 +452,27 @@ static od_status tune(Grid& G, int32_t iters, int32_t out_tile[3]) {
         }
         if (st != OD_OK) break;
     }
-    // passes over boxes against the best tile: the same iterations on both sides,
-    // in turn, two passes at least (a persistent grid's barriers are part of them)
-    // and half a millisecond of them, the quickest of three
     if (st == OD_OK && !G.deep_plan.tiles.empty()) {
         best[3] &= kNoDeep - 1;
         apply_schedule(G, best[3], best[4]);
         st = G.retile(best.data());
-        int64_t passes = std::max<int64_t>(2, iters), n = passes * G.deep_steps();
-        float least[2] = {1e30f, 1e30f};   // tiles, boxes
-        for (int rep = 0; rep < 4 && st == OD_OK; ++rep)   // (the first is the warm-up)
-            for (int boxes = 0; boxes < 2 && st == OD_OK; ++boxes) {
-                he = hipEventRecord(a, G.st);
+        if (st == OD_OK)
+            st = boxes_or_tiles(G, iters, a, b, best[3], [&](bool boxes, int64_t n) -> od_status {
                 if (pers) {
-                    G.tuning = boxes == 0;
-                    st = G.persistent_run(n);
+                    G.tuning = !boxes;
+                    od_status s = G.persistent_run(n);
                     G.tuning = true;
-                } else if (boxes) {
-                    for (int64_t i = 0; i < passes && st == OD_OK; ++i) st = G.fused_deep_pass(G.st, G.parity);
-                } else {
-                    for (int64_t i = 0; i < n && he == hipSuccess; i += G.two_step ? 2 : 1) he = launch();
+                    return s;
                 }
-                float ms = 0;
-                if (he == hipSuccess) he = hipEventRecord(b, G.st);
-                if (he == hipSuccess) he = hipEventSynchronize(b);
-                if (he == hipSuccess) he = hipEventElapsedTime(&ms, a, b);
-                if (st == OD_OK && he == hipSuccess && pers) st = G.device_error();
-                if (st == OD_OK && he != hipSuccess) st = fail(OD_EHIP, std::string("tuning launch: ") + hipGetErrorString(he));
-                if (rep > 0) {
-                    least[boxes] = std::min(least[boxes], ms);
-                } else if (boxes && st == OD_OK && ms < 0.5f) {
-                    passes = std::min<int64_t>(64, (int64_t)(passes * 0.5f / std::max(ms, 0.005f)) + 1);
-                    n = passes * G.deep_steps();
+                od_status s = OD_OK;
+                hipError_t e = hipSuccess;
+                for (int64_t i = 0; i < n && s == OD_OK && e == hipSuccess;
+                     i += boxes ? G.deep_steps() : (G.two_step ? 2 : 1)) {
+                    if (boxes) s = G.fused_deep_pass(G.st, G.parity);
+                    else e = launch();
                 }
-            }
-        if (least[1] > least[0]) best[3] |= kNoDeep;
+                return e == hipSuccess ? s : fail(OD_EHIP, std::string("tuning launch: ") + hipGetErrorString(e));
+            });
     }
     hipEventDestroy(a);
     hipEventDestroy(b);

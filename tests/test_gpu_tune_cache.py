@@ -25,8 +25,10 @@ def _key(n, exec_):
     cfg, _keep = od.make_config(**kw)
     boxes = len(od.host_plan(**kw)["pass"]["boxes"])
     chare = "x".join(str(v if n == FLAT else v // 2) for v in n)
-    return (f"v2/s8/k7/e{cfg.exec}/n{n[0]}x{n[1]}x{n[2]}/b4x{boxes}/{chare}:{1 if n == FLAT else 8}/h0/i0x0", cfg.exec,
-            chare)
+    # (message-driven grids tune the scheduler at the planned tile, here of pairs)
+    tile = "/t" + "x".join(map(str, od.host_plan(**kw)["tile"])) + "/p2" if exec_ == "msgdriven" else ""
+    return (f"v2/s8/k7/e{cfg.exec}/n{n[0]}x{n[1]}x{n[2]}/b4x{boxes}/{chare}:{1 if n == FLAT else 8}{tile}/h0/i0x0",
+            cfg.exec, chare)
 
 
 def _grid(n, exec_):
@@ -47,6 +49,7 @@ def _write_entries():
         rows.append(f"{_key(KEPT, e)[0]} 32 16 8 {sched} 0")
         _, num, chare = _key(OLD, e)   # as files had it before boxes were part of the key
         rows.append(f"s8/e{num}/n{'x'.join(map(str, OLD))}/{chare}:8/h0/i0x0 32 16 8 {sched} 0")
+    rows.append(f"{_key(KEPT, 'msgdriven')[0]} 0 0 0 {NO_BOXES | 1 | 2 << 2} 0")   # cursor, no publisher
     rows.append(f"{_key(FLAT, 'fused')[0]} 256 1 32 {NO_BOXES} 0")
     _, num, chare = _key(FLAT, "fused")
     rows.append(f"s8/e{num}/n{chare}/{chare}:1/h0/i0x0 256 1 32 {NO_BOXES} 0")
@@ -81,12 +84,13 @@ def test_an_entry_that_cannot_be_applied_changes_nothing(exec_):
         g.close()
 
 
-@pytest.mark.parametrize("exec_", FORMS)
+@pytest.mark.parametrize("exec_", FORMS + ("msgdriven",))
 def test_an_entry_without_boxes_runs_the_tile(exec_):
     g = _grid(KEPT, exec_)
     try:
         g.iterate(5)
-        assert g.autotune(1) == (32, 16, 8)
+        tile = (32, 16, 8) if exec_ != "msgdriven" else tuple(g.plan()["tile"])
+        assert g.autotune(1) == tile and g.plan()["schedule"] == {"persistent": 1, "msgdriven": 9}.get(exec_, 0)
         assert g.pass_info()["steps"] == 2 and len(g.pass_info()["boxes"]) == 0
         g.iterate(4)
         g.iterate(3)
