@@ -245,7 +245,7 @@ bool tiles_quicker(const Plan& p, int dtype_bytes, const DeepPlan& d, int64_t co
 DeepPlan deep_plan(const Plan& p, int dtype_bytes, od_exec exec, int tile_steps) {
     int64_t cost = 0;
     DeepPlan d = plan_boxes(p, dtype_bytes, false, exec == OD_MSGDRIVEN, &cost);
-    if (!d.tiles.empty() && tiles_quicker(p, dtype_bytes, d, cost, exec, tile_steps)) d.tiles.clear();
+    d.by_tiles = !d.tiles.empty() && tiles_quicker(p, dtype_bytes, d, cost, exec, tile_steps);
     return d;
 }
 DeepPlan deep_plan_serve(const Plan& p, int dtype_bytes) { return plan_boxes(p, dtype_bytes, true, false, nullptr); }

@@ -46,12 +46,12 @@ struct DeepPlan {
     bool ragged = false;               // some vectors are not full
     std::vector<DeepTile> tiles;       // in launch order; empty: the grid has no four-step passes
     std::vector<int32_t> vx, vi;       // as in DeepMap
+    bool by_tiles = false;             // the planned tiles are estimated to be quicker
 };
 
 // Lane coverage: LX vectors of 16 bytes by EY rows.
 void deep_shape(int dtype_bytes, const DeepPlan& d, int* lx, int* ey);
-// Boxes for a grid of that form, whose passes by tiles are of tile_steps steps;
-// none where the planned tiles are estimated to be quicker.
+// Boxes for a grid of that form, whose passes by tiles are of tile_steps steps.
 DeepPlan deep_plan(const Plan& p, int dtype_bytes, od_exec exec, int tile_steps);
 // The boxes of a served solve: workgroups of kServeWaves waves in either type,
 // at most kServeBoxes of them (a slot's dependency lists hold 26 for each).

@@ -673,6 +673,7 @@ std::string build_layout(const od_config& cfg, Grid& G) {
         const bool pairs = two_step_possible(G) && sweep2_variant_ok(s, p.tile[0], p.tile[1]) && ntiles <= G.tile2_cap;
         G.deep_plan = cfg.stencil == 5 ? deep_plan2d(p, s) : od::deep_plan(p, s, cfg.exec, pairs ? 2 : 1);
     }
+    G.deep_off = G.deep_plan.by_tiles;
     if (!G.deep_plan.tiles.empty()) {
         G.L.deep = cv.take(G.deep_plan.tiles.size() * sizeof(DeepTile));
         G.L.deep_tab = cv.take((G.deep_plan.vx.size() + G.deep_plan.vi.size() + (size_t)(p.n[1] + 2 * p.n[2])) * 4);

@@ -73,7 +73,7 @@ struct Grid {
     int deep_wgs = 0;
     std::vector<int32_t> deep_ptr, deep_idx;
     int msg_counters = 0;
-    bool deep_off = false;           // the autotuner found the tiles quicker
+    bool deep_off = false;           // the tiles are quicker, by estimate or as the autotuner found
     bool tuning = false;             // the autotuner times tiles: no four-step passes
     void drop_deep() {
         deep_plan.tiles.clear();

@@ -123,3 +123,17 @@ def test_an_entry_of_the_other_stencil_is_not_taken():
         assert np.array_equal(g.read(), want) and g.residual() == r
     finally:
         g.close()
+
+
+def test_the_tuner_may_choose_boxes_where_the_rule_did_not():
+    n = (1, 2000, 600)
+    g = od.Grid(n, odf=1, dtype="f32", exec="fused", hints=1, seed=3)
+    try:
+        assert g.pass_info()["steps"] == 2
+        g.iterate(3)
+        g.autotune(2)
+        g.iterate(9)
+        want, _, r = oracle.solve(n, np.float32, seed=3, iters=12)
+        assert np.array_equal(g.read(), want) and g.residual() == r
+    finally:
+        g.close()
