@@ -12,18 +12,14 @@
 #include <cstdlib>
 #include <chrono>
 #include <cmath>
-#include <condition_variable>
 #include <cstdio>
 #include <cstring>
-#include <deque>
 #include <map>
 #include <memory>
-#include <mutex>
 #include <string>
-#include <system_error>
-#include <thread>
 #include <vector>
 
+#include "copy_crew.hpp"
 #include "kernels.hpp"
 #include "od_runtime.hpp"
 
@@ -1533,80 +1529,6 @@ od_status Grid::residual(double* r) {
 
 namespace {
 
-// Host threads that copy filled staging chunks to the caller's memory while
-// the device fills the next ones.  One thread copies about 14 GB/s into fresh
-// pages, the link brings 57: reading 1.08 GB (512^3 fp64) took 97-109 ms with
-// one thread after each chunk and takes 26-30 ms so.
-class CopyCrew {
-   public:
-    explicit CopyCrew(size_t chunks) : done_(chunks, 0) {
-        const unsigned hw = std::thread::hardware_concurrency();
-        const size_t n = std::min<size_t>(chunks, std::min<unsigned>(hw > 0 ? hw : 1, kMost));
-        try {
-            for (size_t i = 0; i < n; ++i) crew_.emplace_back([this] { work(); });
-        } catch (const std::system_error&) {   // fewer, or none: wait() copies itself
-        }
-    }
-    ~CopyCrew() {
-        {
-            std::lock_guard<std::mutex> lk(mu_);
-            closed_ = true;
-        }
-        filled_.notify_all();
-        for (std::thread& t : crew_) t.join();
-    }
-    void give(size_t chunk, char* to, const char* from, size_t bytes) {
-        {
-            std::lock_guard<std::mutex> lk(mu_);
-            jobs_.push_back({chunk, to, from, bytes});
-        }
-        filled_.notify_one();
-    }
-    // until a chunk that was given is copied
-    void wait(size_t chunk) {
-        std::unique_lock<std::mutex> lk(mu_);
-        while (!done_[chunk]) {
-            if (crew_.empty()) {
-                run(lk);
-            } else {
-                copied_.wait(lk);
-            }
-        }
-    }
-
-   private:
-    static constexpr unsigned kMost = 8;
-    struct Job {
-        size_t chunk;
-        char* to;
-        const char* from;
-        size_t bytes;
-    };
-    void run(std::unique_lock<std::mutex>& lk) {   // the oldest job, with mu_ held around it
-        const Job j = jobs_.front();
-        jobs_.pop_front();
-        lk.unlock();
-        std::memcpy(j.to, j.from, j.bytes);
-        lk.lock();
-        done_[j.chunk] = 1;
-    }
-    void work() {
-        std::unique_lock<std::mutex> lk(mu_);
-        for (;;) {
-            filled_.wait(lk, [this] { return closed_ || !jobs_.empty(); });
-            if (jobs_.empty()) return;
-            run(lk);
-            copied_.notify_all();
-        }
-    }
-    std::mutex mu_;
-    std::condition_variable filled_, copied_;
-    std::deque<Job> jobs_;
-    std::vector<char> done_;
-    bool closed_ = false;
-    std::vector<std::thread> crew_;
-};
-
 struct EventSet {
     std::vector<hipEvent_t> ev;
     ~EventSet() {
@@ -1642,6 +1564,7 @@ od_status Grid::read_field(char* host, size_t plane) {
         return OD_OK;
     }
     EventSet evs;
+    evs.ev.reserve(slots);
     hipError_t e = hipSuccess;
     for (size_t i = 0; i < slots && e == hipSuccess; ++i) {
         hipEvent_t v = nullptr;
@@ -1652,9 +1575,10 @@ od_status Grid::read_field(char* host, size_t plane) {
         hipError_t e2 = fill(c);
         return e2 == hipSuccess ? hipEventRecord(evs.ev[c % slots], st) : e2;
     };
-    for (size_t c = 0; c < slots && e == hipSuccess; ++c) e = start(c);
     {
         CopyCrew crew(chunks);
+        for (size_t c = 0; c < slots && e == hipSuccess; ++c) e = start(c);
+        crew.begin();
         // chunk c's slot is refilled (by chunk c + slots) once it is copied; that
         // is looked at `lag` chunks later, so the copies of several slots overlap
         const size_t lag = slots / 2;
