@@ -1546,9 +1546,15 @@ od_status Grid::read_field(char* host, size_t plane) {
     const int64_t per = (int64_t)std::max<size_t>(1, kChunk / plane);
     const size_t chunks = (size_t)ceil_div(PZ, per), slot = (size_t)per * plane;
     size_t slots = std::min(chunks, kSlots);
-    if (pinned_borrowed) slots = std::min(slots, pinned_bytes / slot);
+    if (pinned_borrowed) slots = std::max<size_t>(1, std::min(slots, pinned_bytes / slot));
     else slots = std::min(slots, std::max<size_t>(2, ((size_t)64 << 20) / slot));
-    od_status os = ensure_pinned(std::max<size_t>(slots, 1) * slot);
+    od_status os = ensure_pinned(slots * slot);
+    if (os != OD_OK && slots > 1 && !pinned_borrowed) {
+        // planes of hundreds of MB: one slot is all that a read has to have
+        (void)hipGetLastError();
+        slots = 1;
+        os = ensure_pinned(slot);
+    }
     if (os != OD_OK) return os;
     char* const pin = static_cast<char*>(pinned);
     auto bytes_of = [&](size_t c) { return (size_t)(std::min<int64_t>(PZ, ((int64_t)c + 1) * per) - (int64_t)c * per) * plane; };
