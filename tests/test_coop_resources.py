@@ -65,3 +65,28 @@ def test_imbalance_variants_keep_lds():
             b = rows[f"od::k_persistent2<{t}, {x}, {y}, {dyn}, true>"]
             assert a[2] == b[2], (t, x, y, dyn)
         assert rows[f"od::k_msgdriven2<{t}, {x}, {y}, false>"][2] == rows[f"od::k_msgdriven2<{t}, {x}, {y}, true>"][2]
+
+
+def test_every_pass_over_boxes_recorded():
+    # the persistent and message-driven passes over boxes, each variant, and the
+    # serving kernel
+    src = open(os.path.join(PKG, "csrc", "deep_dev.hpp")).read()
+    m = re.search(r"#define OD_DEEP_VARIANTS\(X\)((?:[^\n]*\\\n)*[^\n]*)", src)
+    variants = re.findall(r"X\((double|float), (\d+), (true|false)\)", m.group(1))
+    assert len(variants) == 8
+    rows = _table()
+    names = ["od::k_serve"]
+    for t, r, ragged in variants:
+        names += [f"od::k_deep_persistent<{t}, {r}, {ragged}>", f"od::k_deep_msg<{t}, {r}, {ragged}>"]
+    missing = [n for n in names if n not in rows]
+    assert not missing, missing
+    assert all(rows[n][2] > 0 for n in names)   # all of them keep boxes' rows in LDS
+
+
+def test_names_the_sizing_looks_up_are_those_recorded():
+    # a kernel renamed in one place only would be sized by the guess unseen
+    src = open(KERNELS).read()
+    looked = set(re.findall(r'"(od::k_\w+)"', src)) | set(re.findall(r'"(od::k_\w+)<', src))
+    kernels = {n.split("<")[0] for n in _table()}
+    assert {"od::k_deep_persistent", "od::k_deep_msg", "od::k_serve"} <= looked
+    assert looked <= kernels, looked - kernels
