@@ -164,7 +164,8 @@ typedef struct {
      * without a schedule forced by bits 4, 5, 11 or 13), run groups of four
      * iterations as one pass over boxes of the whole grid (od_pass_info;
      * large grids only a few cells thick, whose boxes would be mostly idle,
-     * keep to their tiles; od_autotune times both); the
+     * keep to their tiles; od_autotune times both; OD_MSGDRIVEN where the
+     * count given to od_iterate is long enough to make up for the launches); the
      * values are again the same, and what is left over of a count runs as
      * pairs and a single sweep.  Grids of the 2D stencil run groups of eight
      * (OD_FUSED, OD_GRAPH).

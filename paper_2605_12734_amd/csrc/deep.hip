@@ -209,7 +209,7 @@ DeepPlan plan_boxes(const Plan& p, int dtype_bytes, bool serve, bool tasks, int6
 // Thin grids, whose boxes are mostly lanes outside the grid (three quarters at
 // least): four steps by passes of the planned tiles, `steps` steps a pass, are
 // estimated to take no longer than a pass over the boxes (`cost`, in units of
-// 10 ns).  A tile's march of tz planes takes lat * (tz + 2) and a start-up; a full
+// 10 ns).  tile_time: a tile's march of tz planes takes lat * (tz + 2) and a start-up; a full
 // chip's tiles go through at `rate` per plane, start-up counted as ten planes,
 // more the more of a tile's row is cells (measured over 1 to 8000 cells an axis).
 // us per iteration by boxes / by tiles, fused: fp64 (1,2000,2000) 223 / 170,
@@ -218,11 +218,7 @@ DeepPlan plan_boxes(const Plan& p, int dtype_bytes, bool serve, bool tasks, int6
 // chip idle; (1,1,100000) 85 / 67; fp32 (8000,1,8000) 397 / 212, (4,8000,2000)
 // 423 / 384.  Of 600 random grids with an axis of 1 to 40, in all forms, boxes cost
 // 13 more than 5 % and half a microsecond without the rule, 1 with it.
-bool tiles_quicker(const Plan& p, int dtype_bytes, const DeepPlan& d, int64_t cost, od_exec exec, int steps) {
-    int lx, ey;
-    deep_shape(dtype_bytes, d, &lx, &ey);
-    if (cost < 4000) return false;   // 40 us a pass: either is mostly start-up
-    if (4 * std::min<int64_t>(p.n[0], kEX) * std::min<int64_t>(p.n[1], ey) > (int64_t)kEX * ey) return false;
+double tile_time(const Plan& p, int dtype_bytes, od_exec exec, double full) {
     int32_t ex = 1, ez = 1;
     for (const Chare& c : p.chares) {
         ex = std::max(ex, c.e[0]);
@@ -231,13 +227,21 @@ bool tiles_quicker(const Plan& p, int dtype_bytes, const DeepPlan& d, int64_t co
     const double f = std::min(1.0, (double)ex / p.tile[0]), tz = std::min(p.tile[2], ez), n = (double)p.tiles.size() / 256;
     const bool f64 = dtype_bytes == 8, row = p.tile[1] == 1;
     const double lat = row ? (f64 ? 0.8 : 1.13) * (tz + 6) : 4.8 + (f64 ? 1.0 : 1.25) * (tz + 2);
-    const double rate = row ? (f64 ? 0.15 + 0.33 * f : 0.19 + 0.18 * f) : (f64 ? 0.24 + 0.11 * f : 0.29 + 0.12 * f);
+    const double rate = row ? (f64 ? 0.15 + 0.33 * f : 0.19 + 0.18 * f) : (f64 ? 0.24 : 0.29) + full * f;
     // (the cooperative forms' barrier or queue, per pass over the tiles)
     const double coop = row ? (exec == OD_FUSED || exec == OD_GRAPH ? 1.0 : 1.08)
                             : (exec == OD_PERSISTENT ? 1.13 : (exec == OD_MSGDRIVEN ? (f64 ? 1.3 : 1.5) : 1.0));
+    return coop * std::max(lat, n * (tz + 10) * rate);
+}
+
+bool tiles_quicker(const Plan& p, int dtype_bytes, const DeepPlan& d, int64_t cost, od_exec exec, int steps) {
+    int lx, ey;
+    deep_shape(dtype_bytes, d, &lx, &ey);
+    if (cost < 4000) return false;   // 40 us a pass: either is mostly start-up
+    if (4 * std::min<int64_t>(p.n[0], kEX) * std::min<int64_t>(p.n[1], ey) > (int64_t)kEX * ey) return false;
     // (rows of one cache line or less: the boxes were 5-25 % over the estimate)
     const double boxes = (double)cost * (p.n[0] * dtype_bytes <= 64 ? 1.1 : 1.0);
-    return 100.0 * kDeepSteps / steps * coop * std::max(lat, n * (tz + 10) * rate) <= boxes;
+    return 100.0 * kDeepSteps / steps * tile_time(p, dtype_bytes, exec, dtype_bytes == 8 ? 0.11 : 0.12) <= boxes;
 }
 
 }  // namespace
@@ -245,7 +249,23 @@ bool tiles_quicker(const Plan& p, int dtype_bytes, const DeepPlan& d, int64_t co
 DeepPlan deep_plan(const Plan& p, int dtype_bytes, od_exec exec, int tile_steps) {
     int64_t cost = 0;
     DeepPlan d = plan_boxes(p, dtype_bytes, false, exec == OD_MSGDRIVEN, &cost);
-    d.by_tiles = !d.tiles.empty() && tiles_quicker(p, dtype_bytes, d, cost, exec, tile_steps);
+    if (d.tiles.empty()) return d;
+    d.by_tiles = tiles_quicker(p, dtype_bytes, d, cost, exec, tile_steps);
+    if (exec == OD_MSGDRIVEN) {
+        // Short counts.  us of od_iterate(n) and the residual, by pairs / by boxes
+        // and pairs for the rest: fp64 128^3 (495 boxes) n = 4 157 / 198, 8 236 / 244, 12
+        // 317 / 286, 6 197 / 291, 10 277 / 338; 64^3 (224) 4 140 / 113, 6 176 / 196, 10 250 /
+        // 220; 256^3 (250), whose launches of tiles start slowly, 4 407 / 209, 6 501 /
+        // 496; fp32 128^3 (720) 4 164 / 220, 8 255 / 260, 12 349 / 304; 256^3 4 265 / 220, 6
+        // 325 / 403, 10 440 / 481.
+        // A launch of tiles takes about 60 us and 0.16 for each of up to 1250 tiles to
+        // start, one of boxes 55 and 0.18.
+        const double pass = tile_time(p, dtype_bytes, OD_FUSED, dtype_bytes == 8 ? 0.34 : 0.41);
+        const double slow = std::min(0.16 * (double)p.tiles.size(), 200.0);
+        d.gain = std::max(1.0, pass * kDeepSteps / tile_steps - 0.01 * (double)(cost - (d.rows > 1 ? kTaskRows : 0)));
+        d.start = 0.18 * (double)d.tiles.size() - 5 - slow;
+        d.rest = 45 + slow;
+    }
     return d;
 }
 DeepPlan deep_plan_serve(const Plan& p, int dtype_bytes) { return plan_boxes(p, dtype_bytes, true, false, nullptr); }

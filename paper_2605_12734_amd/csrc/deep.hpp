@@ -47,6 +47,10 @@ struct DeepPlan {
     std::vector<DeepTile> tiles;       // in launch order; empty: the grid has no four-step passes
     std::vector<int32_t> vx, vi;       // as in DeepMap
     bool by_tiles = false;             // the planned tiles are estimated to be quicker
+    // message-driven, us: what a pass gains on pairs, how much longer a launch of
+    // boxes takes to start than one of tiles, and what a further launch of tiles
+    // for the rest of a count adds
+    double gain = 0, start = 0, rest = 0;
 };
 
 // Lane coverage: LX vectors of 16 bytes by EY rows.

@@ -1253,7 +1253,7 @@ od_status Grid::persistent_run(int64_t n) {
     return OD_OK;
 }
 
-od_status Grid::msgdriven_run(int64_t n) {
+od_status Grid::msgdriven_run(int64_t n, bool any_count) {
     if (grid_wgs <= 0) return fail(OD_EHIP, "message-driven kernel: no co-resident workgroups");
     if (iters + n > INT32_MAX) return fail(OD_EINVAL, "step counters limited to 2^31 iterations");
     // One launch runs fewer than 2^16 steps (a task carries its step
@@ -1262,8 +1262,10 @@ od_status Grid::msgdriven_run(int64_t n) {
     const int64_t per = std::max<int64_t>(1, std::min<int64_t>(((int64_t)1 << 16) - 1,
                                                                ((int64_t)1 << 23) / std::max<size_t>(tiles_h.size(), 1)));
     // tasks of four steps over boxes, what is left as tasks of two steps and a
-    // one-step launch
-    if (deep()) {
+    // one-step launch; tiles alone where the boxes would not make up for what
+    // their launch, and another for the rest, takes to start
+    const bool rest = n % kDeepSteps >= (two_step ? 2 : 1);
+    if (deep() && (any_count || (double)(n / kDeepSteps) * deep_plan.gain >= deep_plan.start + (rest ? deep_plan.rest : 0))) {
         const int64_t per_box = std::max<int64_t>(1, std::min<int64_t>(((int64_t)1 << 16) - 1,
                                                                        ((int64_t)1 << 23) / (int64_t)deep_plan.tiles.size()));
         for (int64_t m = n / kDeepSteps; m > 0;) {

@@ -187,7 +187,7 @@ struct Grid {
     int64_t bytes_per_pass() const;
     od_status graph_run(int64_t n);
     od_status persistent_run(int64_t n);
-    od_status msgdriven_run(int64_t n);
+    od_status msgdriven_run(int64_t n, bool any_count = false);   // any_count: boxes however few the passes
     od_status msgdriven_launch(int64_t n, int steps);   // n scheduler steps of `steps` iterations a task
     od_status per_chare_run(int64_t n);
     od_status iterate(int64_t n);

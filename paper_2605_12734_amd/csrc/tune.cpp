@@ -259,7 +259,7 @@ static od_status tune_msgdriven(Grid& G, int32_t iters, std::array<int32_t, 5>& 
         if (st == OD_OK)
             st = boxes_or_tiles(G, iters, a, b, best[3], [&](bool boxes, int64_t n) {
                 G.tuning = !boxes;
-                od_status s = G.msgdriven_run(n);
+                od_status s = G.msgdriven_run(n, boxes);
                 G.tuning = true;
                 return s;
             });

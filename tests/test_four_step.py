@@ -180,6 +180,36 @@ def test_boxes_in_one_launch(dtype, exec_, hints):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype", ["f64", "f32"])
+@pytest.mark.parametrize("iters", [[40], [41], [42, 3], [2, 43, 40], [1, 40, 4, 44]])
+def test_message_driven_boxes_and_tiles_in_turn(dtype, iters):
+    # counts long enough for boxes, what is left of them, and short ones by tiles
+    n = (128, 64, 24)
+    want, _, r = oracle.solve(n, DT[dtype], seed=5, iters=sum(iters), bc=BC6)
+    U, got = _run(n, 8, dtype, iters, "msgdriven")
+    _same(U, want)
+    assert got == r
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,n,count", [("f32", 128, 6), ("f64", 128, 10), ("f64", 64, 6), ("f32", 192, 4)])
+def test_short_message_driven_counts_cost_no_more_than_pairs(dtype, n, count):
+    # a launch of boxes, and another for the rest, took up to 1.7 times as long
+    times = []
+    for hints in (1, 1 | 1 << 14):
+        g = od.Grid(n, odf=8, dtype=dtype, exec="msgdriven", hints=hints)
+        took = []
+        for _ in range(40):
+            t0 = time.perf_counter()
+            g.iterate(count)
+            g.residual()
+            took.append(time.perf_counter() - t0)
+        g.close()
+        times.append(sorted(took)[5])
+    assert times[0] < 1.2 * times[1], times
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["f64", "f32"])
 @pytest.mark.parametrize("odf,iters", [(64, [4]), (64, [3, 8]), (8, [11])])
 def test_imbalance_re_runs_before_the_pass(dtype, odf, iters):
     # half the chares re-run up to four times a step: their re-runs write the

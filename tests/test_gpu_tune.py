@@ -49,13 +49,13 @@ def test_msgdriven_autotune_restores_state(dtype, n, odf):
         g.close()
 
 
-@pytest.mark.parametrize("before", [4, 5])
-@pytest.mark.parametrize("after", [1, 2, 3, 4, 7])
+@pytest.mark.parametrize("before", [40, 41])
+@pytest.mark.parametrize("after", [1, 2, 3, 4, 7, 40])
 def test_msgdriven_autotune_between_boxes_and_tiles(before, after):
-    # 4 iterations leave the step counters of the boxes current, 5 those of
+    # 40 iterations leave the step counters of the boxes current, 41 those of
     # the tiles; what follows starts with either.  (a size of its own for each:
     # tuned sizes are kept in the process)
-    n = (64, 40 + 8 * after, 24 + 8 * before)
+    n = (64, 40 + 8 * min(after, 8), 56 + 8 * (before - 40))
     g = od.Grid(n, odf=8, dtype="f64", exec="msgdriven", hints=1)
     try:
         g.iterate(before)
