@@ -263,7 +263,8 @@ od_status od_create_static(const od_config* cfg, void* hip_stream, void* dev_fie
  * cfg.exec names (Section III for the per-chare form and the fused and
  * graph-captured mitigations cited in Section I).  Where the grid runs
  * iterations in pairs (od_plan_info.steps_per_pass == 2, hints bit 12) a
- * pass does two of them, with identical results.  Allocates nothing and
+ * pass does two of them, over boxes (hints bit 14) four or eight, with
+ * identical results.  Allocates nothing and
  * does not synchronise, except in OD_PER_CHARE mode whose host loop itself
  * issues the work. */
 od_status od_iterate(struct od_grid* g, int64_t n);
@@ -282,7 +283,9 @@ od_status od_residual(struct od_grid* g, double* r);
 /* Iterations done since od_create (or the last od_write). */
 od_status od_iterations(struct od_grid* g, int64_t* iters);
 
-/* Copy the whole padded global field (layout above) to host memory; syncs. */
+/* Copy the whole padded global field (layout above) to host memory; syncs.
+ * Fields above 4 MiB are copied out of the staging memory by up to eight host
+ * threads (no more than the machine has), which end with the call. */
 od_status od_read(struct od_grid* g, void* host_dst, size_t bytes);
 
 /* Set interior and Dirichlet shell from a padded global host array; resets
@@ -314,6 +317,11 @@ typedef struct {
     int32_t nchares, ntiles, npseudo;
     int64_t interior, halo_cells;   /* halo_cells: ghost cells filled from other chares */
     int64_t bytes_per_iter;         /* algorithmic HBM bytes of one sweep            */
+    /* tile, grid_wgs, schedule, coop_waves, steps_per_pass and bytes_per_pass are those of
+       the passes by tiles.  A grid that runs passes over boxes (od_pass_info) uses them
+       for what fours (eights in 2D) leave over of a count: its boxes go to the
+       workgroups of a persistent launch by a fixed stride, and to a message-driven
+       one by the scheduler choices that the hints force, else the automatic ones. */
     int32_t tile[3];                /* tile shape in use                              */
     int32_t grid_wgs;               /* workgroups of the persistent / msg-driven launch */
     int32_t schedule;               /* OD_PERSISTENT: 1 fixed stride, 2 per-XCD counters,
@@ -328,7 +336,7 @@ typedef struct {
                                        storage (the buffer od_create_static takes)    */
     int64_t control_bytes;          /* rest of the workspace: descriptors and device
                                        state, for this handle's plan                 */
-    int32_t steps_per_pass;         /* of the passes by tiles: 2: iterations run in pairs (OD_FUSED, OD_GRAPH,
+    int32_t steps_per_pass;         /* 2: iterations run in pairs (OD_FUSED, OD_GRAPH,
                                        OD_PERSISTENT, OD_MSGDRIVEN; hints bit 12);
                                        else 1                                          */
     int64_t bytes_per_pass;         /* algorithmic HBM bytes of one pass: one sweep, or
@@ -466,8 +474,12 @@ od_status od_launch_overlap(void* dev_ws, size_t ws_bytes, int64_t total_threads
  * and time their scheduler choices (cursor or ready-queue claims,
  * publisher or none, waves cap) over 2 * iters steps each.  For these two,
  * the field, the device state and the iteration count are saved to pinned
- * host memory first and restored afterwards.  The fastest choice is applied and cached per (dtype, mode,
- * grid and chare shapes, hints, imbalance).  OD_PER_CHARE: OD_EINVAL.
+ * host memory first and restored afterwards.  A grid with passes over boxes
+ * (od_pass_info) then times those against the choice, over the same
+ * iterations, and runs the quicker.  The fastest choice is applied and cached per (dtype, stencil, mode,
+ * grid and chare shapes, boxes, hints, imbalance), in the process and, if the
+ * environment names a file in OD_TUNE_CACHE, there.  An entry of that file that
+ * the grid cannot take is an error and changes nothing.  OD_PER_CHARE: OD_EINVAL.
  * `out_tile` receives the chosen shape; od_plan reports the schedule. */
 od_status od_autotune(struct od_grid* g, int32_t iters, int32_t out_tile[3]);
 
