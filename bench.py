@@ -183,8 +183,22 @@ TUNE_ITERS = 6
 def grid_plan(g):
     """The grid's plan with its longest pass as the pass."""
     p, q = g.plan(), g.pass_info()
-    p.update(steps_per_pass=q["steps"], bytes_per_pass=q["bytes"])
+    p.update(steps_per_pass=q["steps"], bytes_per_pass=q["bytes"], boxes=len(q["boxes"]))
     return p
+
+
+def pass_shape(form, plan):
+    """What a form's passes run: boxes of the whole grid (a cooperative launch
+    deals them by a fixed stride, or as message-driven tasks), or the tile with
+    its schedule and workgroups, which with boxes only the rest of a count runs."""
+    if plan["boxes"]:
+        return {form + "_boxes": plan["boxes"]}
+    out = {form + "_tile": list(plan["tile"])}
+    if form == "persistent":
+        out[form + "_schedule"] = SCHEDULES.get(plan["schedule"], plan["schedule"])
+    if form != "batched":
+        out[form + "_grid_wgs"] = plan["grid_wgs"]
+    return out
 
 
 def pass_gbps(plan, launch_s):
@@ -259,10 +273,10 @@ def cpu_baseline(n, dtype, target_s=15.0, max_iters=200, chunk=10):
 
 
 def odf_sweep(n, iters, persistent=True):
-    """Per dtype and ODF: graph-captured fused launches (tile autotuned),
-    the persistent cooperative form (tile and schedule autotuned on its own
-    kernel), the message-driven form (the fastest of a few tiles in short
-    runs, see msgdriven_tile), per-chare launches (the graph's tile).  Each
+    """Per dtype and ODF: graph-captured fused launches and the persistent
+    cooperative form (both autotuned), the message-driven form with a tile (the
+    fastest of a few in short runs, see msgdriven_tile) and as it runs by
+    default, per-chare launches (the graph's tile).  Each
     batched form's roofline fraction divides the algorithmic bytes per
     iteration by its own kernel time per iteration (HIP events)."""
     rows = []
@@ -273,33 +287,36 @@ def odf_sweep(n, iters, persistent=True):
             bp = b["plan"]["bytes_per_iter"]
             k = round(odf ** (1 / 3))
             gb = pass_gbps(b["plan"], b["launch_s"])
-            row = {"dtype": dtype, "odf": odf, "block": n // k, "tile": list(tile),
+            row = {"dtype": dtype, "odf": odf, "block": n // k, "per_chare_tile": list(tile),
+                   **pass_shape("batched", b["plan"]),
                    "batched_steps_per_pass": b["plan"]["steps_per_pass"],
                    "batched_glups": round(b["glups"], 2),
                    "batched_hbm_gbps": round(gb, 1),
                    "batched_frac": round(gb / PEAK_HBM_GBPS, 4),
                    "batched_step_bytes_frac": round(bp / b["launch_s"] / 1e9 / PEAK_HBM_GBPS, 4)}
             if persistent:
-                # tile and schedule tuned on the persistent kernel itself
+                # tuned on the persistent kernels themselves
                 q = grid_leg(n, odf, dtype, "persistent", iters, 2, 1)
                 gq = pass_gbps(q["plan"], q["launch_s"])
-                row.update({"persistent_tile": list(q["plan"]["tile"]),
-                            "persistent_schedule": SCHEDULES.get(q["plan"]["schedule"], q["plan"]["schedule"]),
+                row.update({**pass_shape("persistent", q["plan"]),
                             "persistent_steps_per_pass": q["plan"]["steps_per_pass"],
                             "persistent_glups": round(q["glups"], 2),
                             "persistent_hbm_gbps": round(gq, 1),
                             "persistent_frac": round(gq / PEAK_HBM_GBPS, 4),
                             "persistent_step_bytes_frac": round(bp / q["launch_s"] / 1e9 / PEAK_HBM_GBPS, 4),
-                            "persistent_us_per_iter": round(q["launch_s"] * 1e6, 2),
-                            "persistent_grid_wgs": q["plan"]["grid_wgs"]})
+                            "persistent_us_per_iter": round(q["launch_s"] * 1e6, 2)})
                 m = grid_leg(n, odf, dtype, "msgdriven", iters, 2, 1, tile=msgdriven_tile(n, odf, dtype, tile))
                 gm = pass_gbps(m["plan"], m["launch_s"])
-                row.update({"msgdriven_tile": list(m["plan"]["tile"]),
+                row.update({**pass_shape("msgdriven", m["plan"]),
                             "msgdriven_steps_per_pass": m["plan"]["steps_per_pass"],
                             "msgdriven_glups": round(m["glups"], 2),
                             "msgdriven_hbm_gbps": round(gm, 1),
-                            "msgdriven_frac": round(gm / PEAK_HBM_GBPS, 4),
-                            "msgdriven_grid_wgs": m["plan"]["grid_wgs"]})
+                            "msgdriven_frac": round(gm / PEAK_HBM_GBPS, 4)})
+                # and as the form runs with no tile fixed
+                d = grid_leg(n, odf, dtype, "msgdriven", iters, 2, 1, autotune=False)
+                row.update({**pass_shape("msgdriven_default", d["plan"]),
+                            "msgdriven_default_steps_per_pass": d["plan"]["steps_per_pass"],
+                            "msgdriven_default_glups": round(d["glups"], 2)})
             pc_iters = 10 if odf <= 64 else (4 if odf <= 512 else 2)
             p = grid_leg(n, odf, dtype, "per_chare", pc_iters, 1, 1, tile=tile)
             row.update({"per_chare_glups": round(p["glups"], 3),
@@ -331,7 +348,8 @@ def amr_leg(iters=500, multires_only=False):
                       "hbm_gbps": round(gb, 1),
                       "frac": round(gb / PEAK_HBM_GBPS, 4),
                       "step_bytes_frac": round(bp * iters / t["dev_s"] / 1e9 / PEAK_HBM_GBPS, 4),
-                      "tile": list(plan["tile"]), "tiles": plan["ntiles"], "iters": iters}
+                      **({"boxes": plan["boxes"]} if plan["boxes"] else
+                         {"tile": list(plan["tile"]), "tiles": plan["ntiles"]}), "iters": iters}
         log("amr:", exec_, out[exec_])
     # multi-resolution reading: the same octree, 16 cells per leaf edge
     # (finest leaves unit cells), resolution-change faces filled by
@@ -595,7 +613,7 @@ def main():
     s = 8 if args.dtype == "f64" else 4
     strict = 2 * s * plan["interior"] / leg["launch_s"] / 1e9
     log(f"bench: {leg['glups']:.1f} GLUP/s, {leg['launch_s'] * 1e6:.1f} us/iteration, {spp} step(s) per pass, "
-        f"{achieved:.0f} GB/s algorithmic, tile {plan['tile']}")
+        f"{achieved:.0f} GB/s algorithmic, " + (f"{plan['boxes']} boxes" if plan["boxes"] else f"tile {plan['tile']}"))
 
     ceil = None if args.no_ceilings else od.hbm_ceilings(4 << 30, iters=8)
     if ceil:
@@ -641,7 +659,9 @@ def main():
         "data": "synthetic: SplitMix64 U[0,1) interior, Dirichlet 1 on x-, 0 elsewhere",
         "config": {"workload": f"{args.n}^3 {args.dtype} 7-point Jacobi, {plan['nchares']} chares of "
                                f"{args.n // k}^3, {args.iters} iterations per step, exec={args.exec}",
-                   "odf": plan["nchares"], "iters_per_step": args.iters, "tile": list(plan["tile"]),
+                   "odf": plan["nchares"], "iters_per_step": args.iters,
+                   # (with boxes the tile runs what fours leave over of a count)
+                   "boxes": plan["boxes"], "tile": list(plan["tile"]),
                    "exec": args.exec, "hints": args.hints},
         "roofline": roof,
         "residual": leg["residual"],
