@@ -1073,7 +1073,10 @@ od_status Grid::ensure_pinned(size_t bytes) {
     pinned = nullptr;
     pinned_bytes = 0;
     hipError_t e = hipHostMalloc(&pinned, bytes, hipHostMallocDefault);
-    if (e != hipSuccess) return fail(OD_EHIP, std::string("hipHostMalloc staging: ") + hipGetErrorString(e));
+    if (e != hipSuccess) {
+        (void)hipGetLastError();   // not the next launch's: callers may go on without
+        return fail(OD_EHIP, std::string("hipHostMalloc staging: ") + hipGetErrorString(e));
+    }
     pinned_bytes = bytes;
     return OD_OK;
 }
@@ -1553,7 +1556,6 @@ od_status Grid::read_field(char* host, size_t plane) {
     od_status os = ensure_pinned(slots * slot);
     if (os != OD_OK && slots > 1 && !pinned_borrowed) {
         // planes of hundreds of MB: one slot is all that a read has to have
-        (void)hipGetLastError();
         slots = 1;
         os = ensure_pinned(slot);
     }
@@ -1652,9 +1654,7 @@ od_status Grid::block_io(int32_t b, void* host, size_t bytes, bool to_host) {
     hipError_t e = hipSuccess;
     // a small block comes with the error word in one launch (see kSmallBlock)
     const size_t at_err = align_up(need, 16), one = at_err + 16;
-    if (to_host && need <= kSmallBlock && (!pinned_borrowed || pinned_bytes >= one)) {
-        od_status os = ensure_pinned(one);
-        if (os != OD_OK) return os;
+    if (to_host && need <= kSmallBlock && ensure_pinned(one) == OD_OK) {   // (else the copies below)
         char* pin = static_cast<char*>(pinned);
         const int32_t cells[3] = {B.ex, B.ey, B.ez};
         e = launch_read_block(s, st, base + (size_t)(parity ? B.off[1] : B.off[0]) * s, cells, B.py, B.pz, pin,
