@@ -25,9 +25,17 @@
 // counters included.  64 x 64 cells are what a CU can hold: 128 VGPRs of
 // levels per lane at two waves per SIMD in fp64, and 128 KB of LDS for the outer
 // rows; fp32 holds two such tiles.  The lanes' overlap computes 1.3 times the
-// cells at 512^3.  The pass is now bound by issue (VALU 60-75 % busy) and by
-// the latency of the plane loaded ahead; with every load hitting the cache it
-// runs 115-120 us per iteration at 512^3 fp64, with the stores too.
+// cells at 512^3.  The pass is now bound by issue (VALU active in 57 % of the busy
+// cycles in fp64, 76 % in fp32; 19 and 15 VALU instructions per update) and by the
+// latency of the plane loaded ahead (waves wait 35 % of theirs, two to a SIMD).
+// Four rows spill 16-24 bytes of scratch per lane in fp64 and 68-100 in fp32
+// (the cooperative forms 136-236, whose loops around the pass hold more), one
+// row none (message-driven 12-20).
+//
+// Sums too small for the quick division (Sixth, below), zeros among them, send a
+// wave's level through true divisions.  A field of zeros with one hot face, 512^3, us
+// per iteration against U[0,1) and against pairs from the same start: fp64 182 /
+// 155 / 263, fp32 118 / 80 / 165.
 //
 // One row a strip (R = 1) makes a box of 16 rows whose iterations are shorter:
 // what small grids, which wait for one box's planes, are quicker with.

@@ -1959,7 +1959,7 @@ k_deep_persistent(DeepMap g, const DeepTile* __restrict__ tiles, int32_t ntiles,
 // Message-driven tasks of four steps: a task is one pass of one box, and a box
 // waits for those whose cells its lanes read (the lists reach its whole ring).
 // us per iteration against tasks of two steps: 512^3 fp64 ODF 512 149 / 292,
-// fp32 100 / 166, 256^3 fp64 29 / 52, 64^3 fp64 7.7 / 18.6.
+// fp32 100 / 166, 256^3 fp64 29 / 52, 64^3 fp64 6.0 / 18.6.
 template <typename T, int R, bool RAG>
 __global__ void __launch_bounds__(deep_waves((int)sizeof(T)) * 64) OD_DEEP_OCC(R)
 k_deep_msg(MsgArgs a, DeepMap g, const DeepTile* __restrict__ tiles) {
@@ -1981,7 +1981,8 @@ k_deep_msg(MsgArgs a, DeepMap g, const DeepTile* __restrict__ tiles) {
 // are in flight.  ms against tasks of one step: 16 solves of 32-256 cells an edge,
 // mixed types, 600 iterations checked every 10 80 / 168, of 32-48 11.7 / 35.1; one
 // of 256^3 fp64 24.2 / 54.0, of 64^3 10.7 / 20.1.  Checked at every iteration, where
-// each pass is one step: 205 / 211, 22.6 / 36.4, 57.8 / 60.9, 17.5 / 20.7.
+// each pass is one step: 205 / 211, 22.6 / 36.4, 57.8 / 60.9, 17.5 / 20.7.  All
+// variants in one kernel cost 244 bytes of scratch per lane and 281 spilled SGPRs.
 constexpr size_t serve_lds() {
     size_t m = sizeof(typename Deep<double, 4, kServeWaves>::Lds);
     m = m > sizeof(typename Deep<double, 1, kServeWaves>::Lds) ? m : sizeof(typename Deep<double, 1, kServeWaves>::Lds);
