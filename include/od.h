@@ -266,7 +266,10 @@ od_status od_create_static(const od_config* cfg, void* hip_stream, void* dev_fie
  * pass does two of them, over boxes (hints bit 14) four or eight, with
  * identical results.  Allocates nothing and
  * does not synchronise, except in OD_PER_CHARE mode whose host loop itself
- * issues the work. */
+ * issues the work.  OD_FUSED and OD_PERSISTENT calls may be captured into a
+ * HIP graph by the caller; the capture counts as the call's n iterations, and
+ * each replay after the first goes on for n more if the passes by tiles of n
+ * are even in number (pairs: n % 4 is 0 or 3; one step per pass: n is even). */
 od_status od_iterate(struct od_grid* g, int64_t n);
 
 /* Synchronise the stream; *r = residual of the last sweep (0 before any):

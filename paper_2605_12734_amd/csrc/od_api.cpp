@@ -1182,6 +1182,22 @@ od_status Grid::graph_run(int64_t n) {
     return OD_OK;
 }
 
+// Iterations of a count that run over boxes (the rest follows by tiles).  Under
+// the caller's stream capture the count keeps an odd or even number of passes as
+// by tiles alone: a replay goes on from where the last one ended only if they are
+// even, since each pass changes the parity that the next one reads.
+int64_t Grid::long_steps(int64_t n) {
+    const int64_t D = deep_steps(), most = deep() ? n / D : 0;
+    if (most == 0) return 0;
+    auto tiles = [&](int64_t m) { return two_step ? m / 2 + m % 2 : m; };
+    if (((most + tiles(n - most * D) - tiles(n)) & 1) != 0) {
+        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(st, &cs) != hipSuccess) (void)hipGetLastError();
+        else if (cs != hipStreamCaptureStatusNone) return (most - 1) * D;
+    }
+    return most * D;
+}
+
 od_status Grid::persistent_run(int64_t n) {
     if (grid_wgs <= 0) return fail(OD_EHIP, "persistent kernel: no co-resident workgroups");
     if (plan.multires) {
@@ -1198,14 +1214,13 @@ od_status Grid::persistent_run(int64_t n) {
         iters += n;
         return OD_OK;
     }
-    if (deep() && n >= kDeepSteps) {
-        const int64_t passes = n / kDeepSteps;
+    if (const int64_t passes = long_steps(n) / kDeepSteps; passes > 0) {
         hipError_t e = launch_deep_persistent(s, deep_plan, st, deep_wgs, deep_map, reinterpret_cast<const DeepTile*>(cp(L.deep)),
                                               parity, passes, res_ptr(),
                                               reinterpret_cast<unsigned int*>(cp(L.bar)),
                                               reinterpret_cast<unsigned int*>(cp(L.err)),
                                               device_wait_ticks(cfg.wait_s > 0 ? cfg.wait_s : 10.0), mode(),
-                                              n % kDeepSteps == 0);
+                                              n == passes * kDeepSteps);
         if (e != hipSuccess) return fail(OD_EHIP, std::string("persistent launch: ") + hipGetErrorString(e));
         parity ^= (int)(passes & 1);
         iters += passes * kDeepSteps;
@@ -1462,8 +1477,9 @@ od_status Grid::iterate(int64_t n) {
     switch (cfg.exec) {
         case OD_FUSED: {
             msg_final = false;
+            const int64_t boxes = long_steps(n);
             for (int64_t i = 0; i < n;) {
-                const int k = steps_of(n - i);
+                const int k = i < boxes ? deep_steps() : (two_step && n - i >= 2 ? 2 : 1);
                 od_status os = fused_pass(st, parity, iters, k, i + k == n);
                 if (os != OD_OK) return os;
                 parity ^= 1;

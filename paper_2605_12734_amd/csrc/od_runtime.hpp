@@ -185,6 +185,7 @@ struct Grid {
     od_status fused_pass(hipStream_t s2, int par, int64_t step, int k, bool last);
     od_status upload_tiles();                      // tile descriptors (and two-step lines) to the device
     int64_t bytes_per_pass() const;
+    int64_t long_steps(int64_t n);                 // iterations of n that run over boxes
     od_status graph_run(int64_t n);
     od_status persistent_run(int64_t n);
     od_status msgdriven_run(int64_t n, bool any_count = false);   // any_count: boxes however few the passes

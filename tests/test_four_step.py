@@ -294,6 +294,43 @@ def test_sums_below_the_quick_division_beside_huge_ones(scale):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("exec_,dims,n", [("fused", 3, 3), ("fused", 3, 4), ("fused", 3, 7), ("fused", 3, 8), ("fused", 3, 12),
+                                          ("fused", 3, 20), ("fused", 2, 8), ("fused", 2, 12), ("fused", 2, 16),
+                                          ("persistent", 3, 4), ("persistent", 3, 8), ("persistent", 3, 12)])
+def test_replays_of_a_captured_count_go_on(exec_, dims, n):
+    # each replay continues where the last ended: the passes of the count keep
+    # the parity they have by pairs, whatever part of it runs over boxes
+    import torch
+
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        if dims == 3:
+            g = od.Grid((64, 64, 24), odf=8, dtype="f64", exec=exec_, seed=5, bc=BC6, hints=1, stream=s)
+        else:
+            g = od.Grid2D((300, 64), odf=4, dtype="f64", exec=exec_, seed=5, hints=1, stream=s)
+    try:
+        s.synchronize()
+        g.iterate(8)   # (the first launches are not in the graph)
+        g.residual()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=s, capture_error_mode="relaxed"):
+            g.iterate(n)
+        assert g.pass_info()["steps"] == (4 if dims == 3 else 8)
+        for i in range(1, 4):
+            with torch.cuda.stream(s):
+                graph.replay()
+            s.synchronize()
+            if dims == 3:
+                want, _, r = oracle.solve((64, 64, 24), np.float64, seed=5, iters=8 + i * n, bc=BC6)
+            else:
+                want, _, r = oracle.solve2d((300, 64), np.float64, 5, 8 + i * n, (1.0, 0.0, 0.0, 0.0))
+            _same(g.read(), want)
+            assert g.residual() == r
+    finally:
+        g.close()
+
+
+@pytest.mark.gpu
 def test_a_long_axis_does_not_make_creation_long():
     # the table of planes behind a chare's: quadratic work on it took 0.36 s for a
     # chare of 60000 planes, so 16 s here, what is linear takes hundredths
