@@ -62,10 +62,15 @@ int per_cu(int dtype_bytes, int rows) { return (dtype_bytes == 8 ? 1 : 2) * (row
 // leave less of a shared chip to the others, each box computing eight more.  ms
 // for 600 iterations checked every 10, without a least / 8 / 12 / 16 planes: 16
 // solves of 32-48 cells an edge 42 / 11.7 / 12.0 / 13.8, of 32-256 120 / 80 / 75 / 70;
-// fp64 64^3 alone 7.2 / 10.7 / 13.4 / 14.6, 128^3 10.4 / 10.9 / 12.4 / 14.5.  At 12 a
-// solve of one-step tasks that is checked at every iteration was quicker (64^3 20.7
-// against 23.2), at 8 none is.
-constexpr int64_t kServePlanes = 8;
+// fp64 64^3 alone 7.2 / 10.7 / 13.4 / 14.6, 128^3 10.4 / 10.9 / 12.4 / 14.5.
+// A solve checked at every iteration has passes of one step, whose boxes need a
+// ring of one cell and may be cut finer in a tiny solve.  ms for 200 iterations by
+// tiles / with a ring of four and 8 planes / so: 64 solves of 32-64 cells an edge 37 /
+// 43 / 35, of 48-100 79 / 89 / 77, 32 of 64-256 198 / 192 / 181; fp64 alone 8^3 2.5 / 3.9 /
+// 3.3, 16^3 3.1 / 3.9 / 3.3, 64^3 6.9 / 6.0 / 6.7, 200^3 14.1 / 10.4 / 10.3.
+int64_t serve_planes(int32_t ring, int64_t n) {
+    return ring > 1 ? 8 : (n <= 24 ? std::max<int64_t>(4, n / 4) : 10);
+}
 
 struct Cut {
     int32_t start, o0, o1;
@@ -74,18 +79,18 @@ struct Cut {
 // Boxes along an axis of n items (vectors, or rows) of which the lanes cover L:
 // item i holds cells(i + 1) - cells(i) cells.  A box writes [o0, o1) from the
 // lanes [start, start + L); between what it writes and lanes with more grid
-// behind them lie at least kDeepSteps cells.
+// behind them lie at least `ring` cells.
 template <typename Cells>
-std::vector<Cut> cut_axis(int32_t n, int32_t L, Cells cells) {
+std::vector<Cut> cut_axis(int32_t n, int32_t L, int32_t ring, Cells cells) {
     auto left = [&](int32_t o) {   // first lane needed to write from o on
         int32_t s = o;
-        while (s > 0 && cells(o) - cells(s) < kDeepSteps) --s;
+        while (s > 0 && cells(o) - cells(s) < ring) --s;
         return s;
     };
     auto right = [&](int32_t s) {   // items a box that starts at s can write up to
         if (s + L >= n) return n;
         int32_t o = s + L;
-        while (o > s && cells(s + L) - cells(o) < kDeepSteps) --o;
+        while (o > s && cells(s + L) - cells(o) < ring) --o;
         return o;
     };
     auto build = [&](int32_t most) {   // boxes of at most `most` items each
@@ -137,7 +142,7 @@ std::vector<DeepTile> xcd_runs(const std::vector<DeepTile>& list) {
 
 namespace {
 
-DeepPlan plan_boxes(const Plan& p, int dtype_bytes, bool serve, bool tasks, int64_t* pass_cost) {
+DeepPlan plan_boxes(const Plan& p, int dtype_bytes, bool serve, bool tasks, int32_t ring, int64_t* pass_cost) {
     DeepPlan out;
     const int32_t VX = 16 / dtype_bytes;
     if (p.multires || p.chares.empty()) return out;
@@ -173,8 +178,8 @@ DeepPlan plan_boxes(const Plan& p, int dtype_bytes, bool serve, bool tasks, int6
         shape.waves = d.waves;
         deep_shape(dtype_bytes, shape, &lx, &ey);
         if (rows > 1 && p.n[1] < ey) continue;   // the last row ends a strip
-        const std::vector<Cut> ax = cut_axis(nv, lx, [&](int32_t i) { return d.vx[(size_t)i]; }),
-                               ay = cut_axis((int32_t)p.n[1], ey, [](int32_t i) { return i; });
+        const std::vector<Cut> ax = cut_axis(nv, lx, ring, [&](int32_t i) { return d.vx[(size_t)i]; }),
+                               ay = cut_axis((int32_t)p.n[1], ey, ring, [](int32_t i) { return i; });
         if (ax.empty() || ay.empty()) continue;
         // z: as many pieces as fill the chip's 256 CUs in the fewest plane
         // iterations, a piece of l planes taking l + 8
@@ -182,8 +187,8 @@ DeepPlan plan_boxes(const Plan& p, int dtype_bytes, bool serve, bool tasks, int6
                       slots = 256 * (serve ? 1 : per_cu(dtype_bytes, rows));
         for (int64_t k = 1; k <= p.n[2] && (!serve || xy * k <= kServeBoxes); ++k) {
             const int64_t len = (p.n[2] + k - 1) / k;
-            if (serve && k > 1 && len < kServePlanes) break;
-            const int64_t cost = ((xy * k + slots - 1) / slots) * (len + 2 * kDeepSteps) * plane_cost(dtype_bytes, rows) +
+            if (serve && k > 1 && len < serve_planes(ring, p.n[2])) break;
+            const int64_t cost = ((xy * k + slots - 1) / slots) * (len + 2 * ring) * plane_cost(dtype_bytes, rows) +
                                  (tasks ? xy * k * task_cost(dtype_bytes) + (rows > 1 ? kTaskRows : 0) : 0);
             if (cost < best) {
                 best = cost;
@@ -248,7 +253,7 @@ bool tiles_quicker(const Plan& p, int dtype_bytes, const DeepPlan& d, int64_t co
 
 DeepPlan deep_plan(const Plan& p, int dtype_bytes, od_exec exec, int tile_steps) {
     int64_t cost = 0;
-    DeepPlan d = plan_boxes(p, dtype_bytes, false, exec == OD_MSGDRIVEN, &cost);
+    DeepPlan d = plan_boxes(p, dtype_bytes, false, exec == OD_MSGDRIVEN, kDeepSteps, &cost);
     if (d.tiles.empty()) return d;
     d.by_tiles = tiles_quicker(p, dtype_bytes, d, cost, exec, tile_steps);
     if (exec == OD_MSGDRIVEN) {
@@ -268,7 +273,9 @@ DeepPlan deep_plan(const Plan& p, int dtype_bytes, od_exec exec, int tile_steps)
     }
     return d;
 }
-DeepPlan deep_plan_serve(const Plan& p, int dtype_bytes) { return plan_boxes(p, dtype_bytes, true, false, nullptr); }
+DeepPlan deep_plan_serve(const Plan& p, int dtype_bytes, int steps) {
+    return plan_boxes(p, dtype_bytes, true, false, steps, nullptr);
+}
 
 std::vector<int32_t> deep_tables(const Plan& p, const DeepPlan& d, size_t at[5]) {
     std::vector<int32_t> tab(d.vx);
@@ -292,13 +299,13 @@ std::vector<int32_t> deep_tables(const Plan& p, const DeepPlan& d, size_t at[5])
     return tab;
 }
 
-void deep_deps(const DeepPlan& d, int dtype_bytes, std::vector<int32_t>& ptr, std::vector<int32_t>& idx) {
+void deep_deps(const DeepPlan& d, int dtype_bytes, std::vector<int32_t>& ptr, std::vector<int32_t>& idx, int steps) {
     const std::vector<DeepTile>& t = d.tiles;
     int ex, ey;
     deep_shape(dtype_bytes, d, &ex, &ey);
     auto reads = [&](const DeepTile& a, const DeepTile& b) {
-        return b.wo0 < a.ws + ex && a.ws < b.wo1 && b.yo0 < a.ys + ey && a.ys < b.yo1 && b.z0 < a.z1 + kDeepSteps &&
-               a.z0 - kDeepSteps < b.z1;
+        return b.wo0 < a.ws + ex && a.ws < b.wo1 && b.yo0 < a.ys + ey && a.ys < b.yo1 && b.z0 < a.z1 + steps &&
+               a.z0 - steps < b.z1;
     };
     // boxes by their place on each axis; along an axis only cuts whose lanes and
     // written cells together meet can be related
@@ -312,7 +319,7 @@ void deep_deps(const DeepPlan& d, int dtype_bytes, std::vector<int32_t>& ptr, st
         const DeepTile& b = t[i];
         cuts[0][b.wo0] = {std::min(b.ws, b.wo0), std::max(b.ws + ex, b.wo1)};
         cuts[1][b.yo0] = {std::min(b.ys, b.yo0), std::max(b.ys + ey, b.yo1)};
-        cuts[2][b.z0] = {b.z0 - kDeepSteps, b.z1 + kDeepSteps};
+        cuts[2][b.z0] = {b.z0 - steps, b.z1 + steps};
         at[{b.wo0, b.yo0, b.z0}] = (int32_t)i;
     }
     std::array<std::map<int32_t, std::vector<int32_t>>, 3> near;

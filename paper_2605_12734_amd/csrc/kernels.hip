@@ -1981,7 +1981,7 @@ k_deep_msg(MsgArgs a, DeepMap g, const DeepTile* __restrict__ tiles) {
 // are in flight.  ms against tasks of one step: 16 solves of 32-256 cells an edge,
 // mixed types, 600 iterations checked every 10 80 / 168, of 32-48 11.7 / 35.1; one
 // of 256^3 fp64 24.2 / 54.0, of 64^3 10.7 / 20.1.  Checked at every iteration, where
-// each pass is one step: 205 / 211, 22.6 / 36.4, 57.8 / 60.9, 17.5 / 20.7.  All
+// each pass is one step: 188 / 211, 21.0 / 36.6, 57.6 / 60.6, 19.4 / 20.3.  All
 // variants in one kernel cost 244 bytes of scratch per lane and 281 spilled SGPRs.
 constexpr size_t serve_lds() {
     size_t m = sizeof(typename Deep<double, 4, kServeWaves>::Lds);
