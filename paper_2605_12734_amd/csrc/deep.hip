@@ -58,16 +58,22 @@ k_deep(DeepMap g, const DeepTile* __restrict__ tiles, int parity, unsigned long 
 // levels), LDS at one.
 int per_cu(int dtype_bytes, int rows) { return (dtype_bytes == 8 ? 1 : 2) * (rows == 1 ? 2 : 1); }
 
+// Planes a box reads beyond what it writes, on either side: passes of more than
+// one step march as four do (the levels not needed copy).
+int32_t pass_planes(int32_t ring) { return ring == 1 ? 1 : kDeepSteps; }
+
 // Planes of a served solve's box at least: fewer make a solve alone quicker and
 // leave less of a shared chip to the others, each box computing eight more.  ms
 // for 600 iterations checked every 10, without a least / 8 / 12 / 16 planes: 16
 // solves of 32-48 cells an edge 42 / 11.7 / 12.0 / 13.8, of 32-256 120 / 80 / 75 / 70;
 // fp64 64^3 alone 7.2 / 10.7 / 13.4 / 14.6, 128^3 10.4 / 10.9 / 12.4 / 14.5.
-// A solve checked at every iteration has passes of one step, whose boxes need a
-// ring of one cell and may be cut finer in a tiny solve.  ms for 200 iterations by
-// tiles / with a ring of four and 8 planes / so: 64 solves of 32-64 cells an edge 37 /
-// 43 / 35, of 48-100 79 / 89 / 77, 32 of 64-256 198 / 192 / 181; fp64 alone 8^3 2.5 / 3.9 /
-// 3.3, 16^3 3.1 / 3.9 / 3.3, 64^3 6.9 / 6.0 / 6.7, 200^3 14.1 / 10.4 / 10.3.
+// A solve checked at every one to three iterations has passes of as many steps,
+// whose boxes need a ring of no more cells; with one step they may also be cut finer
+// in a tiny solve.  ms for 200 iterations checked at each, by tiles / with a ring of
+// four and 8 planes / so: 64 solves of 32-64 cells an edge 37 / 43 / 37, of 48-100 79 / 88 /
+// 78, 32 of 64-256 198 / 192 / 179; fp64 alone 8^3 2.5 / 3.9 / 3.3, 16^3 3.1 / 3.9 / 3.3,
+// 64^3 6.9 / 6.0 / 6.7, 200^3 14.1 / 10.4 / 10.4.  At every second: 64 of 32-48 30.9 /
+// 29.0 / 25.3, of 48-100 64.1 / 67.9 / 66.8, 8^3 alone 2.4 / 3.0 / 3.1.
 int64_t serve_planes(int32_t ring, int64_t n) {
     return ring > 1 ? 8 : (n <= 24 ? std::max<int64_t>(4, n / 4) : 10);
 }
@@ -188,7 +194,7 @@ DeepPlan plan_boxes(const Plan& p, int dtype_bytes, bool serve, bool tasks, int3
         for (int64_t k = 1; k <= p.n[2] && (!serve || xy * k <= kServeBoxes); ++k) {
             const int64_t len = (p.n[2] + k - 1) / k;
             if (serve && k > 1 && len < serve_planes(ring, p.n[2])) break;
-            const int64_t cost = ((xy * k + slots - 1) / slots) * (len + 2 * ring) * plane_cost(dtype_bytes, rows) +
+            const int64_t cost = ((xy * k + slots - 1) / slots) * (len + 2 * pass_planes(ring)) * plane_cost(dtype_bytes, rows) +
                                  (tasks ? xy * k * task_cost(dtype_bytes) + (rows > 1 ? kTaskRows : 0) : 0);
             if (cost < best) {
                 best = cost;
@@ -273,8 +279,8 @@ DeepPlan deep_plan(const Plan& p, int dtype_bytes, od_exec exec, int tile_steps)
     }
     return d;
 }
-DeepPlan deep_plan_serve(const Plan& p, int dtype_bytes, int steps) {
-    return plan_boxes(p, dtype_bytes, true, false, steps, nullptr);
+DeepPlan deep_plan_serve(const Plan& p, int dtype_bytes, int ring) {
+    return plan_boxes(p, dtype_bytes, true, false, ring, nullptr);
 }
 
 std::vector<int32_t> deep_tables(const Plan& p, const DeepPlan& d, size_t at[5]) {
@@ -299,7 +305,8 @@ std::vector<int32_t> deep_tables(const Plan& p, const DeepPlan& d, size_t at[5])
     return tab;
 }
 
-void deep_deps(const DeepPlan& d, int dtype_bytes, std::vector<int32_t>& ptr, std::vector<int32_t>& idx, int steps) {
+void deep_deps(const DeepPlan& d, int dtype_bytes, std::vector<int32_t>& ptr, std::vector<int32_t>& idx, int ring) {
+    const int32_t steps = pass_planes(ring);
     const std::vector<DeepTile>& t = d.tiles;
     int ex, ey;
     deep_shape(dtype_bytes, d, &ex, &ey);

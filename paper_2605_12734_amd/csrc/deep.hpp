@@ -60,8 +60,9 @@ DeepPlan deep_plan(const Plan& p, int dtype_bytes, od_exec exec, int tile_steps)
 // The boxes of a served solve: workgroups of kServeWaves waves in either type,
 // at most kServeBoxes of them (a slot's dependency lists hold 26 for each).
 constexpr int kServeWaves = 8, kServeBoxes = 2048;
-// steps: of its passes at most (1: checked at every iteration).
-DeepPlan deep_plan_serve(const Plan& p, int dtype_bytes, int steps);
+// ring: cells beside what is written that its lanes cover along x and y, the
+// steps of its longest pass.
+DeepPlan deep_plan_serve(const Plan& p, int dtype_bytes, int ring);
 // vx, vi, iy, iz and zn of DeepMap one after another; `at`: where each begins.
 std::vector<int32_t> deep_tables(const Plan& p, const DeepPlan& d, size_t at[5]);
 
@@ -117,6 +118,6 @@ hipError_t launch_fill_i32(hipStream_t st, int32_t* p, int32_t n, int32_t v);
 // For each box the boxes whose written cells its lanes read, and those that
 // read its own (CSR, ascending, symmetric).
 void deep_deps(const DeepPlan& d, int dtype_bytes, std::vector<int32_t>& ptr, std::vector<int32_t>& idx,
-               int steps = kDeepSteps);
+               int ring = kDeepSteps);
 
 }  // namespace od

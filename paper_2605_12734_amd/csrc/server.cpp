@@ -641,10 +641,10 @@ od_status plan_request(const od_request* r, std::unique_ptr<od::Grid>& G, od::Re
         G->dep_idx.size() > (size_t)od::kMaxDeps)
         return fail(OD_EINVAL, "request too large for a serving slot (tiles/blocks/dependencies)");
     if (R) {
-        // (a solve checked at every iteration has passes of one step)
-        const int steps = r->check_every == 1 ? 1 : od::kDeepSteps;
-        R->boxes = od::deep_plan_serve(G->plan, G->s, steps);
-        od::deep_deps(R->boxes, G->s, R->dep_ptr, R->dep_idx, steps);
+        // (passes end at the checks)
+        const int ring = r->check_every > 0 ? std::min<int>(r->check_every, od::kDeepSteps) : od::kDeepSteps;
+        R->boxes = od::deep_plan_serve(G->plan, G->s, ring);
+        od::deep_deps(R->boxes, G->s, R->dep_ptr, R->dep_idx, ring);
         if (R->boxes.tiles.empty() || R->boxes.tiles.size() > (size_t)od::kServeBoxes ||
             R->dep_idx.size() > (size_t)od::kMaxDeps)
             return fail(OD_EINVAL, "request too large for a serving slot (boxes)");

@@ -435,12 +435,14 @@ def test_served_passes_match_oracle(dtype, check_every):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype", ["f64", "f32"])
-def test_served_one_step_passes_at_the_edges_of_their_boxes(dtype):
-    # checked at every iteration: passes of one step over boxes with a ring of one
-    # cell, of 62 and 14 rows, 62 cells along x and pieces of 4 to 10 planes
+@pytest.mark.parametrize("check_every", [1, 2, 3])
+def test_served_short_passes_at_the_edges_of_their_boxes(dtype, check_every):
+    # passes of up to one, two or three steps over boxes with a ring of as many
+    # cells: of 62 to 58 and 14 to 10 rows, checked at every iteration also with
+    # pieces of 4 to 10 planes
     from paper_2605_12734_amd.serving import Server
 
-    reqs = [dict(n=n, dtype=dtype, odf=odf, tol=tol, max_iters=iters, check_every=1, seed=n)
+    reqs = [dict(n=n, dtype=dtype, odf=odf, tol=tol, max_iters=iters, check_every=check_every, seed=n)
             for n, odf, tol, iters in [(2, 1, 0.0, 3), (8, 8, 0.0, 9), (14, 1, 0.0, 5), (15, 1, 0.0, 6), (16, 8, 0.0, 17),
                                        (24, 27, 0.0, 8), (25, 1, 0.0, 8), (29, 8, 0.0, 7), (62, 1, 0.0, 6),
                                        (63, 1, 2e-3, 40), (125, 27, 0.0, 4), (126, 1, 0.0, 5), (190, 64, 0.0, 3)]]
@@ -448,6 +450,7 @@ def test_served_one_step_passes_at_the_edges_of_their_boxes(dtype):
         tickets = [srv.submit(**q) for q in reqs]
         for t, q in zip(tickets, reqs):
             res, field = srv.wait(t), srv.fetch(t)
-            want, it, r = oracle.solve(q["n"], DT[dtype], seed=q["seed"], iters=q["max_iters"], tol=q["tol"], check_every=1)
+            want, it, r = oracle.solve(q["n"], DT[dtype], seed=q["seed"], iters=q["max_iters"], tol=q["tol"],
+                                       check_every=check_every)
             assert (res["iters"], res["residual"]) == (it, r), q
             assert np.array_equal(field, want), q
