@@ -27,9 +27,10 @@ int64_t plane_cost(int dtype_bytes, int rows) {
 // iteration with nothing added and so: fp32 300 x 300 x 4 11.8 / 5.2 (888 and 222
 // boxes; pairs 8.1), 250 x 250 x 12 13.9 / 8.6 (pairs 11.9), 225 x 391 x 6 9.3 / 7.5
 // (pairs 8.3), 128^3 14.0 / 12.2, 64^3 7.1 / 5.7; fp64 64^3 7.7 / 6.0, 512^3 the same
-// boxes.  Twice as much in fp64 took 237 x 747 x 6 from 11.2 to 14.3.
+// boxes.  Twice as much in fp64 took 237 x 747 x 6 from 11.2 to 14.3, a start-up of
+// 6 us for four rows 140^3 from 11.6 (252 boxes) to 12.1 (510 of one row).
 int64_t task_cost(int dtype_bytes) { return dtype_bytes == 8 ? 1 : 2; }
-constexpr int64_t kTaskRows = 600;
+constexpr int64_t kTaskRows = 200;
 
 template <typename T, int R, bool RAG>
 __global__ void __launch_bounds__(deep_waves((int)sizeof(T)) * 64) OD_DEEP_OCC(R)
@@ -241,7 +242,7 @@ double tile_time(const Plan& p, int dtype_bytes, od_exec exec, double full) {
     const double rate = row ? (f64 ? 0.15 + 0.33 * f : 0.19 + 0.18 * f) : (f64 ? 0.24 : 0.29) + full * f;
     // (the cooperative forms' barrier or queue, per pass over the tiles)
     const double coop = row ? (exec == OD_FUSED || exec == OD_GRAPH ? 1.0 : 1.08)
-                            : (exec == OD_PERSISTENT ? 1.13 : (exec == OD_MSGDRIVEN ? (f64 ? 1.3 : 1.5) : 1.0));
+                            : (exec == OD_PERSISTENT ? 1.13 : (exec == OD_MSGDRIVEN ? (f64 ? 1.25 : 1.5) : 1.0));
     return coop * std::max(lat, n * (tz + 10) * rate);
 }
 
